@@ -124,7 +124,12 @@ int rewl_init(const rewl_params* params, int32_t n_instances,
 int rewl_run_sweeps(rewl_ctx* ctx, int64_t flips);
 
 /* Launch shape of the sweep.  Walkers are grouped by kernel class:
- * 0 = Ising L <= 32, 1 = Ising 32 < L <= 64, 2 = Potts.  For class cls (-1:
+ * 0 = Ising L <= 32, 1 = Ising 32 < L <= 64, 2 = Potts.  A class is swept
+ * with one lane per walker, in the shape below, or with one wavefront per
+ * walker (walkers_per_group = 1; also the default, every argument left at
+ * its default, of a batch of at most 8192 walkers): then the other
+ * arguments matter only to a fused launch (rewl_set_batching), which always
+ * takes the lane form.  For class cls (-1:
  * all classes) keep page_bins ln g bins of each walker's window in LDS (the
  * rest stays in device memory; the page follows the walker) and put
  * walkers_per_group walkers in each workgroup; 0 picks the default (the
@@ -166,8 +171,8 @@ int rewl_set_launch(rewl_ctx* ctx, int32_t cls, int32_t page_bins, int32_t walke
  * settings), HIP. */
 int rewl_set_batching(rewl_ctx* ctx, int32_t fused, int32_t splits, int32_t order, int32_t* out);
 
-/* Chooses the launch shape of every class and the batching
- * (rewl_set_batching) by timing sweeps of `flips` attempts (median of
+/* Chooses the launch shape of every class (lanes or wavefronts per walker
+ * among them) and the batching (rewl_set_batching) by timing sweeps of `flips` attempts (median of
  * `repeats` sweeps per candidate) on the whole batch: classes sweep side by
  * side and share the compute units, so a candidate replaces the best plan
  * only when the batch is faster with it.  Candidates are first one page

@@ -18,7 +18,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librewl.so")
 ALU_LIB = os.path.join(HERE, "libalurate.so")
-SOURCES = ["rewl_sweep.hip", "rewl_kernels.hip", "rewl_api.cpp", "rewl_plan.cpp"]
+SOURCES = ["rewl_sweep.hip", "rewl_wave.hip", "rewl_kernels.hip", "rewl_api.cpp", "rewl_plan.cpp"]
 ARCH = os.environ.get("REWL_OFFLOAD_ARCH", "gfx950")
 
 

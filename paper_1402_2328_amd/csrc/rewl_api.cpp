@@ -216,7 +216,9 @@ int build_layout(const rewl_params* params, int32_t n, const int32_t* wlo, const
   return REWL_OK;
 }
 
-// Sweep launch plan, per kernel class: walkers per workgroup (G, one
+// Sweep launch plan, per kernel class: either one wavefront per walker
+// (wave; rewl_wave.hip), or one lane per walker:
+// walkers per workgroup (G, one
 // wavefront), ln g page slots (P, a power of two), LDS bytes and the class's
 // slice of the workgroup table.  Per lane a class needs 4 * lat_words +
 // 12 * P bytes of LDS.  The page must hold bin +- 2D (D = 4 for q >= 3
@@ -228,6 +230,9 @@ struct ClassPlan {
   int32_t prod = 0;  // RNG producer wavefront per workgroup
   int32_t nib = 0;   // Potts spins: 0 bytes, 1 nibbles with the neighbour table, 2 nibbles
   size_t lds_bytes = 0;
+  // one wavefront per walker instead of the shape above, which a fused
+  // launch of the batch still takes
+  int32_t wave = 0;
 };
 // Batch-level choices: fused = every class in one launch (one LDS size, one
 // RNG-producer setting) rather than one launch per class on forked streams;
@@ -276,10 +281,15 @@ int n_compute_units() {
   return 256;  // MI355X
 }
 
+// Spin bytes of a class's largest lattice in the wavefront-per-walker form.
+int wave_lat_bytes(const Layout& Lo, int cls) { return (int)align_up((size_t)Lo.n_max[cls], 16); }
+
 int plan_class(const Layout& Lo, int cls, int lds_budget, int page_req, int g_req, int prod_req,
                int nib_req, ClassPlan& cp) {
   cp = ClassPlan();
   if (Lo.walkers[cls] == 0) return REWL_OK;
+  const bool any_shape = page_req == 0 && g_req == 0 && prod_req < 0 && nib_req < 0;
+  cp.wave = g_req == 1 || (any_shape && Lo.n_slots <= kWaveMaxWalkers);
   // Potts nibbles halve the lattice and so raise the workgroups per compute
   // unit, at a little extra latency per attempt: by default when the class
   // has more workgroups than the GPU has compute units
@@ -328,13 +338,14 @@ void fill_table(const Layout& Lo, LaunchPlan& pl) {
   for (int cls = 0; cls < 3; ++cls) {
     const ClassPlan& cp = pl.cls[cls];
     if (cp.G <= 0) continue;
+    const int G = cp.wave && !pl.fused ? 1 : cp.G;
     for (const InstDesc& I : Lo.inst) {
       if (class_of(I) != cls) continue;
-      for (int s0 = 0; s0 < I.W; s0 += cp.G) {
+      for (int s0 = 0; s0 < I.W; s0 += G) {
         WgDesc d{};
         d.inst = I.inst;
         d.slot_first = I.slot_base + s0;
-        d.count = std::min(cp.G, I.W - s0);
+        d.count = std::min(G, I.W - s0);
         d.cls = cls;
         per[cls].push_back(d);
       }
@@ -513,7 +524,9 @@ hipError_t enqueue_sweeps(rewl_ctx* c, int64_t flips) {
     hipStream_t s = (fork && i > 0) ? c->side[i - 1] : c->stream;
     for (int k = 0; k < parts && e == hipSuccess; ++k) {
       const int64_t f = part_flips(flips, parts, k);
-      if (f > 0) e = launch_sweep_class(c->P, cls, sh, cp.count, f, cp.lds_bytes, cp.prod != 0, s);
+      if (f <= 0) continue;
+      if (cp.wave) e = launch_sweep_wave(c->P, cls, cp.offset, cp.count, wave_lat_bytes(c->lo, cls), f, s);
+      else e = launch_sweep_class(c->P, cls, sh, cp.count, f, cp.lds_bytes, cp.prod != 0, s);
     }
   }
   if (fork) {
@@ -677,12 +690,13 @@ int install_plan(rewl_ctx* c, const LaunchPlan& pl) {
   return rc;
 }
 
-void plan_out(const LaunchPlan& pl, int32_t* out) {
+void plan_out(const Layout& Lo, const LaunchPlan& pl, int32_t* out) {
   if (!out) return;
   for (int cls = 0; cls < 3; ++cls) {
+    const bool wave = pl.cls[cls].wave && !pl.fused;
     out[6 * cls + 0] = pl.cls[cls].P;
-    out[6 * cls + 1] = pl.cls[cls].G;
-    out[6 * cls + 2] = (int32_t)pl.cls[cls].lds_bytes;
+    out[6 * cls + 1] = wave ? 1 : pl.cls[cls].G;
+    out[6 * cls + 2] = wave ? 2 * wave_lat_bytes(Lo, cls) : (int32_t)pl.cls[cls].lds_bytes;
     out[6 * cls + 3] = pl.cls[cls].count;
     out[6 * cls + 4] = pl.cls[cls].prod;
     out[6 * cls + 5] = pl.cls[cls].nib;
@@ -713,7 +727,7 @@ int rewl_set_launch(rewl_ctx* c, int32_t cls, int32_t page_bins, int32_t walkers
   if (pl.fused && !fusable(c->lo, pl)) pl.fused = 0;
   fill_table(c->lo, pl);
   int rc = install_plan(c, pl);
-  if (!rc) plan_out(c->plan, out);
+  if (!rc) plan_out(c->lo, c->plan, out);
   return rc;
 }
 
@@ -727,7 +741,7 @@ int rewl_set_batching(rewl_ctx* c, int32_t fused, int32_t splits, int32_t order,
   if (fused && !fusable(c->lo, pl)) return REWL_E_INVAL;
   fill_table(c->lo, pl);
   int rc = install_plan(c, pl);
-  if (!rc) plan_out(c->plan, out);
+  if (!rc) plan_out(c->lo, c->plan, out);
   return rc;
 }
 
@@ -834,6 +848,22 @@ int rewl_autotune(rewl_ctx* c, int64_t flips, int32_t repeats, int32_t* out) {
           rc = consider(pl);
         }
       }
+  // One wavefront per walker in every class, unless there are far too many
+  // walkers for it to pay.
+  auto as_wave = [&](LaunchPlan& pl, int cls) {
+    if (L.walkers[cls] == 0) return true;
+    if (plan_class(L, cls, budget, 0, 0, -1, -1, pl.cls[cls])) return false;
+    pl.cls[cls].wave = 1;
+    return true;
+  };
+  const bool try_wave = L.n_slots <= 4 * kWaveMaxWalkers;
+  if (try_wave && !rc) {
+    LaunchPlan pl = c->plan;
+    pl.fused = 0;
+    pl.splits = 1;
+    pl.order = 0;
+    if (as_wave(pl, 0) && as_wave(pl, 1) && as_wave(pl, 2)) rc = consider(pl);
+  }
   // Then coordinate descent, two passes over the classes: every shape of
   // one class with the others at their best so far (a fused plan stays
   // fused while the producer settings agree).
@@ -843,6 +873,10 @@ int rewl_autotune(rewl_ctx* c, int64_t flips, int32_t repeats, int32_t* out) {
     int pmin, pmax;
     page_range(L, cls, pmin, pmax);
     const LaunchPlan from = best();
+    if (try_wave && classes > 1 && !from.fused) {
+      LaunchPlan pl = from;
+      if (as_wave(pl, cls)) rc = consider(pl);
+    }
     for (int p = pmin; p <= pmax && !rc; p <<= 1)
       for (int prod = 0; prod < 2 && !rc; ++prod)
         for (int nib = 0; nib < (cls == 2 && L.nib_ok[cls] ? 3 : 1) && !rc; ++nib) {
@@ -933,7 +967,7 @@ int rewl_autotune(rewl_ctx* c, int64_t flips, int32_t repeats, int32_t* out) {
   if (!rc) rc = hip_rc(hipMemcpyAsync(c->ws, snap.data(), L.total, hipMemcpyHostToDevice, c->stream));
   if (!rc) rc = install_plan(c, chosen);
   if (!rc) rc = sync(c);
-  if (!rc) plan_out(c->plan, out);
+  if (!rc) plan_out(c->lo, c->plan, out);
   return rc;
 }
 

@@ -16,6 +16,15 @@ constexpr int kMaxWalkersPerWindow = 64;
 constexpr int kMaxL = 64;
 constexpr int kSweepWave = 64;    // walkers' wavefront of a sweep workgroup
 constexpr int kRngChunk = 16;     // attempts per hand-over of the RNG producer
+// Batches of at most this many walkers are swept with one wavefront per
+// walker by default, larger ones with one lane per walker.  A wavefront
+// makes an attempt in 130 to 210 ns while no SIMD holds two of them (1024
+// walkers) and the SIMDs fill up from there; a lane takes 440 to 620 ns in
+// its default shape however many there are.  At 8192 walkers, wavefronts
+// against lanes per attempt: Ising L = 32 397 against 442 ns, L = 64 455
+// against 606, q = 10 Potts L = 20 492 against 557 (two-float 546 against
+// 621); at 16384 723 against 445, 772 against 613, 861 against 560.
+constexpr int kWaveMaxWalkers = 8192;
 constexpr int kMaxTemps = 16384;  // rewl_thermo temperatures per call
 // Allocation-free jackknife: doubles of the per-GPU device array that holds
 // one instance's window representatives and (m + 2) x nbins leave-one-out
@@ -116,6 +125,11 @@ hipError_t launch_init(const DevPtrs& P, hipStream_t s);
 // producer: a second wavefront per workgroup computes the random numbers.
 hipError_t launch_sweep_class(const DevPtrs& P, int cls, SweepShape sh, int32_t n_wg, int64_t flips,
                               size_t lds_bytes, bool producer, hipStream_t s);
+// One wavefront per walker: n_wg entries of the table from wg_offset, each of
+// one walker of class cls; lat_bytes: spins of the class's largest lattice,
+// rounded up to 16.
+hipError_t launch_sweep_wave(const DevPtrs& P, int cls, int32_t wg_offset, int32_t n_wg,
+                             int32_t lat_bytes, int64_t flips, hipStream_t s);
 // Every class in one launch (k_sweep_fused): n_wg entries of the table from
 // 0, class shapes sh[0..2], lds_bytes of the largest class.
 hipError_t launch_sweep_fused(const DevPtrs& P, const SweepShape sh[3], int32_t n_wg, int64_t flips,
