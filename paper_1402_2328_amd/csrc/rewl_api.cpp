@@ -650,7 +650,7 @@ int rewl_init(const rewl_params* params, int32_t n, const int32_t* win_lo, const
                        hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = prepare_sweep_lds((size_t)lds_budget_bytes());
   if (e == hipSuccess) e = scratch_address(&c->scratch);
-  if (e == hipSuccess) e = launch_init(c->P, c->stream);
+  if (e == hipSuccess) e = launch_init(c->P, std::max({wave_lat_bytes(L, 0), wave_lat_bytes(L, 1), wave_lat_bytes(L, 2)}), c->stream);
   // host vectors above are pageable; make sure the copies finished
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e == hipSuccess) e = create_side_streams(c);

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "rewl_internal.h"
+
 namespace rewl {
 
 // x ^ y ^ z in one instruction (gfx950 three-input bitwise op, truth table
@@ -47,6 +49,13 @@ __device__ __forceinline__ uint4 philox_rounds(uint4 c, uint32_t k0, uint32_t k1
                    xor3((uint32_t)(p0 >> 32), c.w, kr1), (uint32_t)p0);
   }
   return c;
+}
+
+// Philox block `idx` of an instance's stream `tag`; w2 is the third counter
+// word (the walker's slot, or what the stream says).
+__device__ __forceinline__ uint4 draw(const InstDesc& I, uint64_t idx, uint32_t w2, uint32_t tag) {
+  return philox10(make_uint4((uint32_t)idx, (uint32_t)(idx >> 32), w2, tag | ((uint32_t)I.inst << 8)),
+                  I.key0, I.key1);
 }
 
 // Fused multiply-add with all three operands in vector registers.  Written

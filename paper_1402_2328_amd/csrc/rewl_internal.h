@@ -119,7 +119,8 @@ struct SweepShape {
 };
 
 // Launchers (kernels TU).  All enqueue on `s` and return the launch status.
-hipError_t launch_init(const DevPtrs& P, hipStream_t s);
+// lat_bytes: spins of the batch's largest lattice, rounded up to 16.
+hipError_t launch_init(const DevPtrs& P, int32_t lat_bytes, hipStream_t s);
 // One sweep kernel class: 0 = Ising L <= 32, 1 = Ising 32 < L <= 64,
 // 2 = Potts; n_wg workgroups starting at sh.wg_offset of the table;
 // producer: a second wavefront per workgroup computes the random numbers.

@@ -1,5 +1,5 @@
 // REWL kernels for gfx950 (MI355X), everything except the sweep (which is
-// in rewl_sweep.hip).
+// in rewl_sweep.hip and rewl_wave.hip) and the initialisation (rewl_wave.hip).
 //
 // Once per cycle: k_merge_windows (flatness by block reductions
 // and the in-window average), k_merge_finish, k_exchange (Eq. 1, swaps
@@ -15,126 +15,6 @@
 #include "rewl_internal.h"
 
 namespace rewl {
-
-namespace {
-
-__device__ __forceinline__ int find_instance(const DevPtrs& P, int slot) {
-  int i = 0;
-  while (i + 1 < P.n_inst && P.inst[i + 1].slot_base <= slot) ++i;
-  return i;
-}
-
-__device__ __forceinline__ uint4 draw(const InstDesc& I, uint64_t idx, uint32_t w2, uint32_t tag) {
-  return philox10(make_uint4((uint32_t)idx, (uint32_t)(idx >> 32), w2,
-                             tag | ((uint32_t)I.inst << 8)),
-                  I.key0, I.key1);
-}
-
-__device__ int32_t full_energy(const InstDesc& I, const int8_t* sp) {
-  const int L = I.L;
-  int32_t e = 0;
-  for (int y = 0; y < L; ++y) {
-    const int yd = (y + 1 == L) ? 0 : y + 1;
-    for (int x = 0; x < L; ++x) {
-      const int xr = (x + 1 == L) ? 0 : x + 1;
-      const int s0 = sp[y * L + x], sr = sp[y * L + xr], sd = sp[yd * L + x];
-      if (I.model == kIsing) e -= s0 * sr + s0 * sd;
-      else e -= (s0 == sr) + (s0 == sd);
-    }
-  }
-  return e;
-}
-
-// Proposal on a lattice in global memory (warm-up only).
-__device__ int propose_global(const InstDesc& I, const int8_t* sp, uint4 r, int& site, int& nv) {
-  const int L = I.L;
-  const int st = (int)__umulhi(r.x, (uint32_t)I.N);
-  const int y = st / L, x = st - y * L;
-  const int a = sp[y * L + ((x + 1 == L) ? 0 : x + 1)];
-  const int b = sp[y * L + ((x == 0) ? L - 1 : x - 1)];
-  const int c = sp[((y + 1 == L) ? 0 : y + 1) * L + x];
-  const int d = sp[((y == 0) ? L - 1 : y - 1) * L + x];
-  const int s0 = sp[st];
-  site = st;
-  if (I.model == kIsing) {
-    nv = -s0;
-    return 2 * s0 * (a + b + c + d);
-  }
-  int v = s0 + 1 + (int)__umulhi(r.y, (uint32_t)(I.q - 1));
-  v = (v >= I.q) ? v - I.q : v;
-  nv = v;
-  return ((a == s0) + (b == s0) + (c == s0) + (d == s0)) - ((a == v) + (b == v) + (c == v) + (d == v));
-}
-
-__device__ __forceinline__ int32_t dist_to(int32_t E, int32_t elo, int32_t ehi) {
-  return E < elo ? elo - E : (E > ehi ? E - ehi : 0);
-}
-
-}  // namespace
-
-// ---------------------------------------------------------------------------
-// Initialisation: random spins (one Philox block per 4 sites), full energy,
-// then warm-up into the window: greedy moves that never increase the
-// distance of E to the window, budget 1000 N; on failure one restart from an
-// extreme state (ground state below the middle of the range, checkerboard
-// above) and a second budget.  One thread per walker; not on the hot path.
-// ---------------------------------------------------------------------------
-__global__ void k_init(DevPtrs P) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= P.n_slots) return;
-  const InstDesc I = P.inst[find_instance(P, g)];
-  const int loc = g - I.slot_base;
-  const int w = loc / I.m;
-  const WinDesc W = P.win[I.win_base + w];
-  int8_t* sp = P.spins + I.spin_base + (int64_t)loc * I.npad;
-  for (int site = 0; site < I.N; site += 4) {
-    const uint4 r = draw(I, (uint64_t)(site >> 2), (uint32_t)loc, kTagInit);
-    const uint32_t rv[4] = {r.x, r.y, r.z, r.w};
-    for (int j = 0; j < 4 && site + j < I.N; ++j) {
-      const uint32_t v = rv[j];
-      sp[site + j] = (I.model == kIsing) ? (int8_t)((v >> 31) ? 1 : -1)
-                                         : (int8_t)__umulhi(v, (uint32_t)I.q);
-    }
-  }
-  const int32_t elo = I.emin + W.lo * I.binw, ehi = I.emin + W.hi * I.binw;
-  int32_t E = full_energy(I, sp);
-  uint64_t wa = 0;
-  for (int phase = 0; phase < 2; ++phase) {
-    const int64_t budget = 1000LL * I.N;
-    for (int64_t it = 0; it < budget && dist_to(E, elo, ehi) > 0; ++it) {
-      const uint4 r = draw(I, wa++, (uint32_t)loc, kTagWarm);
-      int site, nv;
-      const int dE = propose_global(I, sp, r, site, nv);
-      if (dist_to(E + dE, elo, ehi) <= dist_to(E, elo, ehi)) {
-        sp[site] = (int8_t)nv;
-        E += dE;
-      }
-    }
-    if (dist_to(E, elo, ehi) == 0) break;
-    if (phase == 0) {
-      const uint4 r = draw(I, wa++, (uint32_t)loc, kTagWarm);
-      const bool below = (W.lo + W.hi) < (I.nbins - 1);
-      int a, b;
-      if (I.model == kIsing) {
-        a = (r.x >> 31) ? 1 : -1;
-        b = -a;
-      } else {
-        a = (int)__umulhi(r.x, (uint32_t)I.q);
-        b = a + 1 + (int)__umulhi(r.y, (uint32_t)(I.q - 1));
-        b = (b >= I.q) ? b - I.q : b;
-      }
-      for (int y = 0; y < I.L; ++y)
-        for (int x = 0; x < I.L; ++x)
-          sp[y * I.L + x] = (int8_t)((below || ((x + y) & 1) == 0) ? a : b);
-      E = full_energy(I, sp);
-    }
-  }
-  P.cfg[g] = g;
-  P.E[g] = E;
-  P.att[g] = 0;
-  P.watt[g] = wa;
-  if (dist_to(E, elo, ehi) != 0) atomicMin(&P.ist[I.inst].error, -7);
-}
 
 // ---------------------------------------------------------------------------
 // Flatness and in-window merge: one 256-thread block per window.
@@ -626,12 +506,6 @@ __global__ void k_thermo(DevPtrs P, int32_t instance, int32_t nT) {
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_init(const DevPtrs& P, hipStream_t s) {
-  const int bs = 64;
-  hipLaunchKernelGGL(k_init, dim3((P.n_slots + bs - 1) / bs), dim3(bs), 0, s, P);
-  return hipGetLastError();
-}
-
 hipError_t launch_merge(const DevPtrs& P, hipStream_t s) {
   hipLaunchKernelGGL(k_merge_windows, dim3(P.n_win), dim3(256), 0, s, P);
   hipLaunchKernelGGL(k_merge_finish, dim3((P.n_inst + 63) / 64), dim3(64), 0, s, P);

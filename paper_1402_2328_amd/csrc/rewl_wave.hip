@@ -1,6 +1,7 @@
-// The Wang-Landau sweep with one wavefront per walker, for batches of few
-// walkers.
+// One wavefront per walker: the Wang-Landau sweep of batches of few walkers,
+// and the initialisation of every batch (further down).
 //
+// The sweep.
 // With one walker per lane (rewl_sweep.hip) an attempt is a serial chain of
 // two LDS round trips and some eighty dependent instructions, about 300 to
 // 430 ns, and a batch of few walkers leaves most of the chip idle.  Here the
@@ -84,6 +85,7 @@ struct Around<kIsing> {
     auto up = [&](int s) { return (uint32_t)(lat[s] >> 7) ^ 1u; };  // +1 -> 1, -1 (0xFF) -> 0
     n = up(nr) | up(nl) << 1 | up(nd) << 2 | up(nu) << 3 | up(site) << 4;
   }
+  static constexpr int kUnit = 4;  // energy of a bin step with bshift = 0
   // bin step of the flip: agreeing neighbours - 2 (Delta E = 2 s sum, bins of 4)
   __device__ __forceinline__ int step(int, int) const {
     const uint32_t own = (uint32_t)((int32_t)(n << 27) >> 31);  // all ones when up
@@ -115,6 +117,7 @@ struct Around<kPotts> {
     u = (int)__umulhi(draw, (uint32_t)(q - 1));
     propose(q);
   }
+  static constexpr int kUnit = 1;
   // bin step: (neighbours equal to s0) - (neighbours equal to v)
   __device__ __forceinline__ int step(int, int bshift) const {
     return (nonzero_bytes(n ^ ((uint32_t)v * 0x01010101u)) -
@@ -130,6 +133,49 @@ struct Around<kPotts> {
     propose(q);
   }
   static __device__ __forceinline__ uint8_t byte_of(int v) { return (uint8_t)v; }
+};
+
+// The site that one attempt picks, its neighbours and the lattice around
+// them, per lane; and whether another of the wavefront's attempts picks one
+// of the five.
+template <int MODEL>
+struct Pick {
+  int site, nr, nl, nd, nu;
+  Around<MODEL> ar;
+  // r: the attempt's random numbers; live: the lane makes an attempt;
+  // picked: a byte per site, zero before and after.  Returns the lanes whose
+  // five sites another lane picks one of.
+  __device__ __forceinline__ uint64_t load(const uint8_t* lat, uint8_t* picked, uint4 r, bool live,
+                                           int side, int N, int q) {
+    site = (int)__umulhi(r.x, (uint32_t)N);
+    // site = floor(r.x L^2 / 2^32), so its row is floor(r.x L / 2^32)
+    const int y = (int)__umulhi(r.x, (uint32_t)side);
+    const int x = site - __mul24(y, side);
+    nr = site + (x + 1 == side ? 1 - side : 1);
+    nl = site + (x == 0 ? side - 1 : -1);
+    nd = site + (y + 1 == side ? side - N : side);
+    nu = site + (y == 0 ? N - side : -side);
+    if (live) atomicAdd(reinterpret_cast<uint32_t*>(picked) + (site >> 2), 1u << ((site & 3) * 8));
+    ar.load(lat, site, nr, nl, nd, nu, r.y, q);
+    wave_order();
+    const bool others = picked[site] > 1 || (picked[nr] | picked[nl] | picked[nd] | picked[nu]) != 0;
+    wave_order();
+    picked[site] = 0;
+    return __ballot(others);
+  }
+  // attempt i was accepted: every lane's view follows
+  __device__ __forceinline__ void follow(int i, int q) {
+    ar.change(lane_of(site, i), lane_of(ar.proposed(), i), site, nr, nl, nd, nu, q);
+  }
+  // the accepted lanes' sites (moved) back to the lattice: a site that other
+  // lanes touch (shared) was kept up to date in every lane that holds it
+  __device__ __forceinline__ void settle(uint8_t* lat, uint64_t moved, uint64_t shared, int lane) const {
+    if ((moved >> lane) & 1) {
+      const int val = ((shared >> lane) & 1) ? ar.own() : ar.proposed();
+      lat[site] = Around<MODEL>::byte_of(val);
+    }
+    wave_order();
+  }
 };
 
 // ln g of one bin, the walker's running value, and the acceptance test in
@@ -201,6 +247,145 @@ struct LnG<kFP32C> {
 };
 
 }  // namespace
+
+// ---------------------------------------------------------------------------
+// Initialisation: random spins (one Philox block per 4 sites), full energy,
+// then warm-up into the window: greedy moves that never increase the
+// distance of E to the window, budget 1000 N; on failure one restart from an
+// extreme state (ground state below the middle of the range, checkerboard
+// above) and a second budget.
+//
+// One wavefront per walker.  The slowest walker of a batch decides: in the
+// ordered phase it makes up to a million attempts, of which few are
+// accepted.  The distance of E + dE to the window decides a greedy move, so
+// 64 attempts are judged at once and only the accepted ones (found by a
+// ballot) go one after the other, each moving E and, where another attempt
+// shares its site or a neighbour, the view of the lanes behind it.  The
+// 64-instance mix (17455 walkers) is set up in 11 ms; one lane per walker on
+// a lattice in device memory took 494 ms.
+// ---------------------------------------------------------------------------
+template <int MODEL>
+__device__ __forceinline__ int32_t wave_energy(const uint8_t* lat, int side, int N, int lane) {
+  int32_t e = 0;
+  for (int s = lane; s < N; s += kWave) {
+    const int y = s / side, x = s - y * side;
+    const uint8_t s0 = lat[s], sr = lat[x + 1 == side ? s + 1 - side : s + 1],
+                  sd = lat[y + 1 == side ? s + side - N : s + side];
+    const int same = (s0 == sr) + (s0 == sd);
+    e -= MODEL == kIsing ? 2 * same - 2 : same;
+  }
+  return wave_reduce(e, [](int32_t a, int32_t b) { return a + b; });
+}
+
+__device__ __forceinline__ int32_t dist_to(int32_t E, int32_t elo, int32_t ehi) {
+  return max(max(elo - E, E - ehi), 0);
+}
+
+template <int MODEL>
+__device__ __forceinline__ void init_walker(const DevPtrs& P, const InstDesc& I, int g, uint8_t* lat,
+                                            uint8_t* picked) {
+  const int lane = threadIdx.x;
+  const int loc = g - I.slot_base;
+  const int w = loc / I.m;
+  const WinDesc W = P.win[I.win_base + w];
+  const int side = I.L, N = I.N, q = I.q;
+  const int words = I.npad >> 2;
+  for (int i = lane; i < words; i += kWave) {
+    const uint4 r = draw(I, (uint64_t)i, (uint32_t)loc, kTagInit);
+    const uint32_t rv[4] = {r.x, r.y, r.z, r.w};
+    uint32_t word = 0;
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t v = MODEL == kIsing ? (rv[j] >> 31 ? 1u : 0xFFu) : __umulhi(rv[j], (uint32_t)q);
+      if (4 * i + j < N) word |= v << (8 * j);
+    }
+    reinterpret_cast<uint32_t*>(lat)[i] = word;
+    reinterpret_cast<uint32_t*>(picked)[i] = 0u;
+  }
+  wave_order();
+  const int32_t elo = I.emin + W.lo * I.binw, ehi = I.emin + W.hi * I.binw;
+  int32_t E = __builtin_amdgcn_readfirstlane(wave_energy<MODEL>(lat, side, N, lane));
+  uint64_t wa = 0;
+  for (int phase = 0; phase < 2; ++phase) {
+    const int budget = 1000 * N;
+    for (int it = 0; it < budget && dist_to(E, elo, ehi) > 0;) {
+      const int n = budget - it < kWave ? budget - it : kWave;
+      const uint4 r = draw(I, wa + (uint64_t)lane, (uint32_t)loc, kTagWarm);
+      Pick<MODEL> pick;
+      const uint64_t shared = pick.load(lat, picked, r, lane < n, side, N, q);
+      int dE = pick.ar.step(q, 0) * Around<MODEL>::kUnit;
+      uint64_t left = n < kWave ? (1ull << n) - 1 : ~0ull, moved = 0;
+      int made = n;
+      while (left) {
+        const int d = dist_to(E, elo, ehi);
+        const uint64_t ok = __ballot(dist_to(E + dE, elo, ehi) <= d) & left;
+        if (!ok) break;
+        const int i = __builtin_ctzll(ok);
+        moved |= 1ull << i;
+        E += lane_of(dE, i);
+        if ((shared >> i) & 1) {
+          pick.follow(i, q);
+          dE = pick.ar.step(q, 0) * Around<MODEL>::kUnit;
+        }
+        if (dist_to(E, elo, ehi) == 0) {
+          made = i + 1;
+          break;
+        }
+        left &= i < kWave - 1 ? ~0ull << (i + 1) : 0ull;
+      }
+      pick.settle(lat, moved, shared, lane);
+      it += made;
+      wa += (uint64_t)made;
+    }
+    if (dist_to(E, elo, ehi) == 0) break;
+    if (phase == 0) {
+      const uint4 r = draw(I, wa++, (uint32_t)loc, kTagWarm);
+      const bool below = (W.lo + W.hi) < (I.nbins - 1);
+      int a, b;
+      if (MODEL == kIsing) {
+        a = (r.x >> 31) ? 1 : 0xFF;
+        b = a ^ 0xFE;
+      } else {
+        a = (int)__umulhi(r.x, (uint32_t)q);
+        b = a + 1 + (int)__umulhi(r.y, (uint32_t)(q - 1));
+        b = (b >= q) ? b - q : b;
+      }
+      for (int s = lane; s < N; s += kWave) {
+        const int y = s / side, x = s - y * side;
+        lat[s] = (uint8_t)((below || ((x + y) & 1) == 0) ? a : b);
+      }
+      wave_order();
+      E = __builtin_amdgcn_readfirstlane(wave_energy<MODEL>(lat, side, N, lane));
+    }
+  }
+  uint32_t* const gsp = reinterpret_cast<uint32_t*>(P.spins + I.spin_base + (int64_t)loc * I.npad);
+  for (int i = lane; i < words; i += kWave) gsp[i] = reinterpret_cast<const uint32_t*>(lat)[i];
+  if (lane == 0) {
+    P.cfg[g] = g;
+    P.E[g] = E;
+    P.att[g] = 0;
+    P.watt[g] = wa;
+    if (dist_to(E, elo, ehi) != 0) atomicMin(&P.ist[I.inst].error, -7);
+  }
+}
+
+__global__ __launch_bounds__(kWave) void k_init(DevPtrs P, int32_t lat_bytes) {
+  extern __shared__ __align__(16) uint8_t wlds[];
+  const int g = (int)blockIdx.x;
+  int lo = 0, hi = P.n_inst - 1;  // the instance that owns slot g
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (P.inst[mid].slot_base <= g) lo = mid;
+    else hi = mid - 1;
+  }
+  const InstDesc& I = P.inst[lo];
+  if (I.model == kIsing) init_walker<kIsing>(P, I, g, wlds, wlds + lat_bytes);
+  else init_walker<kPotts>(P, I, g, wlds, wlds + lat_bytes);
+}
+
+hipError_t launch_init(const DevPtrs& P, int32_t lat_bytes, hipStream_t s) {
+  hipLaunchKernelGGL(k_init, dim3(P.n_slots), dim3(kWave), (size_t)2 * lat_bytes, s, P, lat_bytes);
+  return hipGetLastError();
+}
 
 template <int MODEL, int PREC>
 __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offset, int32_t lat_bytes,
@@ -286,22 +471,9 @@ __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offs
     // ---- one attempt per lane
     const uint64_t a = att + (uint64_t)lane;
     const uint4 r = philox10(make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)loc, tagw), k0, k1);
-    const int site = (int)__umulhi(r.x, (uint32_t)N);
-    // site = floor(r.x L^2 / 2^32), so its row is floor(r.x L / 2^32)
-    const int y = (int)__umulhi(r.x, (uint32_t)side);
-    const int x = site - __mul24(y, side);
-    const int nr = site + (x + 1 == side ? 1 - side : 1), nl = site + (x == 0 ? side - 1 : -1);
-    const int nd = site + (y + 1 == side ? side - N : side), nu = site + (y == 0 ? N - side : -side);
-    if (lane < n)
-      atomicAdd(reinterpret_cast<uint32_t*>(picked) + (site >> 2), 1u << ((site & 3) * 8));
-    Around<MODEL> ar;
-    ar.load(lat, site, nr, nl, nd, nu, r.y, q);
-    wave_order();
-    const bool others = picked[site] > 1 || (picked[nr] | picked[nl] | picked[nd] | picked[nu]) != 0;
-    const uint64_t shared = __ballot(others);
-    wave_order();
-    picked[site] = 0;
-    int step = ar.step(q, bshift);
+    Pick<MODEL> pick;
+    const uint64_t shared = pick.load(lat, picked, r, lane < n, side, N, q);
+    int step = pick.ar.step(q, bshift);
     Bound yes, no;
     L::bounds(r, yes, no);
     uint64_t moved = 0;  // attempts whose move was accepted
@@ -322,8 +494,8 @@ __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offs
           acc = __ballot(L::accept((uint32_t)lane_of((int)r.z, i), (uint32_t)lane_of((int)r.w, i),
                                    delta)) & bit;  // the same in every lane
         if (acc & shared) {
-          ar.change(lane_of(site, i), lane_of(ar.proposed(), i), site, nr, nl, nd, nu, q);
-          step = ar.step(q, bshift);
+          pick.follow(i, q);
+          step = pick.ar.step(q, bshift);
         }
       }
       moved |= acc;
@@ -343,13 +515,7 @@ __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offs
     follow();
     for (; i < n; ++i) attempt(i);
     att += (uint64_t)n;
-    // ---- accepted sites back to the lattice: a site that other attempts
-    // touch was kept up to date in every lane that holds it
-    if ((moved >> lane) & 1) {
-      const int val = ((shared >> lane) & 1) ? ar.own() : ar.proposed();
-      lat[site] = Around<MODEL>::byte_of(val);
-    }
-    wave_order();
+    pick.settle(lat, moved, shared, lane);
   }
 
   store_page();
