@@ -563,6 +563,13 @@ hipError_t create_side_streams(rewl_ctx* c) {
   return e;
 }
 
+// Window bins of an instance, all windows.
+int32_t rep_count(const Layout& L, const InstDesc& I) {
+  int32_t n = 0;
+  for (int w = 0; w < I.h; ++w) n += L.win[I.win_base + w].nb;
+  return n;
+}
+
 int enqueue_cycle(rewl_ctx* c, int64_t flips) {
   hipError_t e = enqueue_sweeps(c, flips);
   if (e == hipSuccess) e = launch_merge(c->P, c->stream);
@@ -649,6 +656,7 @@ int rewl_init(const rewl_params* params, int32_t n, const int32_t* win_lo, const
     e = hipMemcpyAsync(c->ws + L.o_sm, sm.data(), sizeof(int64_t) * sm.size(),
                        hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = prepare_sweep_lds((size_t)lds_budget_bytes());
+  if (e == hipSuccess) e = prepare_join_lds();
   if (e == hipSuccess) e = scratch_address(&c->scratch);
   if (e == hipSuccess) e = launch_init(c->P, std::max({wave_lat_bytes(L, 0), wave_lat_bytes(L, 1), wave_lat_bytes(L, 2)}), c->stream);
   // host vectors above are pageable; make sure the copies finished
@@ -1180,7 +1188,7 @@ int rewl_get_lng(rewl_ctx* c, int32_t instance, int32_t which, double* out, int3
   const InstDesc& I = c->lo.inst[instance];
   if (n_bins_out) *n_bins_out = I.nbins;
   if (capacity < I.nbins) return REWL_E_INVAL;
-  int rc = hip_rc(launch_join(c->P, instance, which == 0, c->stream));
+  int rc = hip_rc(launch_join(c->P, I, rep_count(c->lo, I), which == 0, c->stream));
   if (rc) return rc;
   rc = d2h(c, out, c->P.R + I.r_base, (size_t)I.nbins);
   if (!rc && joins && I.h > 1) rc = d2h(c, joins, c->P.joins + I.win_base + 1, (size_t)(I.h - 1));
@@ -1221,7 +1229,7 @@ int rewl_jackknife(rewl_ctx* c, int32_t instance, double* mean, double* err, int
   int rc = d2h(c, &st, c->P.ist + instance, 1);
   if (rc) return rc;
   if (!st.done) return REWL_E_STATE;
-  rc = hip_rc(launch_jackknife(c->P, instance, c->P.rep + I.rep_base, c->P.jk, c->stream));
+  rc = hip_rc(launch_jackknife(c->P, I, rep_count(c->lo, I), c->P.jk, c->stream));
   if (!rc) rc = d2h(c, mean, c->P.jk + (int64_t)I.m * I.nbins, (size_t)I.nbins);
   if (!rc) rc = d2h(c, err, c->P.jk + (int64_t)(I.m + 1) * I.nbins, (size_t)I.nbins);
   return rc;
@@ -1235,8 +1243,7 @@ int rewl_jackknife_noalloc(rewl_ctx* c, int32_t instance, double* mean, double* 
   if (capacity < I.nbins) return REWL_E_INVAL;
   if (I.m < 2) return REWL_E_STATE;
   // representatives first, then the (m + 2) x nbins rows
-  size_t reps = 0;
-  for (int w = 0; w < I.h; ++w) reps += (size_t)c->lo.win[I.win_base + w].nb;
+  const size_t reps = (size_t)rep_count(c->lo, I);
   const size_t rows_at = (reps + 31) / 32 * 32;  // 256-byte aligned rows
   if (rows_at + (size_t)(I.m + 2) * (size_t)I.nbins > kScratchDoubles) return REWL_E_NOMEM;
   if (!c->scratch) return REWL_E_HIP;
@@ -1245,7 +1252,7 @@ int rewl_jackknife_noalloc(rewl_ctx* c, int32_t instance, double* mean, double* 
   if (rc) return rc;
   if (!st.done) return REWL_E_STATE;
   double* jk = c->scratch + rows_at;
-  rc = hip_rc(launch_jackknife(c->P, instance, c->scratch, jk, c->stream));
+  rc = hip_rc(launch_jackknife(c->P, I, rep_count(c->lo, I), jk, c->stream));
   if (!rc) rc = d2h(c, mean, jk + (int64_t)I.m * I.nbins, (size_t)I.nbins);
   if (!rc) rc = d2h(c, err, jk + (int64_t)(I.m + 1) * I.nbins, (size_t)I.nbins);
   return rc;
@@ -1257,7 +1264,8 @@ int rewl_thermo(rewl_ctx* c, int32_t instance, const double* T, int32_t nT, doub
   if (nT < 1 || nT > kMaxTemps) return REWL_E_INVAL;
   for (int i = 0; i < nT; ++i)
     if (!(T[i] > 0.0)) return REWL_E_INVAL;
-  int rc = hip_rc(launch_join(c->P, instance, 1, c->stream));
+  const InstDesc& I = c->lo.inst[instance];
+  int rc = hip_rc(launch_join(c->P, I, rep_count(c->lo, I), 1, c->stream));
   if (rc) return rc;
   rc = hip_rc(hipMemcpyAsync(c->P.thermo, T, sizeof(double) * nT, hipMemcpyHostToDevice, c->stream));
   if (rc) return rc;

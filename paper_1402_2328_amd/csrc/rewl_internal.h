@@ -137,12 +137,12 @@ hipError_t launch_sweep_fused(const DevPtrs& P, const SweepShape sh[3], int32_t 
                               size_t lds_bytes, bool producer, hipStream_t s);
 hipError_t launch_merge(const DevPtrs& P, hipStream_t s);
 hipError_t launch_exchange(const DevPtrs& P, hipStream_t s);
-hipError_t launch_join(const DevPtrs& P, int32_t instance, int32_t normalise, hipStream_t s);
-// Leave-one-out joins of an instance's frozen pieces, with the instance's
-// window representatives in rep (sum of its window sizes) and the rows in jk
+// reps: sum of the instance's window sizes.
+hipError_t launch_join(const DevPtrs& P, const InstDesc& I, int32_t reps, int32_t normalise, hipStream_t s);
+// Leave-one-out joins of an instance's frozen pieces, rows 0..m-1 of jk
 // ((m + 2) x nbins); mean and error land in rows m and m + 1.
-hipError_t launch_jackknife(const DevPtrs& P, int32_t instance, double* rep, double* jk,
-                            hipStream_t s);
+hipError_t launch_jackknife(const DevPtrs& P, const InstDesc& I, int32_t reps, double* jk, hipStream_t s);
+hipError_t prepare_join_lds();
 // Device address, on the current GPU, of the allocation-free jackknife's
 // kScratchDoubles-double array (looked up once per device).
 hipError_t scratch_address(double** out);

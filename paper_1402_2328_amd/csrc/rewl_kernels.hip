@@ -4,8 +4,9 @@
 // Once per cycle: k_merge_windows (flatness by block reductions
 // and the in-window average), k_merge_finish, k_exchange (Eq. 1, swaps
 // configuration indices, never lattice data), k_exchange_finish.  End of
-// run: k_join (Sec. 3 joining + normalisation in FP64), k_jackknife
-// (error bars from the m pieces per window) and k_thermo (Sec. 5, Eqs. 7-8).
+// run: k_join (Sec. 3 joining + normalisation in FP64), k_jackknife and
+// k_jackknife_rows (error bars from the m pieces per window) and k_thermo
+// (Sec. 5, Eqs. 7-8).
 #include <float.h>
 #include <math.h>
 
@@ -15,6 +16,88 @@
 #include "rewl_internal.h"
 
 namespace rewl {
+
+namespace {
+
+// Sum of values pushed one after the other, added pairwise by levels in their
+// order (an odd last element is carried): the sum of 2^l values sits in
+// acc[l] as long as bit l of the number of values so far is set, like the
+// digits of a binary counter.  Every thread pushes the same number of
+// values, so the branches are uniform and acc stays in registers.
+template <typename T, typename Add, int LEVELS>
+struct PairwiseDigits {
+  T acc;
+  PairwiseDigits<T, Add, LEVELS - 1> up;
+  __device__ __forceinline__ void push(T x, int n, Add add) {
+    if (n & 1) up.push(add(acc, x), n >> 1, add);
+    else acc = x;
+  }
+  __device__ __forceinline__ T total(T x, bool any, int n, Add add) const {
+    if (n & 1) x = any ? add(acc, x) : acc;
+    return up.total(x, any || (n & 1), n >> 1, add);
+  }
+};
+template <typename T, typename Add>
+struct PairwiseDigits<T, Add, 0> {
+  __device__ __forceinline__ void push(T, int, Add) {}
+  __device__ __forceinline__ T total(T x, bool, int, Add) const { return x; }
+};
+template <typename T, typename Add>
+struct PairwiseSum {
+  PairwiseDigits<T, Add, 7> digits;  // up to 127 values
+  int n = 0;
+  __device__ __forceinline__ void push(T x, Add add) { digits.push(x, n++, add); }
+  __device__ __forceinline__ T total(Add add) const { return digits.total(T(), false, n, add); }
+};
+static_assert(kMaxWalkersPerWindow < 128, "PairwiseSum holds up to 127 values");
+
+struct AddF64 {
+  __device__ __forceinline__ double operator()(double a, double b) const { return a + b; }
+};
+struct TwoFloat {
+  float h, l;
+};
+struct AddTwoFloat {
+  __device__ __forceinline__ TwoFloat operator()(TwoFloat a, TwoFloat b) const {
+    TwoFloat r;
+    df_add(a.h, a.l, b.h, b.l, r.h, r.l);
+    return r;
+  }
+};
+
+// f(k, value k) for k = 0..n-1, the values loaded eight at a time so that
+// their latencies overlap.
+template <typename T, typename Load, typename F>
+__device__ __forceinline__ void each_of(int n, Load load, F f) {
+  int k = 0;
+  for (; k + 8 <= n; k += 8) {
+    T v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = load(k + i);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) f(k + i, v[i]);
+  }
+  for (; k < n; ++k) f(k, load(k));
+}
+
+// Mean over the m walkers of the FP64 rows at x (stride nb).
+__device__ __forceinline__ double mean_f64(const double* x, int64_t nb, int m) {
+  PairwiseSum<double, AddF64> s;
+  each_of<double>(m, [&](int k) { return x[k * nb]; }, [&](int, double v) { s.push(v, AddF64()); });
+  return s.total(AddF64()) / (double)m;
+}
+
+__device__ __forceinline__ TwoFloat mean_two_float(const float* hi, const float* lo, int64_t nb, int m) {
+  PairwiseSum<TwoFloat, AddTwoFloat> s;
+  each_of<TwoFloat>(m, [&](int k) { return TwoFloat{hi[k * nb], lo[k * nb]}; },
+                    [&](int, TwoFloat v) { s.push(v, AddTwoFloat()); });
+  const TwoFloat t = s.total(AddTwoFloat());
+  TwoFloat r;
+  df_div_int(t.h, t.l, m, r.h, r.l);
+  return r;
+}
+
+}  // namespace
 
 // ---------------------------------------------------------------------------
 // Flatness and in-window merge: one 256-thread block per window.
@@ -240,8 +323,28 @@ __global__ void k_exchange_finish(DevPtrs P) {
 }
 
 // ---------------------------------------------------------------------------
-// Joining (Sec. 3, Eq. 2) and normalisation, FP64, one block per call.
+// Joining (Sec. 3, Eq. 2) and normalisation, FP64, one 1024-thread block per
+// joined curve.
+//
+// Nothing here moves more than a few megabytes; what costs is latency.  So
+// the representatives of all windows that fit in LDS (a chunk; all of them
+// unless the windows are huge) are computed at once, every thread a bin; the
+// best join bin of a window pair does not depend on the other pairs and takes
+// one wavefront each; only the shifts (one addition chain over the windows)
+// are serial.  Window after window in one 256-thread block with
+// representatives in device memory, the join took 116 us (Ising L = 32,
+// 16 windows x 8 walkers) to 290 us (q = 10 Potts L = 20, 32 x 16).
 // ---------------------------------------------------------------------------
+constexpr int kJoinThreads = 1024;
+constexpr int kChunkWindows = 256;
+
+struct JoinShared {
+  double red[kJoinThreads / 64];
+  int64_t redi[kJoinThreads / 64];
+  double a[kChunkWindows], b[kChunkWindows], shift[kChunkWindows];
+  int best[kChunkWindows];
+};
+
 __device__ __forceinline__ double beta5(const double* l, int j) {
   return (((l[j - 2] - 8.0 * l[j - 1]) + 8.0 * l[j + 1]) - l[j + 2]) / 12.0;
 }
@@ -249,75 +352,108 @@ __device__ __forceinline__ double beta5(const double* l, int j) {
 // Joins the window representatives into R (Sec. 3, Eq. 2): the
 // first window as it is, then window w from the bin of (w-1, w) where the
 // five-point slopes agree best (lowest such bin on ties; the middle of the
-// overlap if no bin qualifies), shifted to continue the joined curve.
+// overlap if no bin qualifies), shifted to continue the joined curve: a bin
+// belongs to the last window whose range from its join bin up holds it.
 // normalise: Ising sum g = 2^N, Potts g(E_min) = q.  Whole block.
-// rep: this instance's representatives, window w at rep + (rep_off -
-// the instance's rep_base).
-__device__ void stitch_normalise(const DevPtrs& P, const InstDesc& I, const double* rep, double* R,
-                                 int normalise, double* redd, int64_t* redi, double& shift_s,
-                                 int& best_s, bool record_joins) {
-  const int tid = threadIdx.x, nt = blockDim.x;
-  __syncthreads();
+// rep_of(W, j): representative of window W at its bin j; rep: LDS for cap of
+// them, at least two windows' worth.
+template <typename RepOf>
+__device__ void join_windows(const DevPtrs& P, const InstDesc& I, RepOf rep_of, double* rep, int cap,
+                             double* R, int normalise, bool record_joins, JoinShared& S) {
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6, waves = nt >> 6;
+  const WinDesc* const win = P.win + I.win_base;
   for (int b = tid; b < I.nbins; b += nt) R[b] = -INFINITY;
-  __syncthreads();
-  {
-    const WinDesc W0 = P.win[I.win_base];
-    const uint8_t* U0 = P.U + W0.u_base;
-    const double* r0 = rep + (W0.rep_off - I.rep_base);
-    for (int j = tid; j < W0.nb; j += nt) R[W0.lo + j] = U0[j] ? r0[j] : -INFINITY;
-  }
-  if (tid == 0) shift_s = 0.0;
-  __syncthreads();
-  for (int w = 1; w < I.h; ++w) {
-    const WinDesc Wa = P.win[I.win_base + w - 1];
-    const WinDesc Wb = P.win[I.win_base + w];
-    const double* la = rep + (Wa.rep_off - I.rep_base);
-    const double* lb = rep + (Wb.rep_off - I.rep_base);
-    const uint8_t* Ua = P.U + Wa.u_base;
-    const uint8_t* Ub = P.U + Wb.u_base;
-    double bestd = INFINITY;
-    for (int b = Wb.lo + 2 + tid; b <= Wa.hi - 2; b += nt) {
-      bool ok = true;
-      for (int d = -2; d <= 2 && ok; ++d) ok = Ua[b + d - Wa.lo] && Ub[b + d - Wb.lo];
-      if (!ok) continue;
-      const double db = fabs(beta5(la, b - Wa.lo) - beta5(lb, b - Wb.lo));
-      if (db < bestd) bestd = db;
+  double carry = 0.0;  // shift of the chunk's first window
+  for (int w0 = 0;;) {
+    // windows w0..w1-1 of this chunk; the next one starts with its last
+    int w1 = w0 + 1;
+    while (w1 < I.h && w1 - w0 < kChunkWindows && win[w1].rep_off + win[w1].nb - win[w0].rep_off <= cap) ++w1;
+    const int off0 = win[w0].rep_off;
+    const int items = win[w1 - 1].rep_off + win[w1 - 1].nb - off0;
+    for (int e = tid; e < items; e += nt) {
+      int lo = w0, hi = w1 - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (win[mid].rep_off - off0 <= e) lo = mid;
+        else hi = mid - 1;
+      }
+      rep[e] = rep_of(win[lo], e - (win[lo].rep_off - off0));
     }
-    bestd = block_reduce(bestd, [](double a, double b) { return a < b ? a : b; }, redd);
-    int64_t bi = INT64_MAX;
-    if (bestd < INFINITY) {
-      for (int b = Wb.lo + 2 + tid; b <= Wa.hi - 2; b += nt) {
+    __syncthreads();
+    for (int w = w0 + 1 + wave; w < w1; w += waves) {
+      const WinDesc Wa = win[w - 1], Wb = win[w];
+      const double* la = rep + (Wa.rep_off - off0);
+      const double* lb = rep + (Wb.rep_off - off0);
+      const uint8_t* Ua = P.U + Wa.u_base;
+      const uint8_t* Ub = P.U + Wb.u_base;
+      double bestd = INFINITY;
+      int best = INT32_MAX;
+      for (int b = Wb.lo + 2 + lane; b <= Wa.hi - 2; b += 64) {
         bool ok = true;
-        for (int d = -2; d <= 2 && ok; ++d) ok = Ua[b + d - Wa.lo] && Ub[b + d - Wb.lo];
+        for (int d = -2; d <= 2; ++d) ok = ok && Ua[b + d - Wa.lo] && Ub[b + d - Wb.lo];
         if (!ok) continue;
         const double db = fabs(beta5(la, b - Wa.lo) - beta5(lb, b - Wb.lo));
-        if (db == bestd && b < bi) bi = b;
+        if (db < bestd) {
+          bestd = db;
+          best = b;
+        }
+      }
+      const double least = wave_reduce(bestd, [](double x, double y) { return x < y ? x : y; });
+      if (bestd != least) best = INT32_MAX;
+      best = wave_reduce(best, [](int x, int y) { return x < y ? x : y; });
+      if (best == INT32_MAX) best = (Wb.lo + Wa.hi) / 2;
+      if (lane == 0) {
+        S.best[w - w0] = best;
+        S.a[w - w0] = la[best - Wa.lo];
+        S.b[w - w0] = lb[best - Wb.lo];
+        if (record_joins) P.joins[I.win_base + w] = best;
       }
     }
-    bi = block_reduce(bi, [](int64_t a, int64_t b) { return a < b ? a : b; }, redi);
+    __syncthreads();
     if (tid == 0) {
-      const int best = (bi == INT64_MAX) ? (Wb.lo + Wa.hi) / 2 : (int)bi;
-      best_s = best;
-      shift_s = (la[best - Wa.lo] + shift_s) - lb[best - Wb.lo];
-      if (record_joins) P.joins[I.win_base + w] = best;
+      double s = carry;
+      S.shift[0] = s;
+      for (int w = 1; w < w1 - w0; ++w) {
+        s = (S.a[w] + s) - S.b[w];
+        S.shift[w] = s;
+      }
     }
     __syncthreads();
-    const int best = best_s;
-    const double sh = shift_s;
-    for (int b = best + tid; b <= Wb.hi; b += nt)
-      R[b] = Ub[b - Wb.lo] ? lb[b - Wb.lo] + sh : -INFINITY;
+    const int from = w0 == 0 ? win[0].lo : win[w0 + 1].lo;
+    for (int b = from + tid; b <= win[w1 - 1].hi; b += nt) {
+      int lo = w0, hi = w1 - 1;  // last window of the chunk that starts at or below b
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (win[mid].lo <= b) lo = mid;
+        else hi = mid - 1;
+      }
+      for (int w = lo; w >= w0 && win[w].hi >= b; --w) {
+        if (w == w0 && w0 > 0) break;  // the chunk before wrote these
+        if (w > w0 && S.best[w - w0] > b) continue;
+        const WinDesc W = win[w];
+        const int j = b - W.lo;
+        if (j >= 0)
+          R[b] = P.U[W.u_base + j] ? (w == 0 ? rep[W.rep_off - off0 + j]
+                                             : rep[W.rep_off - off0 + j] + S.shift[w - w0])
+                                   : -INFINITY;
+        break;
+      }
+    }
+    carry = S.shift[w1 - 1 - w0];
     __syncthreads();
+    if (w1 >= I.h) break;
+    w0 = w1 - 1;
   }
   if (!normalise) return;
   double c;
   if (I.model == kIsing) {
     double mx = -INFINITY;
     for (int b = tid; b < I.nbins; b += nt) mx = fmax(mx, R[b]);
-    mx = block_reduce(mx, [](double a, double b) { return a > b ? a : b; }, redd);
+    mx = block_reduce(mx, [](double a, double b) { return a > b ? a : b; }, S.red);
     double acc = 0.0;
     for (int b = tid; b < I.nbins; b += nt)
       if (isfinite(R[b])) acc += exp(R[b] - mx);
-    acc = block_reduce(acc, [](double a, double b) { return a + b; }, redd);
+    acc = block_reduce(acc, [](double a, double b) { return a + b; }, S.red);
     c = (double)I.N * log(2.0) - (mx + log(acc));
   } else {
     c = log((double)I.q) - R[0];
@@ -327,123 +463,74 @@ __device__ void stitch_normalise(const DevPtrs& P, const InstDesc& I, const doub
     if (isfinite(R[b])) R[b] += c;
 }
 
-__global__ __launch_bounds__(256) void k_join(DevPtrs P, int32_t instance, int32_t normalise) {
-  __shared__ double redd[8];
-  __shared__ int64_t redi[8];
-  __shared__ double shift_s;
-  __shared__ int best_s;
+// Window representatives: mean over walkers, same tree as the merge.
+__global__ __launch_bounds__(kJoinThreads) void k_join(DevPtrs P, int32_t instance, int32_t normalise,
+                                                       int32_t cap) {
+  extern __shared__ __align__(16) double join_rep[];
+  __shared__ JoinShared S;
   const InstDesc& I = P.inst[instance];
-  const int tid = threadIdx.x, nt = blockDim.x;
   const int m = I.m;
-  double* R = P.R + I.r_base;
-  // window representatives: mean over walkers, same tree as the merge
-  for (int w = 0; w < I.h; ++w) {
-    const WinDesc W = P.win[I.win_base + w];
-    double* rep = P.rep + W.rep_off;
-    for (int j = tid; j < W.nb; j += nt) {
-      if (P.prec == kFP64) {
-        double v[kMaxWalkersPerWindow];
-        for (int k = 0; k < m; ++k) v[k] = P.lng[W.lng_base + (int64_t)k * W.nb + j];
-        int n = m;
-        while (n > 1) {
-          int o = 0;
-          for (int i = 0; i + 1 < n; i += 2) v[o++] = v[i] + v[i + 1];
-          if (n & 1) v[o++] = v[n - 1];
-          n = o;
-        }
-        rep[j] = v[0] / (double)m;
-      } else {
-        float vh[kMaxWalkersPerWindow], vl[kMaxWalkersPerWindow];
-        for (int k = 0; k < m; ++k) {
-          vh[k] = P.lhi[W.lng_base + (int64_t)k * W.nb + j];
-          vl[k] = P.llo[W.lng_base + (int64_t)k * W.nb + j];
-        }
-        int n = m;
-        while (n > 1) {
-          int o = 0;
-          for (int i = 0; i + 1 < n; i += 2) {
-            float a, b;
-            df_add(vh[i], vl[i], vh[i + 1], vl[i + 1], a, b);
-            vh[o] = a;
-            vl[o] = b;
-            ++o;
-          }
-          if (n & 1) {
-            vh[o] = vh[n - 1];
-            vl[o] = vl[n - 1];
-            ++o;
-          }
-          n = o;
-        }
-        float mh, ml;
-        df_div_int(vh[0], vl[0], m, mh, ml);
-        rep[j] = (double)mh + (double)ml;
-      }
-    }
-  }
-  stitch_normalise(P, I, P.rep + I.rep_base, R, normalise, redd, redi, shift_s, best_s, true);
+  join_windows(
+      P, I,
+      [&](const WinDesc& W, int j) {
+        const int64_t e0 = W.lng_base + j;
+        if (P.prec == kFP64) return mean_f64(P.lng + e0, W.nb, m);
+        const TwoFloat r = mean_two_float(P.lhi + e0, P.llo + e0, W.nb, m);
+        return (double)r.h + (double)r.l;
+      },
+      join_rep, cap, P.R + I.r_base, normalise, true, S);
 }
 
-// Jackknife over the m pieces per window (Sec. 3): for k = 0..m-1 the
-// representatives are the pairwise means of the pieces without walker k,
-// joined and normalised into row k of jk; then per bin the mean of the m
-// rows and sqrt((m-1)/m * sum (R_k - mean)^2) go to rows m and m + 1 (-inf
-// and 0 where any row is not finite).  rep holds the instance's window
-// representatives (sum of its window sizes), jk (m + 2) x nbins doubles;
-// every element of both is written before it is read.  One block.
-__global__ __launch_bounds__(256) void k_jackknife(DevPtrs P, int32_t instance, double* rep_buf,
-                                                   double* jk) {
-  __shared__ double redd[8];
-  __shared__ int64_t redi[8];
-  __shared__ double shift_s;
-  __shared__ int best_s;
+// Jackknife over the m pieces per window (Sec. 3): block k joins and
+// normalises the pairwise means of the pieces without walker k into row k of
+// jk ((m + 2) x nbins doubles).  A block per k: one block for all of them
+// took 25 ms at Ising L = 32, 16 windows x 64 walkers.
+__global__ __launch_bounds__(kJoinThreads) void k_jackknife(DevPtrs P, int32_t instance, double* jk,
+                                                            int32_t cap) {
+  extern __shared__ __align__(16) double join_rep[];
+  __shared__ JoinShared S;
   const InstDesc& I = P.inst[instance];
-  const int tid = threadIdx.x, nt = blockDim.x;
+  const int m = I.m, out = blockIdx.x;
+  join_windows(
+      P, I,
+      [&](const WinDesc& W, int j) {
+        const double* const x = P.pieces + W.lng_base + j;
+        const int64_t nb = W.nb;
+        PairwiseSum<double, AddF64> s;
+        each_of<double>(m - 1, [&](int k) { return x[(k + (k >= out ? 1 : 0)) * nb]; },
+                        [&](int, double v) { s.push(v, AddF64()); });
+        return s.total(AddF64()) / (double)(m - 1);
+      },
+      join_rep, cap, jk + (int64_t)out * I.nbins, 1, false, S);
+}
+
+// Per bin the mean of the m rows of jk and sqrt((m-1)/m * sum (R_k - mean)^2)
+// into rows m and m + 1 (-inf and 0 where any row is not finite).
+__global__ __launch_bounds__(64) void k_jackknife_rows(DevPtrs P, int32_t instance, double* jk) {
+  const InstDesc& I = P.inst[instance];
   const int m = I.m, nbins = I.nbins;
-  for (int k = 0; k < m; ++k) {
-    for (int w = 0; w < I.h; ++w) {
-      const WinDesc W = P.win[I.win_base + w];
-      double* rep = rep_buf + (W.rep_off - I.rep_base);
-      for (int j = tid; j < W.nb; j += nt) {
-        double v[kMaxWalkersPerWindow];
-        int n = 0;
-        for (int i = 0; i < m; ++i)
-          if (i != k) v[n++] = P.pieces[W.lng_base + (int64_t)i * W.nb + j];
-        const int cnt = n;
-        while (n > 1) {
-          int o = 0;
-          for (int i = 0; i + 1 < n; i += 2) v[o++] = v[i] + v[i + 1];
-          if (n & 1) v[o++] = v[n - 1];
-          n = o;
-        }
-        rep[j] = v[0] / (double)cnt;
-      }
-    }
-    __syncthreads();
-    stitch_normalise(P, I, rep_buf, jk + (int64_t)k * nbins, 1, redd, redi, shift_s, best_s, false);
-    __syncthreads();
+  const int b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b >= nbins) return;
+  bool fin = true;
+  double acc = 0.0;
+  each_of<double>(m, [&](int k) { return jk[(int64_t)k * nbins + b]; },
+                  [&](int, double r) {
+                    fin = fin && isfinite(r);
+                    acc += r;
+                  });
+  double mu = -INFINITY, e = 0.0;
+  if (fin) {
+    mu = acc / (double)m;
+    double v = 0.0;
+    each_of<double>(m, [&](int k) { return jk[(int64_t)k * nbins + b]; },
+                    [&](int, double r) {
+                      const double d = r - mu;
+                      v += d * d;
+                    });
+    e = sqrt((double)(m - 1) / (double)m * v);
   }
-  for (int b = tid; b < nbins; b += nt) {
-    bool fin = true;
-    double acc = 0.0;
-    for (int k = 0; k < m; ++k) {
-      const double r = jk[(int64_t)k * nbins + b];
-      fin = fin && isfinite(r);
-      acc += r;
-    }
-    double mu = -INFINITY, e = 0.0;
-    if (fin) {
-      mu = acc / (double)m;
-      double v = 0.0;
-      for (int k = 0; k < m; ++k) {
-        const double d = jk[(int64_t)k * nbins + b] - mu;
-        v += d * d;
-      }
-      e = sqrt((double)(m - 1) / (double)m * v);
-    }
-    jk[(int64_t)m * nbins + b] = mu;
-    jk[(int64_t)(m + 1) * nbins + b] = e;
-  }
+  jk[(int64_t)m * nbins + b] = mu;
+  jk[(int64_t)(m + 1) * nbins + b] = e;
 }
 
 // Device memory of the allocation-free jackknife (rewl_jackknife_noalloc):
@@ -470,37 +557,45 @@ hipError_t scratch_address(double** out) {
   return hipSuccess;
 }
 
-// Canonical <E> and C_V (Sec. 5, Eqs. 7-8) from the joined ln g: one thread per T.
-__global__ void k_thermo(DevPtrs P, int32_t instance, int32_t nT) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// Canonical <E> and C_V (Sec. 5, Eqs. 7-8) from the joined ln g: one
+// wavefront per temperature, the bins over its lanes (one thread per
+// temperature took 403 us for 2000 temperatures of 801 bins).
+__global__ __launch_bounds__(256) void k_thermo(DevPtrs P, int32_t instance, int32_t nT) {
+  const int i = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
   if (i >= nT) return;
   const InstDesc& I = P.inst[instance];
   const double* lng = P.R + I.r_base;
   const double t = P.thermo[i];
+  auto sum = [](double a, double b) { return a + b; };
   double mx = -INFINITY;
-  for (int b = 0; b < I.nbins; ++b) {
+  for (int b = lane; b < I.nbins; b += 64) {
     if (!isfinite(lng[b])) continue;
     const double a = lng[b] - (double)(I.emin + b * I.binw) / t;
     if (a > mx) mx = a;
   }
+  mx = wave_reduce(mx, [](double a, double b) { return a > b ? a : b; });
   double z = 0.0, e1 = 0.0;
-  for (int b = 0; b < I.nbins; ++b) {
+  for (int b = lane; b < I.nbins; b += 64) {
     if (!isfinite(lng[b])) continue;
     const double E = (double)(I.emin + b * I.binw);
     const double wgt = exp(lng[b] - E / t - mx);
     z += wgt;
     e1 += wgt * E;
   }
-  const double em = e1 / z;
+  z = wave_reduce(z, sum);
+  const double em = wave_reduce(e1, sum) / z;
   double v = 0.0;
-  for (int b = 0; b < I.nbins; ++b) {
+  for (int b = lane; b < I.nbins; b += 64) {
     if (!isfinite(lng[b])) continue;
     const double E = (double)(I.emin + b * I.binw);
     const double wgt = exp(lng[b] - E / t - mx);
     v += wgt * (E - em) * (E - em);
   }
-  P.thermo[kMaxTemps + i] = em;
-  P.thermo[2 * kMaxTemps + i] = (v / z) / (t * t);
+  v = wave_reduce(v, sum);
+  if (lane == 0) {
+    P.thermo[kMaxTemps + i] = em;
+    P.thermo[2 * kMaxTemps + i] = (v / z) / (t * t);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -518,19 +613,38 @@ hipError_t launch_exchange(const DevPtrs& P, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_join(const DevPtrs& P, int32_t instance, int32_t normalise, hipStream_t s) {
-  hipLaunchKernelGGL(k_join, dim3(1), dim3(256), 0, s, P, instance, normalise);
+// LDS representatives of an instance: all of them up to 128 KiB, and always
+// two of its largest windows (8193 bins at most, 128 KiB + 16 B).
+static int join_cap(int reps, int nbmax) {
+  const int most = (128 << 10) / (int)sizeof(double);
+  return reps <= most ? (reps > 2 ? reps : 2) : (2 * nbmax > most ? 2 * nbmax : most);
+}
+
+hipError_t prepare_join_lds() {
+  const int bytes = join_cap(1 << 30, 8193) * (int)sizeof(double);
+  hipError_t e = hipFuncSetAttribute((const void*)k_join, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void*)k_jackknife, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  return e;
+}
+
+hipError_t launch_join(const DevPtrs& P, const InstDesc& I, int32_t reps, int32_t normalise, hipStream_t s) {
+  const int cap = join_cap(reps, I.nbmax);
+  hipLaunchKernelGGL(k_join, dim3(1), dim3(kJoinThreads), (size_t)cap * sizeof(double), s, P, I.inst,
+                     normalise, cap);
   return hipGetLastError();
 }
 
-hipError_t launch_jackknife(const DevPtrs& P, int32_t instance, double* rep, double* jk,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(k_jackknife, dim3(1), dim3(256), 0, s, P, instance, rep, jk);
+hipError_t launch_jackknife(const DevPtrs& P, const InstDesc& I, int32_t reps, double* jk, hipStream_t s) {
+  const int cap = join_cap(reps, I.nbmax);
+  hipLaunchKernelGGL(k_jackknife, dim3(I.m), dim3(kJoinThreads), (size_t)cap * sizeof(double), s, P, I.inst,
+                     jk, cap);
+  hipLaunchKernelGGL(k_jackknife_rows, dim3((I.nbins + 63) / 64), dim3(64), 0, s, P, I.inst, jk);
   return hipGetLastError();
 }
 
 hipError_t launch_thermo(const DevPtrs& P, int32_t instance, int32_t nT, hipStream_t s) {
-  hipLaunchKernelGGL(k_thermo, dim3((nT + 63) / 64), dim3(64), 0, s, P, instance, nT);
+  hipLaunchKernelGGL(k_thermo, dim3((nT + 3) / 4), dim3(256), 0, s, P, instance, nT);
   return hipGetLastError();
 }
 
