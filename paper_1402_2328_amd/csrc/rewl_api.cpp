@@ -572,8 +572,7 @@ int32_t rep_count(const Layout& L, const InstDesc& I) {
 
 int enqueue_cycle(rewl_ctx* c, int64_t flips) {
   hipError_t e = enqueue_sweeps(c, flips);
-  if (e == hipSuccess) e = launch_merge(c->P, c->stream);
-  if (e == hipSuccess) e = launch_exchange(c->P, c->stream);
+  if (e == hipSuccess) e = launch_merge_exchange(c->P, c->stream);
   return hip_rc(e);
 }
 

@@ -137,6 +137,8 @@ hipError_t launch_sweep_fused(const DevPtrs& P, const SweepShape sh[3], int32_t 
                               size_t lds_bytes, bool producer, hipStream_t s);
 hipError_t launch_merge(const DevPtrs& P, hipStream_t s);
 hipError_t launch_exchange(const DevPtrs& P, hipStream_t s);
+// The end of a cycle: launch_merge and launch_exchange in one launch less.
+hipError_t launch_merge_exchange(const DevPtrs& P, hipStream_t s);
 // reps: sum of the instance's window sizes.
 hipError_t launch_join(const DevPtrs& P, const InstDesc& I, int32_t reps, int32_t normalise, hipStream_t s);
 // Leave-one-out joins of an instance's frozen pieces, rows 0..m-1 of jk

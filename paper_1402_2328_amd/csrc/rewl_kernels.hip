@@ -1,12 +1,11 @@
 // REWL kernels for gfx950 (MI355X), everything except the sweep (which is
 // in rewl_sweep.hip and rewl_wave.hip) and the initialisation (rewl_wave.hip).
 //
-// Once per cycle: k_merge_windows (flatness by block reductions
-// and the in-window average), k_merge_finish, k_exchange (Eq. 1, swaps
-// configuration indices, never lattice data), k_exchange_finish.  End of
-// run: k_join (Sec. 3 joining + normalisation in FP64), k_jackknife and
-// k_jackknife_rows (error bars from the m pieces per window) and k_thermo
-// (Sec. 5, Eqs. 7-8).
+// Once per cycle: k_merge_windows (flatness and the in-window average) and
+// k_cycle_end (finished flags; replica exchange by Eq. 1, which swaps
+// configuration indices, never lattice data).  End of run: k_join (Sec. 3
+// joining + normalisation in FP64), k_jackknife and k_jackknife_rows (error
+// bars from the m pieces per window) and k_thermo (Sec. 5, Eqs. 7-8).
 #include <float.h>
 #include <math.h>
 
@@ -101,9 +100,15 @@ __device__ __forceinline__ TwoFloat mean_two_float(const float* hi, const float*
 
 // ---------------------------------------------------------------------------
 // Flatness and in-window merge: one 256-thread block per window.
+//
+// Latency of reading the m histograms bounds it, so the loads of eight
+// walkers are in flight at once, and the flatness test takes one walker per
+// wavefront (a block reduction per walker took 181 us for 64 walkers of a
+// 206-bin window).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_merge_windows(DevPtrs P) {
-  __shared__ uint64_t red64[8];
+  __shared__ uint32_t red[8];
+  __shared__ int not_ready;
   const int gw = blockIdx.x;
   const WinDesc W = P.win[gw];
   const InstDesc& I = P.inst[W.inst];
@@ -112,40 +117,45 @@ __global__ __launch_bounds__(256) void k_merge_windows(DevPtrs P) {
   const int m = I.m, nb = W.nb;
   const int tid = threadIdx.x;
   uint8_t* U = P.U + W.u_base;
+  uint32_t* const H = P.H + W.lng_base;
+  if (tid == 0) not_ready = 0;
 
   // visited union; every walker's H is read here at every check, so the
   // 2^31 guard on the histogram counters sits in this loop
-  uint64_t cnt = 0;
+  uint32_t cnt = 0;
   for (int j = tid; j < nb; j += blockDim.x) {
-    uint8_t u = U[j];
-    for (int k = 0; k < m; ++k) {
-      const uint32_t h = P.H[W.lng_base + (int64_t)k * nb + j];
-      if (h > 0) u = 1;
-      if (h >= 0x80000000u) atomicMin(&P.ist[W.inst].error, -5);
-    }
+    uint32_t any = 0;
+    each_of<uint32_t>(m, [&](int k) { return H[(int64_t)k * nb + j]; },
+                      [&](int, uint32_t h) { any |= h; });
+    if (any & 0x80000000u) atomicMin(&P.ist[W.inst].error, -5);
+    const uint8_t u = any ? 1 : U[j];
     U[j] = u;
     cnt += u;
   }
-  cnt = block_reduce(cnt, [](uint64_t a, uint64_t b) { return a + b; }, red64);
+  cnt = block_reduce(cnt, [](uint32_t a, uint32_t b) { return a + b; }, red);
   const bool one_t = I.schedule == kOneOverT;
   const bool phase_b = one_t && ws0.phase == 1;
-  bool ready = cnt > 0;
-  for (int k = 0; k < m && ready && !phase_b; ++k) {
-    uint64_t mn = UINT64_MAX, sm = 0;
-    for (int j = tid; j < nb; j += blockDim.x) {
-      const uint64_t h = P.H[W.lng_base + (int64_t)k * nb + j];
-      sm += h;
-      if (U[j] && h < mn) mn = h;
+  if (cnt == 0) return;
+  if (!phase_b) {
+    const int lane = tid & 63;
+    volatile int* const stop = &not_ready;
+    for (int k = tid >> 6; k < m && !*stop; k += (int)blockDim.x >> 6) {
+      uint32_t mn = 0xFFFFFFFFu;
+      uint64_t sm = 0;
+      for (int j = lane; j < nb; j += 64) {
+        const uint32_t h = H[(int64_t)k * nb + j];
+        sm += h;
+        if (U[j] && h < mn) mn = h;
+      }
+      mn = wave_reduce(mn, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
+      sm = wave_reduce(sm, [](uint64_t a, uint64_t b) { return a + b; });
+      const bool fails = one_t ? mn == 0
+                               : (uint64_t)I.flat_den * cnt * mn < (uint64_t)I.flat_num * sm;
+      if (fails && lane == 0) *stop = 1;
     }
-    mn = block_reduce(mn, [](uint64_t a, uint64_t b) { return a < b ? a : b; }, red64);
-    sm = block_reduce(sm, [](uint64_t a, uint64_t b) { return a + b; }, red64);
-    if (one_t) {
-      if (mn == 0) ready = false;
-    } else if ((uint64_t)I.flat_den * cnt * mn < (uint64_t)I.flat_num * sm) {
-      ready = false;
-    }
+    __syncthreads();
+    if (not_ready) return;
   }
-  if (!ready) return;
 
   // new ln f: halve (phase A / halving schedule), or 1/t with t the attempts
   // per walker over the visited bins; phase A hands over to B once halving
@@ -158,56 +168,26 @@ __global__ __launch_bounds__(256) void k_merge_windows(DevPtrs P) {
   const bool freezing = next <= I.lnf_final;
 
   for (int j = tid; j < nb; j += blockDim.x) {
+    const int64_t e0 = W.lng_base + j;
     if (P.prec == kFP64) {
-      double v[kMaxWalkersPerWindow];
-      for (int k = 0; k < m; ++k) v[k] = P.lng[W.lng_base + (int64_t)k * nb + j];
       if (freezing)
-        for (int k = 0; k < m; ++k) P.pieces[W.lng_base + (int64_t)k * nb + j] = v[k];
-      int n = m;
-      while (n > 1) {
-        int o = 0;
-        for (int i = 0; i + 1 < n; i += 2) v[o++] = v[i] + v[i + 1];
-        if (n & 1) v[o++] = v[n - 1];
-        n = o;
-      }
-      const double mean = v[0] / (double)m;
+        each_of<double>(m, [&](int k) { return P.lng[e0 + (int64_t)k * nb]; },
+                        [&](int k, double v) { P.pieces[e0 + (int64_t)k * nb] = v; });
+      const double mean = mean_f64(P.lng + e0, nb, m);
       if (!isfinite(mean)) atomicMin(&P.ist[W.inst].error, -4);
-      for (int k = 0; k < m; ++k) P.lng[W.lng_base + (int64_t)k * nb + j] = mean;
+      for (int k = 0; k < m; ++k) P.lng[e0 + (int64_t)k * nb] = mean;
     } else {
-      float vh[kMaxWalkersPerWindow], vl[kMaxWalkersPerWindow];
-      for (int k = 0; k < m; ++k) {
-        vh[k] = P.lhi[W.lng_base + (int64_t)k * nb + j];
-        vl[k] = P.llo[W.lng_base + (int64_t)k * nb + j];
-      }
       if (freezing)
-        for (int k = 0; k < m; ++k)
-          P.pieces[W.lng_base + (int64_t)k * nb + j] = (double)vh[k] + (double)vl[k];
-      int n = m;
-      while (n > 1) {
-        int o = 0;
-        for (int i = 0; i + 1 < n; i += 2) {
-          float a, b;
-          df_add(vh[i], vl[i], vh[i + 1], vl[i + 1], a, b);
-          vh[o] = a;
-          vl[o] = b;
-          ++o;
-        }
-        if (n & 1) {
-          vh[o] = vh[n - 1];
-          vl[o] = vl[n - 1];
-          ++o;
-        }
-        n = o;
-      }
-      float mh, ml;
-      df_div_int(vh[0], vl[0], m, mh, ml);
-      if (!isfinite(mh) || !isfinite(ml)) atomicMin(&P.ist[W.inst].error, -4);
+        each_of<double>(m, [&](int k) { return (double)P.lhi[e0 + (int64_t)k * nb] + (double)P.llo[e0 + (int64_t)k * nb]; },
+                        [&](int k, double v) { P.pieces[e0 + (int64_t)k * nb] = v; });
+      const TwoFloat mean = mean_two_float(P.lhi + e0, P.llo + e0, nb, m);
+      if (!isfinite(mean.h) || !isfinite(mean.l)) atomicMin(&P.ist[W.inst].error, -4);
       for (int k = 0; k < m; ++k) {
-        P.lhi[W.lng_base + (int64_t)k * nb + j] = mh;
-        P.llo[W.lng_base + (int64_t)k * nb + j] = ml;
+        P.lhi[e0 + (int64_t)k * nb] = mean.h;
+        P.llo[e0 + (int64_t)k * nb] = mean.l;
       }
     }
-    for (int k = 0; k < m; ++k) P.H[W.lng_base + (int64_t)k * nb + j] = 0;
+    for (int k = 0; k < m; ++k) H[(int64_t)k * nb + j] = 0;
   }
   if (tid == 0) {
     WinState ws = ws0;
@@ -222,104 +202,107 @@ __global__ __launch_bounds__(256) void k_merge_windows(DevPtrs P) {
   }
 }
 
-__global__ void k_merge_finish(DevPtrs P) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P.n_inst) return;
-  InstState st = P.ist[i];
-  if (st.done || st.error) return;
-  const InstDesc& I = P.inst[i];
-  int all = 1;
-  for (int w = 0; w < I.h; ++w) all &= P.wst[I.win_base + w].frozen;
-  if (all) {
-    st.done = 1;
-    st.done_merge = st.merges;
-  }
-  st.merges += 1;
-  P.ist[i] = st;
-}
+// ---------------------------------------------------------------------------
+// End of a cycle, one 256-thread block per instance: the instance's merge
+// counter and finished flag (merged), then a replica exchange round over its
+// window pairs (exchange).  One launch in place of three: each costs 10 us
+// or so of a small batch's cycle, whose sweep takes 130 us (Ising L = 8).
+// The permutations are drawn by one thread per pair, the swaps made by one
+// wavefront per pair.
+// ---------------------------------------------------------------------------
+constexpr int kPairs = 64;  // window pairs at a time
 
-// ---------------------------------------------------------------------------
-// Replica exchange round: one 64-thread block per lower window w of a pair.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void k_exchange(DevPtrs P) {
-  __shared__ int pi[kMaxWalkersPerWindow];
-  __shared__ uint64_t red[1];
-  const int gw = blockIdx.x;
-  const WinDesc W = P.win[gw];
-  const InstDesc& I = P.inst[W.inst];
-  const InstState st = P.ist[W.inst];
+__global__ __launch_bounds__(256) void k_cycle_end(DevPtrs P, int32_t merged, int32_t exchange) {
+  __shared__ uint8_t pi[kPairs][kMaxWalkersPerWindow];
+  __shared__ int open;
+  const int inst = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = (int)blockDim.x >> 6;
+  const InstDesc& I = P.inst[inst];
+  const InstState st = P.ist[inst];
   if (st.done || st.error) return;
-  const int w = gw - I.win_base;
+  if (merged) {
+    if (tid == 0) open = 0;
+    __syncthreads();
+    for (int w = tid; w < I.h; w += blockDim.x)
+      if (!P.wst[I.win_base + w].frozen) open = 1;
+    __syncthreads();
+    if (tid == 0) {
+      if (!open) {
+        P.ist[inst].done = 1;
+        P.ist[inst].done_merge = st.merges;
+      }
+      P.ist[inst].merges = st.merges + 1;
+    }
+    if (!open) return;
+  }
+  if (!exchange) return;
   const uint64_t t = st.rounds;
-  if ((uint64_t)(w & 1) != (t & 1) || w + 1 >= I.h) return;
   const int m = I.m;
-  const int tid = threadIdx.x;
-  if (tid == 0) {
-    for (int k = 0; k < m; ++k) pi[k] = k;
-    uint4 r = make_uint4(0, 0, 0, 0);
-    int used = 4, call = 0;
-    for (int i = m - 1; i >= 1; --i) {
-      if (used == 4) {
-        r = draw(I, t, ((uint32_t)w << 8) | (uint32_t)call++, kTagPerm);
-        used = 0;
-      }
-      const uint32_t rv = used == 0 ? r.x : used == 1 ? r.y : used == 2 ? r.z : r.w;
-      ++used;
-      const int j = (int)__umulhi(rv, (uint32_t)(i + 1));
-      const int tmp = pi[i];
-      pi[i] = pi[j];
-      pi[j] = tmp;
-    }
-  }
-  __syncthreads();
-  const WinDesc Wn = P.win[gw + 1];
-  uint64_t tries = 0, inr = 0, acc = 0;
-  if (tid < m) {
-    const int li = w * m + tid, lj = (w + 1) * m + pi[tid];
-    const int si = I.slot_base + li, sj = I.slot_base + lj;
-    const int32_t EX = P.E[si], EY = P.E[sj];
-    const int bx = (EX - I.emin) >> I.binw_shift, by = (EY - I.emin) >> I.binw_shift;
-    tries = 1;
-    if (!(by < W.lo || by > W.hi || bx < Wn.lo || bx > Wn.hi)) {
-      inr = 1;
-      const int64_t bi = W.lng_base + (int64_t)tid * W.nb;
-      const int64_t bj = Wn.lng_base + (int64_t)pi[tid] * Wn.nb;
-      const int ix = bx - W.lo, iy = by - W.lo, jx = bx - Wn.lo, jy = by - Wn.lo;
-      const uint4 r = draw(I, t, (uint32_t)li, kTagAcc);
-      bool a;
-      if (P.prec == kFP64) {
-        const double lnP = (P.lng[bi + ix] - P.lng[bi + iy]) + (P.lng[bj + jy] - P.lng[bj + jx]);
-        a = accept64(u53(r.z, r.w), lnP);
-      } else {
-        const float x1 = (P.lhi[bi + ix] - P.lhi[bi + iy]) + (P.llo[bi + ix] - P.llo[bi + iy]);
-        const float x2 = (P.lhi[bj + jy] - P.lhi[bj + jx]) + (P.llo[bj + jy] - P.llo[bj + jx]);
-        a = accept32(r.z >> 8, x1 + x2);
-      }
-      if (a) {
-        acc = 1;
-        const int32_t ci = P.cfg[si];
-        P.cfg[si] = P.cfg[sj];
-        P.cfg[sj] = ci;
-        P.E[si] = EY;
-        P.E[sj] = EX;
+  for (int base = (int)(t & 1); base + 1 < I.h; base += 2 * kPairs) {
+    const int pairs = min((I.h - base) / 2, kPairs);
+    if (tid < pairs) {
+      const int w = base + 2 * tid;
+      uint8_t* const p = pi[tid];
+      for (int k = 0; k < m; ++k) p[k] = (uint8_t)k;
+      uint4 r = make_uint4(0, 0, 0, 0);
+      int used = 4, call = 0;
+      for (int i = m - 1; i >= 1; --i) {
+        if (used == 4) {
+          r = draw(I, t, ((uint32_t)w << 8) | (uint32_t)call++, kTagPerm);
+          used = 0;
+        }
+        const uint32_t rv = used == 0 ? r.x : used == 1 ? r.y : used == 2 ? r.z : r.w;
+        ++used;
+        const int j = (int)__umulhi(rv, (uint32_t)(i + 1));
+        const uint8_t tmp = p[i];
+        p[i] = p[j];
+        p[j] = tmp;
       }
     }
+    __syncthreads();
+    for (int q = wave; q < pairs; q += waves) {
+      const int w = base + 2 * q, gw = I.win_base + w;
+      const WinDesc W = P.win[gw], Wn = P.win[gw + 1];
+      bool inr = false, acc = false;
+      if (lane < m) {
+        const int k = pi[q][lane];
+        const int li = w * m + lane, lj = (w + 1) * m + k;
+        const int si = I.slot_base + li, sj = I.slot_base + lj;
+        const int32_t EX = P.E[si], EY = P.E[sj];
+        const int bx = (EX - I.emin) >> I.binw_shift, by = (EY - I.emin) >> I.binw_shift;
+        if (!(by < W.lo || by > W.hi || bx < Wn.lo || bx > Wn.hi)) {
+          inr = true;
+          const int64_t bi = W.lng_base + (int64_t)lane * W.nb;
+          const int64_t bj = Wn.lng_base + (int64_t)k * Wn.nb;
+          const int ix = bx - W.lo, iy = by - W.lo, jx = bx - Wn.lo, jy = by - Wn.lo;
+          const uint4 r = draw(I, t, (uint32_t)li, kTagAcc);
+          if (P.prec == kFP64) {
+            const double lnP = (P.lng[bi + ix] - P.lng[bi + iy]) + (P.lng[bj + jy] - P.lng[bj + jx]);
+            acc = accept64(u53(r.z, r.w), lnP);
+          } else {
+            const float x1 = (P.lhi[bi + ix] - P.lhi[bi + iy]) + (P.llo[bi + ix] - P.llo[bi + iy]);
+            const float x2 = (P.lhi[bj + jy] - P.lhi[bj + jx]) + (P.llo[bj + jy] - P.llo[bj + jx]);
+            acc = accept32(r.z >> 8, x1 + x2);
+          }
+          if (acc) {
+            const int32_t ci = P.cfg[si];
+            P.cfg[si] = P.cfg[sj];
+            P.cfg[sj] = ci;
+            P.E[si] = EY;
+            P.E[sj] = EX;
+          }
+        }
+      }
+      const int n_inr = __popcll(__ballot(inr)), n_acc = __popcll(__ballot(acc));
+      if (lane == 0) {
+        P.xstats[3 * gw + 0] += (uint64_t)m;
+        P.xstats[3 * gw + 1] += (uint64_t)n_inr;
+        P.xstats[3 * gw + 2] += (uint64_t)n_acc;
+      }
+    }
+    __syncthreads();
   }
-  tries = wave_reduce(tries, [](uint64_t a, uint64_t b) { return a + b; });
-  inr = wave_reduce(inr, [](uint64_t a, uint64_t b) { return a + b; });
-  acc = wave_reduce(acc, [](uint64_t a, uint64_t b) { return a + b; });
-  if (tid == 0) {
-    P.xstats[3 * gw + 0] += tries;
-    P.xstats[3 * gw + 1] += inr;
-    P.xstats[3 * gw + 2] += acc;
-  }
-  (void)red;
-}
-
-__global__ void k_exchange_finish(DevPtrs P) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P.n_inst) return;
-  if (!P.ist[i].done && !P.ist[i].error) P.ist[i].rounds += 1;
+  if (tid == 0) P.ist[inst].rounds = t + 1;
 }
 
 // ---------------------------------------------------------------------------
@@ -603,13 +586,18 @@ __global__ __launch_bounds__(256) void k_thermo(DevPtrs P, int32_t instance, int
 // ---------------------------------------------------------------------------
 hipError_t launch_merge(const DevPtrs& P, hipStream_t s) {
   hipLaunchKernelGGL(k_merge_windows, dim3(P.n_win), dim3(256), 0, s, P);
-  hipLaunchKernelGGL(k_merge_finish, dim3((P.n_inst + 63) / 64), dim3(64), 0, s, P);
+  hipLaunchKernelGGL(k_cycle_end, dim3(P.n_inst), dim3(256), 0, s, P, 1, 0);
   return hipGetLastError();
 }
 
 hipError_t launch_exchange(const DevPtrs& P, hipStream_t s) {
-  hipLaunchKernelGGL(k_exchange, dim3(P.n_win), dim3(64), 0, s, P);
-  hipLaunchKernelGGL(k_exchange_finish, dim3((P.n_inst + 63) / 64), dim3(64), 0, s, P);
+  hipLaunchKernelGGL(k_cycle_end, dim3(P.n_inst), dim3(256), 0, s, P, 0, 1);
+  return hipGetLastError();
+}
+
+hipError_t launch_merge_exchange(const DevPtrs& P, hipStream_t s) {
+  hipLaunchKernelGGL(k_merge_windows, dim3(P.n_win), dim3(256), 0, s, P);
+  hipLaunchKernelGGL(k_cycle_end, dim3(P.n_inst), dim3(256), 0, s, P, 1, 1);
   return hipGetLastError();
 }
 
