@@ -51,6 +51,38 @@ __device__ __forceinline__ uint4 philox_rounds(uint4 c, uint32_t k0, uint32_t k1
   return c;
 }
 
+// Blocks of one walker's stream for attempt numbers n with a common upper
+// half.  With counter (n lo, n hi, w, tag) the first round multiplies n lo and
+// w, and the second one word that only w and n hi enter and one that only n
+// lo and the tag enter.  So the products of w, and one of the second round,
+// are taken once: two of the twenty wide multiplies and their xors less per
+// block.
+struct PhiloxRun {
+  uint32_t y1, z2h, w2;  // lane constants: word 1 after round 1; product of round 2
+  uint32_t tk1, kx2, kz2, k0, k1;
+  PhiloxRun() = default;
+  __device__ __forceinline__ PhiloxRun(uint32_t n_hi, uint32_t w, uint32_t tag, uint32_t key0, uint32_t key1)
+      : tk1(tag ^ key1), kx2(key0 + 0x9E3779B9u), kz2(key1 + 0xBB67AE85u), k0(key0), k1(key1) {
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * w;
+    y1 = (uint32_t)p1;
+    const uint64_t p0 = (uint64_t)0xD2511F53u * ((uint32_t)(p1 >> 32) ^ n_hi ^ key0);
+    z2h = (uint32_t)(p0 >> 32);
+    w2 = (uint32_t)p0;
+  }
+  // Rounds 1 to 4 of the block of attempt n (its lower half).
+  __device__ __forceinline__ uint4 first4(uint32_t n) const {
+    const uint64_t p0 = (uint64_t)0xD2511F53u * n;
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * ((uint32_t)(p0 >> 32) ^ tk1);
+    const uint32_t x = xor3((uint32_t)(p1 >> 32), y1, kx2);
+    const uint32_t z = xor3((uint32_t)p0, z2h, kz2);
+    const uint64_t q0 = (uint64_t)0xD2511F53u * x;
+    const uint64_t q1 = (uint64_t)0xCD9E8D57u * z;
+    const uint4 c = make_uint4(xor3((uint32_t)(q1 >> 32), (uint32_t)p1, k0 + 2u * 0x9E3779B9u), (uint32_t)q1,
+                               xor3((uint32_t)(q0 >> 32), w2, k1 + 2u * 0xBB67AE85u), (uint32_t)q0);
+    return philox_rounds<3, 4>(c, k0, k1);
+  }
+};
+
 // Philox block `idx` of an instance's stream `tag`; w2 is the third counter
 // word (the walker's slot, or what the stream says).
 __device__ __forceinline__ uint4 draw(const InstDesc& I, uint64_t idx, uint32_t w2, uint32_t tag) {
@@ -188,43 +220,40 @@ __device__ __forceinline__ int med3_i32(int a, int b, int c) {
   }
 }
 
-// Fast exact acceptance.  A single-precision estimate e of exp(x), x the
-// clamped delta, from the hardware base-2 exponential of x log2(e) has a
-// relative error below 1e-5: x and log2(e) rounded to float (each < 2^-24
-// relative, |x| <= 40) and the product rounded (< 58 * 2^-24 absolute) shift
-// the exponent by < 1e-5 in total, and the instruction itself is accurate to
-// about one float ulp.  The uniform u = u53 * 2^-53 lies in
-// [hi 2^-32, (hi + 1) 2^-32).  With the slack s = 2^-10, far above that
-// bound and above the float roundings of hi, hi + 1 and the two products
-// (each < 2^-24 relative), u is surely below exp_det(x) when
-// fl(fl(hi) + 1) <= fl(e (1 - s) 2^32), and surely not when
-// fl(hi) > fl(e (1 + s) 2^32); only in between (probability about 2 s e per
+// Fast exact acceptance.  p = 2^(delta log2(e) + 32) from the hardware base-2
+// exponential estimates 2^32 exp(delta) with a relative error below 1e-4:
+// delta rounded to float (< 2^-24 relative, |delta| <= 40 where it counts)
+// and the product plus 32 rounded once (the sum stays below 90, so by less
+// than 4e-6) shift the exponent by less than 1e-5, and the instruction itself
+// is accurate to about one float ulp.  The uniform u = u53 * 2^-53 lies in
+// [hi, hi + 1) 2^-32.  With d = fl(hi) - p and the limit p 2^-10 + 2, far
+// above that error and the roundings of hi, d and the limit (2^-24 relative
+// each), d <= -limit makes u < exp_det(x) certain, x the clamped delta, and d >=
+// limit rules it out; only in between (probability about 2^-9 exp(delta) per
 // attempt) is accept64_flat evaluated.  The decision is therefore always
-// accept64_flat's.  The estimate uses the unclamped delta: for delta >= 0
-// only the first test can hold (e >= 1), and it is right since every such
-// move is accepted; for delta < -40 the second test holds exactly when
-// hi >= 1, and then u >= 2^-32 > exp_det(-40), a rejection; hi = 0 goes to
-// the exact test.
+// accept64_flat's: for delta >= 0 every move is accepted and p >= 2^32 (1 -
+// 1e-4) keeps d below the limit (an infinite p, delta > 66, gives d = -limit:
+// accepted; such moves are common while bins are first visited); for delta <
+// -40, d >= limit holds only for hi >= 2, and then u >= 2^-31 > exp_det(-40),
+// a rejection.  Where delta is not a number no compare holds and the exact
+// test decides.
 __device__ __forceinline__ bool accept64_fast(uint32_t hi, uint32_t lo, double delta) {
-  const float e = __builtin_amdgcn_exp2f((float)delta * 0x1.715476p+0f);
-  const float h = (float)hi;
-  const bool yes = h + 1.0f <= e * 0x1.ff8p+31f;  // (1 - 2^-10) 2^32
-  const bool no = h > e * 0x1.004p+32f;           // (1 + 2^-10) 2^32
-  bool a = yes;
-  if (!yes && !no) a = accept64_flat(hi, lo, delta);
+  const float p = __builtin_amdgcn_exp2f(fmaf((float)delta, 0x1.715476p+0f, 32.0f));
+  const float d = (float)hi - p;
+  const float limit = fmaf(p, 0x1p-10f, 2.0f);
+  bool a = d < 0.0f;
+  if (!(fabsf(d) >= limit)) a = accept64_flat(hi, lo, delta);
   return a;
 }
 
 // The same pre-test for the 24-bit uniform u of accept32_flat (u lies in
 // [u, u + 1) 2^-24 exactly).
 __device__ __forceinline__ bool accept32_fast(uint32_t u, float delta) {
-  const float x = fminf(fmaxf(delta, -17.0f), 0.0f);
-  const double e = (double)__builtin_amdgcn_exp2f(x * 0x1.715476p+0f);
-  const double h = (double)u;
-  const bool yes = h + 1.0 <= e * ((1.0 - 0x1p-10) * 0x1p24);
-  const bool no = h >= e * ((1.0 + 0x1p-10) * 0x1p24);
-  bool a = yes;
-  if (!yes && !no) a = accept32_flat(u, delta);
+  const float p = __builtin_amdgcn_exp2f(fmaf(delta, 0x1.715476p+0f, 24.0f));
+  const float d = (float)u - p;
+  const float limit = fmaf(p, 0x1p-10f, 2.0f);
+  bool a = d < 0.0f;
+  if (!(fabsf(d) >= limit)) a = accept32_flat(u, delta);
   return a;
 }
 

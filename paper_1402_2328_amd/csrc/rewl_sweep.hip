@@ -23,9 +23,18 @@
 // Four compile-time copies of the attempt loop serve any L, L a power of
 // two, Ising L = 32 (one word per row, neighbours by word rotation) and
 // nibble Potts lattices with the neighbour table.
-// LDS is interleaved by lane: element e of lane l sits at e * S + l (S =
-// lanes per workgroup), so the 32-bit words that one instruction touches
-// across the wavefront fall into consecutive banks.  Random numbers come
+// LDS is rows of 32-bit words interleaved by lane: row e of lane l sits at
+// word e * S + l (S = lanes per workgroup), so the words that one instruction
+// touches across the wavefront fall into consecutive banks.  A page slot is
+// three rows next to each other (both words of ln g, then H), so one address
+// serves all three.
+// What bounds it on a full chip is instruction issue, and the clock that the
+// power of the wide multiplies and LDS accesses leaves: 111 vector
+// instructions per wave-attempt on 1024 Ising L = 32 instances (122 with ln
+// g and H as arrays of their own, bins counted from the range's lowest and
+// every Philox round in full), 6.22 against 6.9 ms per sweep of 10^4 attempts
+// with the wavefronts placed alike; 145 against 167 on q = 10 Potts L = 20 in
+// two-float FP32, 4.85 against 6.3 ms.  Random numbers come
 // from Philox4x32-10 keyed by (walker slot, attempt), so results do not
 // depend on the walker-to-lane mapping, page size or launch shape.
 #include <math.h>
@@ -48,6 +57,16 @@ namespace rewl {
 template <typename T>
 __device__ __forceinline__ T* at_off(T* base, uint32_t byte_off) {
   return reinterpret_cast<T*>(reinterpret_cast<unsigned char*>(base) + byte_off);
+}
+
+// The 32-bit LDS word at a byte offset.  The sweep kernels have no static
+// LDS, so their dynamic LDS starts at 0 (prepare_sweep_lds checks it), and
+// offsets are addresses; through a pointer to the array every access would
+// add its base first.
+using LdsWord = __attribute__((address_space(3))) uint32_t;
+__device__ __forceinline__ LdsWord& lds_word(int off) { return *(LdsWord*)(uintptr_t)(uint32_t)off; }
+__device__ __forceinline__ void lds_add(int off, uint32_t v) {  // no return: the lane owns the word
+  (void)__hip_atomic_fetch_add((LdsWord*)(uintptr_t)(uint32_t)off, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // Potts proposal s0 -> v: the new value s0 + 1 + u (u < q - 1) taken
@@ -87,13 +106,16 @@ __device__ __forceinline__ int potts_de(int a, int b, int c, int d, int s0, int 
 // consumes the previous chunk; one workgroup barrier per chunk hands over.
 // This takes the RNG off the walkers' serial chain when few walkers share
 // the chip; the blocks are the ones the walkers would compute themselves.
+// S64: the workgroup's stride is 64 lanes, so that a row is 256 bytes and
+// rows next to each other are reached by offsets in the instruction (one
+// ds_read2st64_b32 for both words of an FP64 ln g).
 // The sweep of workgroup-table entry wgi, with the launch's dynamic LDS.
-template <int MODEL, int PREC, int ROWW, bool PROD>
+template <int MODEL, int PREC, int ROWW, bool PROD, bool S64>
 __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& sh, int64_t flips, int wgi,
                                            unsigned char* lds) {
   const WgDesc wg = P.wg[wgi];
   const InstDesc& Ig = P.inst[wg.inst];
-  const int S = sh.stride;
+  const int S = S64 ? kSweepWave : sh.stride;
   const int NWL = sh.nw;   // lattice words per lane
   const int PG = sh.page;  // page slots per lane, a power of two
   const int PM = PG - 1;
@@ -136,12 +158,6 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   uint32_t* lat = reinterpret_cast<uint32_t*>(lds);                           // [NWL][S]
   unsigned char* latb = lds;                                                   // byte view (Potts)
   // Potts spins: 4-bit nibbles (8 per word; every q <= 16) or bytes
-  unsigned char* pg = lds + (size_t)4 * NWL * S;
-  double* plg = reinterpret_cast<double*>(pg);                                 // [PG][S] FP64
-  float* plh = reinterpret_cast<float*>(pg);                                   // [PG][S] FP32C hi
-  float* pll = plh + (size_t)PG * S;                                           // [PG][S] FP32C lo
-  uint32_t* pH = reinterpret_cast<uint32_t*>(pg + (size_t)8 * PG * S);         // [PG][S]
-
   const int L = Ig.L, N = Ig.N, q = Ig.q, bshift = Ig.binw_shift;
   const bool nib = MODEL == kPotts && sh.nib != 0;
   const uint32_t k0 = Ig.key0, k1 = Ig.key1;
@@ -181,7 +197,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   const int k = loc - w * Ig.m;
   const WinDesc W = P.win[Ig.win_base + w];
   const WinState WS = P.wst[Ig.win_base + w];
-  const int lo = W.lo, hi = W.hi, nb = W.nb;
+  const int nb = W.nb;
   const bool frozen = WS.frozen != 0;
   const double lnf = WS.lnf;
   const float lnf32 = (float)WS.lnf;
@@ -195,20 +211,21 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   const int w0 = loc0 / Ig.m;
   const WinDesc W0 = P.win[Ig.win_base + w0];
   const int64_t gb0 = W0.lng_base + (int64_t)(loc0 - w0 * Ig.m) * W0.nb;
-  const uint32_t eoff = (uint32_t)(W.lng_base + (int64_t)k * nb - gb0) - (uint32_t)lo;  // + bin
+  const uint32_t eoff = (uint32_t)(W.lng_base + (int64_t)k * nb - gb0);  // of the window's lowest bin
   double* const lngw = PREC == kFP64 ? P.lng + gb0 : nullptr;
   float* const lhw = PREC == kFP64 ? nullptr : P.lhi + gb0;
   float* const llw = PREC == kFP64 ? nullptr : P.llo + gb0;
   uint32_t* const Hw = P.H + gb0;
 
-  // the energy is tracked as its bin: E = emin + bin * binw
-  uint64_t att = P.att[g];
-  int bin = (P.E[g] - Ig.emin) >> bshift;
-  if (bin < lo || bin > hi) {
+  // the energy is tracked as its bin, counted from the window's lowest:
+  // E = emin + (lo + bin) * binw
+  const uint64_t att = P.att[g];
+  int bin = ((P.E[g] - Ig.emin) >> bshift) - W.lo;
+  if (bin < 0 || bin >= nb) {
     // only reachable through corrupted state: flag the instance and keep
     // every access inside the window (the instance's results are void)
     atomicMin(&P.ist[wg.inst].error, -6);
-    bin = bin < lo ? lo : hi;
+    bin = bin < 0 ? 0 : nb - 1;
   }
 
   // ---- stage in the lattice ----
@@ -217,18 +234,18 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   if (MODEL == kIsing) {
     for (int y = 0; y < L; ++y) {
       for (int part = 0; part < ROWW; ++part) {
-        uint32_t word = 0;
+        uint32_t bits = 0;
         const int x0 = part * 32;
         const int xe = (L - x0) < 32 ? (L - x0) : 32;
-        for (int b = 0; b < xe; ++b) word |= (uint32_t)(gsp[y * L + x0 + b] > 0) << b;
-        lat[(y * ROWW + part) * S + lane] = word;
+        for (int b = 0; b < xe; ++b) bits |= (uint32_t)(gsp[y * L + x0 + b] > 0) << b;
+        lat[(y * ROWW + part) * S + lane] = bits;
       }
     }
   } else if (nib) {
     for (int i = 0; i < ((N + 7) >> 3); ++i) {
-      uint32_t word = 0;
-      for (int b = 0; b < 8 && 8 * i + b < N; ++b) word |= (uint32_t)(uint8_t)gsp[8 * i + b] << (4 * b);
-      lat[i * S + lane] = word;
+      uint32_t bits = 0;
+      for (int b = 0; b < 8 && 8 * i + b < N; ++b) bits |= (uint32_t)(uint8_t)gsp[8 * i + b] << (4 * b);
+      lat[i * S + lane] = bits;
     }
   } else {
     const uint32_t* src = reinterpret_cast<const uint32_t*>(gsp);
@@ -236,43 +253,61 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
     for (int i = 0; i < nwi; ++i) lat[i * S + lane] = src[i];
   }
 
-  // ---- page: bins [base, base + cnt) of the window, slot of bin b = b & PM
-  const bool paged = nb > PG;
-  int base = lo;
-  if (paged) {
-    base = bin - (PG >> 1);
-    base = base < lo ? lo : base;
-    base = base > hi - PM ? hi - PM : base;
-  }
-  const int cnt = paged ? PG : nb;
-  const int hi_pm = hi - PM;  // highest page start
-  const int m_pm = M - PM;
+  // ---- page: bins [base, base + cnt) of the window, slot of bin b = b & PM.
+  // A slot is three rows of 32-bit words: ln g (FP64 low and high half, or
+  // FP32C high and low part) and the H increments.
+  const int lane4 = lane * 4;
+  const int S4 = S * 4;
+  // byte offset of this lane's word in a row; addresses stay below 2^24, so
+  // 24-bit multiplies (full rate) suffice
+  auto prow = [&](int row) { return S64 ? (row << 8) + lane4 : __mul24(row, S4) + lane4; };
+  const int pg4 = S4 * NWL + lane4;
+  auto pslot = [&](int b) { return __mul24(b & PM, S64 ? 768 : 3 * S4) + pg4; };
+  auto word = [&](int off, int row) -> LdsWord& {
+    return lds_word(off + (S64 ? 256 * row : S4 * row));
+  };
+  auto get64 = [&](int off) { return __hiloint2double((int)word(off, 1), (int)word(off, 0)); };
+  auto put64 = [&](int off, double v) {
+    word(off, 0) = (uint32_t)__double2loint(v);
+    word(off, 1) = (uint32_t)__double2hiint(v);
+  };
+  auto getf = [&](int off, int row) { return __uint_as_float(word(off, row)); };
+  auto putf = [&](int off, int row, float v) { word(off, row) = __float_as_uint(v); };
+  const int cnt = nb < PG ? nb : PG;
+  const int hi_pm = nb - cnt;  // highest page start; 0: the window is in LDS entirely
+  int m_pm = __builtin_amdgcn_readfirstlane(M - PM);
+  asm("" : "+s"(m_pm));  // one scalar, not taken apart into PG and the rest
+  int base = bin - (PG >> 1);
+  base = base > hi_pm ? hi_pm : base;
+  base = base < 0 ? 0 : base;
   for (int i = 0; i < cnt; ++i) {
     const int b = base + i;
-    const int j = __mul24(b & PM, S) + lane;
+    const int j = pslot(b);
     const uint32_t e = eoff + (uint32_t)b;
     if (PREC == kFP64) {
-      plg[j] = *at_off(lngw, e << 3);
+      put64(j, *at_off(lngw, e << 3));
     } else {
-      plh[j] = *at_off(lhw, e << 2);
-      pll[j] = *at_off(llw, e << 2);
+      putf(j, 0, *at_off(lhw, e << 2));
+      putf(j, 1, *at_off(llw, e << 2));
     }
-    pH[j] = 0;
+    word(j, 2) = 0;
   }
   constexpr int DMAX = (MODEL == kPotts) ? 4 : 2;
-  // Bins in flight after a page shift: for slot pend_row[i], the entering
-  // bin's ln g (loaded from device memory) and the leaving bin pend_e[i]
-  // with its ln g and H increments (read from LDS); both are settled one
-  // attempt later, which keeps the LDS read's latency out of the shift.
+  // Bins in flight after a page shift of pend_n bins: slot pend_row[i] holds
+  // the leaving bin of element pend_e + i with its ln g and H increments
+  // (read from LDS) and gets the entering bin's ln g (loaded from device
+  // memory); both are settled one attempt later, which keeps the LDS read's
+  // latency out of the shift.
   int pend_n = 0;
+  uint32_t pend_e = 0u;
   int pend_row[DMAX];
-  uint32_t pend_e[DMAX], ev_h[DMAX];
+  uint32_t ev_h[DMAX];
   double pend_l[DMAX], ev_l[DMAX];
   float pend_hi[DMAX], pend_lo[DMAX], ev_hi[DMAX], ev_lo[DMAX];
 #pragma unroll
   for (int i = 0; i < DMAX; ++i) {
     pend_row[i] = 0;
-    pend_e[i] = ev_h[i] = 0u;
+    ev_h[i] = 0u;
     pend_l[i] = ev_l[i] = 0.0;
     pend_hi[i] = pend_lo[i] = ev_hi[i] = ev_lo[i] = 0.0f;
   }
@@ -280,45 +315,44 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   // stored, H increments added to the histogram in device memory) and the
   // entering bins take their slots.
   auto settle = [&]() {
+    // All lanes' loads have arrived here (vmcnt 0).  Waited for inside the
+    // branch only, the compiler has to take them as pending after it, and
+    // may wait again, then for the stores below as well, where the next
+    // shift reuses their registers.
+    __builtin_amdgcn_s_waitcnt(0x0F70);
 #pragma unroll
     for (int i = 0; i < DMAX; ++i) {
       if (i < pend_n) {
         const int j = pend_row[i];
         if (PREC == kFP64) {
-          plg[j] = pend_l[i];
+          put64(j, pend_l[i]);
         } else {
-          plh[j] = pend_hi[i];
-          pll[j] = pend_lo[i];
+          putf(j, 0, pend_hi[i]);
+          putf(j, 1, pend_lo[i]);
         }
-        pH[j] = 0;
-        const uint32_t e = pend_e[i];
+        word(j, 2) = 0;
         if (PREC == kFP64) {
-          *at_off(lngw, e << 3) = ev_l[i];
+          *at_off(lngw, (pend_e << 3) + 8u * i) = ev_l[i];
         } else {
-          *at_off(lhw, e << 2) = ev_hi[i];
-          *at_off(llw, e << 2) = ev_lo[i];
+          *at_off(lhw, (pend_e << 2) + 4u * i) = ev_hi[i];
+          *at_off(llw, (pend_e << 2) + 4u * i) = ev_lo[i];
         }
-        atomicAdd(at_off(Hw, e << 2), ev_h[i]);
+        atomicAdd(at_off(Hw, (pend_e << 2) + 4u * i), ev_h[i]);
       }
     }
     pend_n = 0;
   };
 
-  int jcur = __mul24(bin & PM, S) + lane;  // LDS row index of the current bin
+  int jcur = pslot(bin);  // LDS offset of the current bin's slot
   double lcur = 0.0;
   float hcur = 0.0f, lcur_lo = 0.0f;
-  if (PREC == kFP64) lcur = plg[jcur];
+  if (PREC == kFP64) lcur = get64(jcur);
   else {
-    hcur = plh[jcur];
-    lcur_lo = pll[jcur];
+    hcur = getf(jcur, 0);
+    lcur_lo = getf(jcur, 1);
   }
 
-  const int lane4 = lane * 4;
-  const int S4 = S * 4;
-  // addresses stay below 2^24, so 24-bit multiplies (full rate) suffice
-  auto pbyte = [&](int site) { return __mul24(site >> 2, S4) + lane4 + (site & 3); };
-
-  auto prow = [&](int row) { return __mul24(row, S) + lane; };
+  auto pbyte = [&](int site) { return prow(site >> 2) + (site & 3); };
   auto pnib = [&](int site) { return prow(site >> 3); };  // word holding a nibble
 
   // Rest of an attempt once the proposal is known: ln g at the proposed
@@ -333,11 +367,11 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
                       uint32_t fm, int site, auto lkt, auto nbt) -> bool {
     constexpr bool NB = decltype(nbt)::value;
     constexpr bool TAB = decltype(lkt)::value == 3;
-    const bool inwin = (bn >= lo) && (bn <= hi);
-    const int jn = prow(bn & PM);
+    const bool inwin = (uint32_t)bn < (uint32_t)nb;
+    const int jn = pslot(bn);
     bool acc;
     if (PREC == kFP64) {
-      const double ln = plg[jn];
+      const double ln = get64(jn);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (!PROD) {
         rn = philox_rounds<4, 7>(rn, k0, k1);
@@ -355,8 +389,8 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       acc = inwin && a;
       lcur = acc ? ln : lcur;
     } else {
-      const float nh = plh[jn];
-      const float nl = pll[jn];
+      const float nh = getf(jn, 0);
+      const float nl = getf(jn, 1);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (!PROD) {
         rn = philox_rounds<4, 7>(rn, k0, k1);
@@ -377,11 +411,11 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
     }
     if (MODEL == kIsing) {
       // the row word is written back either way (unchanged when rejected)
-      *reinterpret_cast<uint32_t*>(lds + wofs) = acc ? wrow ^ fm : wrow;
+      lds_word((int)wofs) = acc ? wrow ^ fm : wrow;
     } else if (acc) {
       if constexpr (NB) {
         const int sh4 = (site & 7) * 4;
-        *reinterpret_cast<uint32_t*>(lds + wofs) = (wrow & ~(15u << sh4)) | ((uint32_t)nv << sh4);
+        lds_word((int)wofs) = (wrow & ~(15u << sh4)) | ((uint32_t)nv << sh4);
       } else {
         latb[pbyte(site)] = (unsigned char)nv;
       }
@@ -392,62 +426,55 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       // frozen walkers add 0.0 and count 0: ln g >= +0 always, so x + 0.0
       // is x bit for bit, and the branch-free form needs no exec mask
       lcur = lcur + lnf_eff;
-      plg[jcur] = lcur;
-      atomicAdd(&pH[jcur], h_inc);
+      put64(jcur, lcur);
+      lds_add(jcur + (S64 ? 512 : 2 * S4), h_inc);
     } else if (!frozen) {
       // a two-float add of 0 could renormalise the pair, so frozen FP32C
       // walkers skip the update instead
       df_add1(hcur, lcur_lo, lnf32, hcur, lcur_lo);
-      plh[jcur] = hcur;
-      pll[jcur] = lcur_lo;
-      atomicAdd(&pH[jcur], 1u);  // no-return LDS add: the lane owns this word
+      putf(jcur, 0, hcur);
+      putf(jcur, 1, lcur_lo);
+      lds_add(jcur + (S64 ? 512 : 2 * S4), 1u);
     }
     // settle the bins of the last shift, then follow the walker
     settle();
-    if (paged) {
-      // bin + M - PM is the lowest page start that still covers bin + M,
-      // bin - M the highest that covers bin - M (PM >= 2M); the start then
-      // stays inside [lo, hi - PM].  Both are integer medians.
-      constexpr bool MA = MODEL == kIsing;  // Ising: 2 % faster; Potts: 1-2 % slower
-      const int nbase = med3_i32<MA>(med3_i32<MA>(base, bin + m_pm, bin - M), lo, hi_pm);
-      const int sft = nbase - base;  // -D..D
-      const bool up = sft > 0;
-      const int shn = up ? sft : -sft;
-      // up: bins base, base+1, .. leave and the bins PG above them enter;
-      // down: bins base+PM, base+PM-1, .. leave and the bins PG below them enter --
-      // each pair shares a slot.  A frozen walker writes back its unchanged
-      // ln g and no H increments.
-      const int stp = up ? 1 : -1;
-      const int ev0 = up ? base : base + PM;
-      const int dpg = __mul24(stp, PG);
+    // bin + M - PM is the lowest page start that still covers bin + M,
+    // bin - M the highest that covers bin - M (PM >= 2M); the start then
+    // stays inside [0, hi_pm] (0 for a window that is in LDS entirely, which
+    // never shifts).  Both are integer medians.
+    constexpr bool MA = MODEL == kIsing;  // Ising: 2 % faster; Potts: 1-2 % slower
+    const int nbase = med3_i32<MA>(med3_i32<MA>(base, bin + m_pm, bin - M), 0, hi_pm);
+    if (nbase != base) {
+      // up: the bins from the old start to the new one leave and those PG
+      // above them enter; down: the bins from the new start to the old one
+      // enter and those PG above them leave.  Either way they are counted
+      // from the lower start, and each pair shares a slot.  A frozen walker
+      // writes back its unchanged ln g and no H increments.
+      const bool up = nbase > base;
+      const int bot = up ? base : nbase;
+      pend_n = (up ? nbase : base) - bot;  // 1..D
+      const uint32_t el = eoff + (uint32_t)bot;
+      pend_e = el + (up ? 0u : (uint32_t)PG);
+      const uint32_t en = el + (up ? (uint32_t)PG : 0u);
+      base = nbase;
 #pragma unroll
       for (int i = 0; i < DMAX; ++i) {
-        if (i < shn) {
-          const int ev = ev0 + i * stp;
-          const uint32_t e = eoff + (uint32_t)ev;
-          const uint32_t en = e + (uint32_t)dpg;
-          const int j = prow(ev & PM);
+        if (i == 0 || i < pend_n) {
+          const int j = pslot(bot + i);
           if (PREC == kFP64) {
-            ev_l[i] = plg[j];
+            pend_l[i] = *at_off(lngw, (en << 3) + 8u * i);
+            ev_l[i] = get64(j);
           } else {
-            ev_hi[i] = plh[j];
-            ev_lo[i] = pll[j];
+            pend_hi[i] = *at_off(lhw, (en << 2) + 4u * i);
+            pend_lo[i] = *at_off(llw, (en << 2) + 4u * i);
+            ev_hi[i] = getf(j, 0);
+            ev_lo[i] = getf(j, 1);
           }
-          ev_h[i] = pH[j];
-          pend_e[i] = e;
-          if (PREC == kFP64) {
-            pend_l[i] = *at_off(lngw, en << 3);
-          } else {
-            pend_hi[i] = *at_off(lhw, en << 2);
-            pend_lo[i] = *at_off(llw, en << 2);
-          }
+          ev_h[i] = word(j, 2);
           pend_row[i] = j;
         }
       }
-      base = nbase;
-      pend_n = shn;
     }
-    ++att;
     return acc;
   };
 
@@ -463,13 +490,11 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   // select compile-time copies of the loop, chosen
   // once per launch, so that no branch splits the attempt's scheduling
   // region.
-  auto attempt = [&](const uint4 r, uint4& rn, auto lkt, auto nbt) {
+  auto attempt = [&](const uint4 r, uint4& rn, const PhiloxRun& pr, uint32_t an, auto lkt, auto nbt) {
     constexpr int LK = decltype(lkt)::value;
     constexpr bool P2 = LK >= 1;
     constexpr bool NB = decltype(nbt)::value;
-    const uint64_t an = att + 1;
-    const uint4 cn = make_uint4((uint32_t)an, (uint32_t)(an >> 32), (uint32_t)loc, tagw);
-    const int site = (int)__umulhi(r.x, (uint32_t)N);
+    const int site = LK == 2 ? (int)(r.x >> 22) : (int)__umulhi(r.x, (uint32_t)N);
     if constexpr (LK == 2) {
       // Ising, L = 32: row y = site / 32 is one word, column x = site % 32.
       // Rotating the row right by x puts the spin at bit 0 and its right
@@ -477,18 +502,28 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       // at bit 0 and the spin at bit 1.  Word shifts and rotations use the
       // low five bits of site, which is x.  The bin step is
       // db = (agreeing neighbours) - 2 (Delta E = 2 s sum, in bins of 4).
-      const int y = site >> 5;
-      const uint32_t aw = __mul24((uint32_t)y, (uint32_t)S4) + (uint32_t)lane4;
-      const uint32_t ad = __mul24((uint32_t)((y + 1) & 31), (uint32_t)S4) + (uint32_t)lane4;
-      const uint32_t au = __mul24((uint32_t)((y - 1) & 31), (uint32_t)S4) + (uint32_t)lane4;
+      // byte offsets of rows y, y + 1 and y - 1 of this lane
+      uint32_t aw, ad, au;
+      if constexpr (S64) {
+        // r.x holds y in its top five bits; 32 rows are 8 KiB, so the wrap
+        // is a mask
+        aw = ((r.x >> 19) & 0x1F00u) | (uint32_t)lane4;
+        ad = (aw + 0x100u) & 0x1FFFu;
+        au = (aw - 0x100u) & 0x1FFFu;
+      } else {
+        const int y = site >> 5;
+        aw = __mul24((uint32_t)y, (uint32_t)S4) + (uint32_t)lane4;
+        ad = __mul24((uint32_t)((y + 1) & 31), (uint32_t)S4) + (uint32_t)lane4;
+        au = __mul24((uint32_t)((y - 1) & 31), (uint32_t)S4) + (uint32_t)lane4;
+      }
       uint32_t awk = aw;
       asm volatile("" : "+v"(awk));  // keep the address for the write-back
-      const uint32_t wrow = *reinterpret_cast<const uint32_t*>(lds + awk);
-      const uint32_t wd = *reinterpret_cast<const uint32_t*>(lds + ad);
-      const uint32_t wu = *reinterpret_cast<const uint32_t*>(lds + au);
+      const uint32_t wrow = lds_word((int)awk);
+      const uint32_t wd = lds_word((int)ad);
+      const uint32_t wu = lds_word((int)au);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (!PROD) {
-        rn = philox_rounds<0, 4>(cn, k0, k1);
+        rn = pr.first4(an);
         REWL_PIN4(rn);
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -509,17 +544,17 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       const uint2 e = tab_e;
       // byte offset of lattice word wd of this lane: wd * 4S + 4 lane
       auto word_at = [&](uint32_t wd) {
-        return *reinterpret_cast<const uint32_t*>(lds + __mul24(wd, (uint32_t)S4) + (uint32_t)lane4);
+        return lds_word(prow((int)wd));
       };
-      const uint32_t wofs = __mul24((uint32_t)site >> 3, (uint32_t)S4) + (uint32_t)lane4;
-      const uint32_t w0 = *reinterpret_cast<const uint32_t*>(lds + wofs);
+      const uint32_t wofs = (uint32_t)pnib(site);
+      const uint32_t w0 = lds_word((int)wofs);
       const uint32_t w1 = word_at(__builtin_amdgcn_ubfe(e.x, 0, 9));
       const uint32_t w2 = word_at(__builtin_amdgcn_ubfe(e.x, 14, 9));
       const uint32_t w3 = word_at(__builtin_amdgcn_ubfe(e.y, 0, 9));
       const uint32_t w4 = word_at(__builtin_amdgcn_ubfe(e.y, 14, 9));
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (!PROD) {
-        rn = philox_rounds<0, 4>(cn, k0, k1);
+        rn = pr.first4(an);
         REWL_PIN4(rn);
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -560,12 +595,12 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       int s0, a, b, c, d;
       if (ROWW == 1) {
         widx = prow(y);
-        wrow = lat[widx];
-        const uint32_t wu = lat[prow(yu)];
-        const uint32_t wd = lat[prow(yd)];
+        wrow = lds_word(widx);
+        const uint32_t wu = lds_word(prow(yu));
+        const uint32_t wd = lds_word(prow(yd));
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (!PROD) {
-          rn = philox_rounds<0, 4>(cn, k0, k1);
+          rn = pr.first4(an);
           REWL_PIN4(rn);
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -576,13 +611,13 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
         d = (wu >> x) & 1;
       } else {
         const int px = x >> 5;
-        const uint32_t r0 = lat[prow(2 * y)];
-        const uint32_t r1 = lat[prow(2 * y + 1)];
-        const uint32_t wu = lat[prow(2 * yu + px)];
-        const uint32_t wd = lat[prow(2 * yd + px)];
+        const uint32_t r0 = lds_word(prow(2 * y));
+        const uint32_t r1 = lds_word(prow(2 * y + 1));
+        const uint32_t wu = lds_word(prow(2 * yu + px));
+        const uint32_t wd = lds_word(prow(2 * yd + px));
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (!PROD) {
-          rn = philox_rounds<0, 4>(cn, k0, k1);
+          rn = pr.first4(an);
           REWL_PIN4(rn);
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -603,12 +638,12 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       if constexpr (NB) {
         const int sa = rowy + xr, sb = rowy + xl, sc = __mul24(yd, L) + x, sd = __mul24(yu, L) + x;
         widx = pnib(site);
-        wrow = lat[widx];
+        wrow = lds_word(widx);
         s0 = (int)__builtin_amdgcn_ubfe(wrow, (site & 7) * 4, 4);
-        a = (int)__builtin_amdgcn_ubfe(lat[pnib(sa)], (sa & 7) * 4, 4);
-        b = (int)__builtin_amdgcn_ubfe(lat[pnib(sb)], (sb & 7) * 4, 4);
-        c = (int)__builtin_amdgcn_ubfe(lat[pnib(sc)], (sc & 7) * 4, 4);
-        d = (int)__builtin_amdgcn_ubfe(lat[pnib(sd)], (sd & 7) * 4, 4);
+        a = (int)__builtin_amdgcn_ubfe(lds_word(pnib(sa)), (sa & 7) * 4, 4);
+        b = (int)__builtin_amdgcn_ubfe(lds_word(pnib(sb)), (sb & 7) * 4, 4);
+        c = (int)__builtin_amdgcn_ubfe(lds_word(pnib(sc)), (sc & 7) * 4, 4);
+        d = (int)__builtin_amdgcn_ubfe(lds_word(pnib(sd)), (sd & 7) * 4, 4);
       } else {
         s0 = (int)latb[pbyte(site)];
         a = (int)latb[pbyte(rowy + xr)];
@@ -618,7 +653,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       }
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (!PROD) {
-        rn = philox_rounds<0, 4>(cn, k0, k1);
+        rn = pr.first4(an);
         REWL_PIN4(rn);
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -626,7 +661,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       nv = v;
       db = (NB ? potts_de<4>(a, b, c, d, s0, v) : potts_de<8>(a, b, c, d, s0, v)) >> bshift;
     }
-    complete(r, rn, bin + db, nv, 4u * (uint32_t)widx, wrow, fm, site, lkt, nbt);
+    complete(r, rn, bin + db, nv, (uint32_t)widx, wrow, fm, site, lkt, nbt);
   };
 
 
@@ -636,13 +671,25 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   auto run = [&](auto lkt, auto nbt) {
     constexpr bool TAB = decltype(lkt)::value == 3;
     if constexpr (!PROD) {
-      uint4 r = philox10(make_uint4((uint32_t)att, (uint32_t)(att >> 32), (uint32_t)loc, tagw), k0, k1);
+      uint64_t an = att;  // attempt of block r
+      uint4 r = philox10(make_uint4((uint32_t)an, (uint32_t)(an >> 32), (uint32_t)loc, tagw), k0, k1);
       if constexpr (TAB) tab_e = tab[__umulhi(r.x, (uint32_t)N)];
-      for (int64_t t = 0; t < flips; ++t) {
-        uint4 rn;
-        attempt(r, rn, lkt, nbt);
-        r = rn;
-        if constexpr (TAB) tab_e = tab_en;
+      for (int64_t left = flips; left > 0;) {
+        // the blocks up to a wrap of the number's lower half share a
+        // PhiloxRun; near one (every 2^32 attempts) each gets its own
+        ++an;
+        const PhiloxRun pr((uint32_t)(an >> 32), (uint32_t)loc, tagw, k0, k1);
+        const bool wraps = 0x100000000ull - (uint32_t)an < (uint64_t)left;
+        const int64_t n = __ballot(wraps) ? 1 : left;
+        uint32_t an_lo = (uint32_t)an;
+        for (int64_t t = 0; t < n; ++t) {
+          uint4 rn;
+          attempt(r, rn, pr, an_lo++, lkt, nbt);
+          r = rn;
+          if constexpr (TAB) tab_e = tab_en;
+        }
+        an += (uint64_t)(n - 1);
+        left -= n;
       }
     } else {
       __syncthreads();  // chunk 0 is in the buffer
@@ -655,7 +702,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
           const uint4 rnext = src[(size_t)(i + 1 < n ? i + 1 : i) * S];
           if constexpr (TAB) tab_en = tab[__umulhi(rnext.x, (uint32_t)N)];
           uint4 unused;
-          attempt(r, unused, lkt, nbt);
+          attempt(r, unused, PhiloxRun(), 0u, lkt, nbt);
           r = rnext;
           if constexpr (TAB) tab_e = tab_en;
         }
@@ -684,55 +731,55 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   if (!frozen) {
     for (int i = 0; i < cnt; ++i) {
       const int b = base + i;
-      const int j = prow(b & PM);
+      const int j = pslot(b);
       const uint32_t e = eoff + (uint32_t)b;
       if (PREC == kFP64) {
-        *at_off(lngw, e << 3) = plg[j];
+        *at_off(lngw, e << 3) = get64(j);
       } else {
-        *at_off(lhw, e << 2) = plh[j];
-        *at_off(llw, e << 2) = pll[j];
+        *at_off(lhw, e << 2) = getf(j, 0);
+        *at_off(llw, e << 2) = getf(j, 1);
       }
-      const uint32_t h = pH[j];
+      const uint32_t h = word(j, 2);
       if (h) atomicAdd(at_off(Hw, e << 2), h);
     }
   }
   if (MODEL == kIsing) {
     for (int y = 0; y < L; ++y) {
       for (int part = 0; part < ROWW; ++part) {
-        const uint32_t word = lat[(y * ROWW + part) * S + lane];
+        const uint32_t bits = lat[(y * ROWW + part) * S + lane];
         const int x0 = part * 32;
         const int xe = (L - x0) < 32 ? (L - x0) : 32;
-        for (int b = 0; b < xe; ++b) gsp[y * L + x0 + b] = ((word >> b) & 1) ? 1 : -1;
+        for (int b = 0; b < xe; ++b) gsp[y * L + x0 + b] = ((bits >> b) & 1) ? 1 : -1;
       }
     }
   } else if (nib) {
     for (int i = 0; i < ((N + 7) >> 3); ++i) {
-      const uint32_t word = lat[i * S + lane];
-      for (int b = 0; b < 8 && 8 * i + b < N; ++b) gsp[8 * i + b] = (int8_t)((word >> (4 * b)) & 15);
+      const uint32_t bits = lat[i * S + lane];
+      for (int b = 0; b < 8 && 8 * i + b < N; ++b) gsp[8 * i + b] = (int8_t)((bits >> (4 * b)) & 15);
     }
   } else {
     uint32_t* dst = reinterpret_cast<uint32_t*>(gsp);
     const int nwi = (N + 3) >> 2;
     for (int i = 0; i < nwi; ++i) dst[i] = lat[i * S + lane];
   }
-  P.E[g] = Ig.emin + (bin << bshift);  // every energy sits on the bin grid
-  P.att[g] = att;
+  P.E[g] = Ig.emin + ((W.lo + bin) << bshift);  // every energy sits on the bin grid
+  P.att[g] = att + (uint64_t)flips;
 }
 
 // One kernel class per launch: the class's workgroups are entries
 // [sh.wg_offset, sh.wg_offset + gridDim.x) of the table.
-template <int MODEL, int PREC, int ROWW, bool PROD>
+template <int MODEL, int PREC, int ROWW, bool PROD, bool S64>
 __global__ __launch_bounds__(PROD ? 2 * kSweepWave : kSweepWave) void k_sweep(DevPtrs P, SweepShape sh,
                                                                                 int64_t flips) {
   extern __shared__ __align__(16) unsigned char lds[];
-  sweep_body<MODEL, PREC, ROWW, PROD>(P, sh, flips, sh.wg_offset + (int)blockIdx.x, lds);
+  sweep_body<MODEL, PREC, ROWW, PROD, S64>(P, sh, flips, sh.wg_offset + (int)blockIdx.x, lds);
 }
 
 // Every kernel class of a batch in one launch: workgroup b runs table entry
 // b with the loop of its class (all its lanes take the same branch), in
 // the LDS size of the largest class.  The table order decides which
 // workgroups the hardware dispatches first.
-template <int PREC, bool PROD>
+template <int PREC, bool PROD, bool S64>
 __global__ __launch_bounds__(PROD ? 2 * kSweepWave : kSweepWave) void k_sweep_fused(DevPtrs P, SweepShape s0,
                                                                                       SweepShape s1,
                                                                                       SweepShape s2,
@@ -740,62 +787,73 @@ __global__ __launch_bounds__(PROD ? 2 * kSweepWave : kSweepWave) void k_sweep_fu
   extern __shared__ __align__(16) unsigned char lds[];
   const int wgi = (int)blockIdx.x;
   const int cls = P.wg[wgi].cls;
-  if (cls == 0) sweep_body<kIsing, PREC, 1, PROD>(P, s0, flips, wgi, lds);
-  else if (cls == 1) sweep_body<kIsing, PREC, 2, PROD>(P, s1, flips, wgi, lds);
-  else sweep_body<kPotts, PREC, 0, PROD>(P, s2, flips, wgi, lds);
+  if (cls == 0) sweep_body<kIsing, PREC, 1, PROD, S64>(P, s0, flips, wgi, lds);
+  else if (cls == 1) sweep_body<kIsing, PREC, 2, PROD, S64>(P, s1, flips, wgi, lds);
+  else sweep_body<kPotts, PREC, 0, PROD, S64>(P, s2, flips, wgi, lds);
 }
+
+namespace {
+
+using SweepFn = void (*)(DevPtrs, SweepShape, int64_t);
+using FusedFn = void (*)(DevPtrs, SweepShape, SweepShape, SweepShape, int64_t);
+
+template <int PREC, bool PROD, bool S64>
+SweepFn sweep_fn(int cls) {
+  return cls == 0 ? k_sweep<kIsing, PREC, 1, PROD, S64>
+                  : cls == 1 ? k_sweep<kIsing, PREC, 2, PROD, S64> : k_sweep<kPotts, PREC, 0, PROD, S64>;
+}
+
+SweepFn sweep_fn(int prec, bool prod, bool s64, int cls) {
+  if (prec == kFP64)
+    return prod ? (s64 ? sweep_fn<kFP64, true, true>(cls) : sweep_fn<kFP64, true, false>(cls))
+                : (s64 ? sweep_fn<kFP64, false, true>(cls) : sweep_fn<kFP64, false, false>(cls));
+  return prod ? (s64 ? sweep_fn<kFP32C, true, true>(cls) : sweep_fn<kFP32C, true, false>(cls))
+              : (s64 ? sweep_fn<kFP32C, false, true>(cls) : sweep_fn<kFP32C, false, false>(cls));
+}
+
+FusedFn fused_fn(int prec, bool prod, bool s64) {
+  if (prec == kFP64)
+    return prod ? (s64 ? k_sweep_fused<kFP64, true, true> : k_sweep_fused<kFP64, true, false>)
+                : (s64 ? k_sweep_fused<kFP64, false, true> : k_sweep_fused<kFP64, false, false>);
+  return prod ? (s64 ? k_sweep_fused<kFP32C, true, true> : k_sweep_fused<kFP32C, true, false>)
+              : (s64 ? k_sweep_fused<kFP32C, false, true> : k_sweep_fused<kFP32C, false, false>);
+}
+
+}  // namespace
 
 hipError_t prepare_sweep_lds(size_t lds_bytes) {
-  const void* fns[] = {
-      (const void*)k_sweep<kIsing, kFP64, 1, false>,  (const void*)k_sweep<kIsing, kFP64, 2, false>,
-      (const void*)k_sweep<kPotts, kFP64, 0, false>,  (const void*)k_sweep<kIsing, kFP32C, 1, false>,
-      (const void*)k_sweep<kIsing, kFP32C, 2, false>, (const void*)k_sweep<kPotts, kFP32C, 0, false>,
-      (const void*)k_sweep<kIsing, kFP64, 1, true>,   (const void*)k_sweep<kIsing, kFP64, 2, true>,
-      (const void*)k_sweep<kPotts, kFP64, 0, true>,   (const void*)k_sweep<kIsing, kFP32C, 1, true>,
-      (const void*)k_sweep<kIsing, kFP32C, 2, true>,  (const void*)k_sweep<kPotts, kFP32C, 0, true>,
-      (const void*)k_sweep_fused<kFP64, false>,       (const void*)k_sweep_fused<kFP64, true>,
-      (const void*)k_sweep_fused<kFP32C, false>,      (const void*)k_sweep_fused<kFP32C, true>};
-  for (const void* f : fns) {
-    hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    if (e != hipSuccess) return e;
+  for (int i = 0; i < 8; ++i) {
+    const int prec = i & 1 ? kFP32C : kFP64;
+    const bool prod = (i & 2) != 0, s64 = (i & 4) != 0;
+    const void* fns[] = {(const void*)sweep_fn(prec, prod, s64, 0), (const void*)sweep_fn(prec, prod, s64, 1),
+                         (const void*)sweep_fn(prec, prod, s64, 2), (const void*)fused_fn(prec, prod, s64)};
+    for (const void* f : fns) {
+      hipFuncAttributes at;
+      hipError_t e = hipFuncGetAttributes(&at, f);
+      if (e != hipSuccess) return e;
+      if (at.sharedSizeBytes != 0) return hipErrorInvalidValue;  // dynamic LDS must start at 0
+      e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+      if (e != hipSuccess) return e;
+    }
   }
   return hipSuccess;
-}
-
-template <bool PROD>
-void launch_class(const DevPtrs& P, int cls, SweepShape sh, dim3 grid, int64_t flips, size_t lds_bytes,
-                  hipStream_t s) {
-  const dim3 blk(PROD ? 2 * kSweepWave : kSweepWave);
-  if (P.prec == kFP64) {
-    if (cls == 0) hipLaunchKernelGGL((k_sweep<kIsing, kFP64, 1, PROD>), grid, blk, lds_bytes, s, P, sh, flips);
-    if (cls == 1) hipLaunchKernelGGL((k_sweep<kIsing, kFP64, 2, PROD>), grid, blk, lds_bytes, s, P, sh, flips);
-    if (cls == 2) hipLaunchKernelGGL((k_sweep<kPotts, kFP64, 0, PROD>), grid, blk, lds_bytes, s, P, sh, flips);
-  } else {
-    if (cls == 0) hipLaunchKernelGGL((k_sweep<kIsing, kFP32C, 1, PROD>), grid, blk, lds_bytes, s, P, sh, flips);
-    if (cls == 1) hipLaunchKernelGGL((k_sweep<kIsing, kFP32C, 2, PROD>), grid, blk, lds_bytes, s, P, sh, flips);
-    if (cls == 2) hipLaunchKernelGGL((k_sweep<kPotts, kFP32C, 0, PROD>), grid, blk, lds_bytes, s, P, sh, flips);
-  }
 }
 
 hipError_t launch_sweep_class(const DevPtrs& P, int cls, SweepShape sh, int32_t n_wg, int64_t flips,
                               size_t lds_bytes, bool producer, hipStream_t s) {
   if (n_wg <= 0) return hipSuccess;
-  if (producer) launch_class<true>(P, cls, sh, dim3(n_wg), flips, lds_bytes, s);
-  else launch_class<false>(P, cls, sh, dim3(n_wg), flips, lds_bytes, s);
+  const SweepFn f = sweep_fn(P.prec, producer, sh.stride == kSweepWave, cls);
+  hipLaunchKernelGGL(f, dim3(n_wg), dim3(producer ? 2 * kSweepWave : kSweepWave), lds_bytes, s, P, sh, flips);
   return hipGetLastError();
 }
 
 hipError_t launch_sweep_fused(const DevPtrs& P, const SweepShape sh[3], int32_t n_wg, int64_t flips,
                               size_t lds_bytes, bool producer, hipStream_t s) {
   if (n_wg <= 0) return hipSuccess;
-  const dim3 grid(n_wg), blk(producer ? 2 * kSweepWave : kSweepWave);
-  if (P.prec == kFP64) {
-    if (producer) hipLaunchKernelGGL((k_sweep_fused<kFP64, true>), grid, blk, lds_bytes, s, P, sh[0], sh[1], sh[2], flips);
-    else hipLaunchKernelGGL((k_sweep_fused<kFP64, false>), grid, blk, lds_bytes, s, P, sh[0], sh[1], sh[2], flips);
-  } else {
-    if (producer) hipLaunchKernelGGL((k_sweep_fused<kFP32C, true>), grid, blk, lds_bytes, s, P, sh[0], sh[1], sh[2], flips);
-    else hipLaunchKernelGGL((k_sweep_fused<kFP32C, false>), grid, blk, lds_bytes, s, P, sh[0], sh[1], sh[2], flips);
-  }
+  bool s64 = true;  // a class that is absent has stride 0
+  for (int cls = 0; cls < 3; ++cls) s64 = s64 && (sh[cls].stride == kSweepWave || sh[cls].stride == 0);
+  hipLaunchKernelGGL(fused_fn(P.prec, producer, s64), dim3(n_wg), dim3(producer ? 2 * kSweepWave : kSweepWave),
+                     lds_bytes, s, P, sh[0], sh[1], sh[2], flips);
   return hipGetLastError();
 }
 
