@@ -425,6 +425,7 @@ struct rewl_ctx {
   int64_t graph_cycles = 0;
   // the allocation-free jackknife's device array on this context's GPU
   double* scratch = nullptr;
+  int n_cu = 256;
 };
 
 namespace {
@@ -493,6 +494,7 @@ int64_t part_flips(int64_t flips, int parts, int k) {
 hipError_t enqueue_sweeps(rewl_ctx* c, int64_t flips) {
   const int parts = std::max(1, c->plan.splits);
   hipError_t e = hipSuccess;
+  if (flips >= kEvenOutFlips && (int)c->plan.wg.size() >= c->n_cu) e = launch_even_out(c->n_cu, c->stream);
   if (c->plan.fused) {
     SweepShape sh[3];
     size_t lds = 0;
@@ -513,7 +515,7 @@ hipError_t enqueue_sweeps(rewl_ctx* c, int64_t flips) {
   for (int cls = 0; cls < 3; ++cls)
     if (c->plan.cls[cls].count > 0) active[n++] = cls;
   const bool fork = n > 1 && c->side[0] != nullptr;
-  if (fork) {
+  if (fork && e == hipSuccess) {
     e = hipEventRecord(c->fork, c->stream);
     for (int i = 1; i < n && e == hipSuccess; ++i) e = hipStreamWaitEvent(c->side[i - 1], c->fork, 0);
   }
@@ -611,6 +613,7 @@ int rewl_init(const rewl_params* params, int32_t n, const int32_t* win_lo, const
   }
   c->ws = static_cast<unsigned char*>(d_workspace);
   c->ws_bytes = workspace_bytes;
+  c->n_cu = n_compute_units();
   c->stream = static_cast<hipStream_t>(stream);
   fill_ptrs(c);
   const Layout& L = c->lo;

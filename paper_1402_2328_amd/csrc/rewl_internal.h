@@ -126,6 +126,11 @@ hipError_t launch_init(const DevPtrs& P, int32_t lat_bytes, hipStream_t s);
 // producer: a second wavefront per workgroup computes the random numbers.
 hipError_t launch_sweep_class(const DevPtrs& P, int cls, SweepShape sh, int32_t n_wg, int64_t flips,
                               size_t lds_bytes, bool producer, hipStream_t s);
+// Deals the wavefronts of the next launch evenly to the SIMDs of every
+// compute unit; before a sweep of at least as many workgroups as there are.
+hipError_t launch_even_out(int32_t n_cu, hipStream_t s);
+// Shorter sweeps (attempts per walker) do without: they take less than 70 us.
+constexpr int64_t kEvenOutFlips = 512;
 // One wavefront per walker: n_wg entries of the table from wg_offset, each of
 // one walker of class cls; lat_bytes: spins of the class's largest lattice,
 // rounded up to 16.
