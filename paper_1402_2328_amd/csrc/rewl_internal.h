@@ -100,7 +100,7 @@ struct DevPtrs {
   uint8_t* U;                // visited-union masks per window
   double* rep;               // window representatives for joining
   double* R;                 // joined ln g per instance
-  double* thermo;            // [3][kMaxTemps]: T, <E>, C_V
+  double* thermo;            // 3 kMaxTemps: T, then from kMaxTemps on nT <E> and nT C_V
   int32_t* joins;            // [windows] join bin of (w-1, w)
   double* jk;                // jackknife scratch: (m + 2) x nbins of one instance
   int32_t n_inst, n_win, n_slots, n_wg;
@@ -144,8 +144,10 @@ hipError_t launch_merge(const DevPtrs& P, hipStream_t s);
 hipError_t launch_exchange(const DevPtrs& P, hipStream_t s);
 // The end of a cycle: launch_merge and launch_exchange in one launch less.
 hipError_t launch_merge_exchange(const DevPtrs& P, hipStream_t s);
-// reps: sum of the instance's window sizes.
-hipError_t launch_join(const DevPtrs& P, const InstDesc& I, int32_t reps, int32_t normalise, hipStream_t s);
+// reps: sum of the instance's window sizes; packed: null, or room for the
+// joined curve (nbins doubles) followed by the h - 1 join bins (int32).
+hipError_t launch_join(const DevPtrs& P, const InstDesc& I, int32_t reps, int32_t normalise, double* packed,
+                       hipStream_t s);
 // Leave-one-out joins of an instance's frozen pieces, rows 0..m-1 of jk
 // ((m + 2) x nbins); mean and error land in rows m and m + 1.
 hipError_t launch_jackknife(const DevPtrs& P, const InstDesc& I, int32_t reps, double* jk, hipStream_t s);

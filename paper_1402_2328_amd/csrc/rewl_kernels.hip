@@ -448,11 +448,12 @@ __device__ void join_windows(const DevPtrs& P, const InstDesc& I, RepOf rep_of, 
 
 // Window representatives: mean over walkers, same tree as the merge.
 __global__ __launch_bounds__(kJoinThreads) void k_join(DevPtrs P, int32_t instance, int32_t normalise,
-                                                       int32_t cap) {
+                                                       int32_t cap, double* packed) {
   extern __shared__ __align__(16) double join_rep[];
   __shared__ JoinShared S;
   const InstDesc& I = P.inst[instance];
   const int m = I.m;
+  double* const R = P.R + I.r_base;
   join_windows(
       P, I,
       [&](const WinDesc& W, int j) {
@@ -461,7 +462,13 @@ __global__ __launch_bounds__(kJoinThreads) void k_join(DevPtrs P, int32_t instan
         const TwoFloat r = mean_two_float(P.lhi + e0, P.llo + e0, W.nb, m);
         return (double)r.h + (double)r.l;
       },
-      join_rep, cap, P.R + I.r_base, normalise, true, S);
+      join_rep, cap, R, normalise, true, S);
+  // the curve and the join bins next to each other, for one copy to the host
+  if (!packed) return;
+  __syncthreads();
+  for (int b = threadIdx.x; b < I.nbins; b += blockDim.x) packed[b] = R[b];
+  int32_t* const joins = reinterpret_cast<int32_t*>(packed + I.nbins);
+  for (int w = 1 + (int)threadIdx.x; w < I.h; w += blockDim.x) joins[w - 1] = P.joins[I.win_base + w];
 }
 
 // Jackknife over the m pieces per window (Sec. 3): block k joins and
@@ -577,7 +584,7 @@ __global__ __launch_bounds__(256) void k_thermo(DevPtrs P, int32_t instance, int
   v = wave_reduce(v, sum);
   if (lane == 0) {
     P.thermo[kMaxTemps + i] = em;
-    P.thermo[2 * kMaxTemps + i] = (v / z) / (t * t);
+    P.thermo[kMaxTemps + nT + i] = (v / z) / (t * t);
   }
 }
 
@@ -616,10 +623,11 @@ hipError_t prepare_join_lds() {
   return e;
 }
 
-hipError_t launch_join(const DevPtrs& P, const InstDesc& I, int32_t reps, int32_t normalise, hipStream_t s) {
+hipError_t launch_join(const DevPtrs& P, const InstDesc& I, int32_t reps, int32_t normalise, double* packed,
+                       hipStream_t s) {
   const int cap = join_cap(reps, I.nbmax);
   hipLaunchKernelGGL(k_join, dim3(1), dim3(kJoinThreads), (size_t)cap * sizeof(double), s, P, I.inst,
-                     normalise, cap);
+                     normalise, cap, packed);
   return hipGetLastError();
 }
 
