@@ -44,6 +44,7 @@ struct Layout {
   int32_t potts3[3] = {0, 0, 0};
   int32_t walkers[3] = {0, 0, 0};
   int32_t n_max[3] = {0, 0, 0};          // most sites of an instance
+  int32_t l_min[3] = {kMaxL, kMaxL, kMaxL};  // side of the smallest lattice
   int32_t prec = 0;
   // byte offsets inside the workspace
   int64_t jk_elems = 0;  // largest (m + 2) * nbins of any instance
@@ -164,6 +165,7 @@ int build_layout(const rewl_params* params, int32_t n, const int32_t* wlo, const
     Lo.potts3[cls] |= (I.model == REWL_POTTS && I.q >= 3);
     Lo.walkers[cls] += I.W;
     Lo.n_max[cls] = std::max(Lo.n_max[cls], I.N);
+    Lo.l_min[cls] = std::min(Lo.l_min[cls], I.L);
     slot += I.W;
     win += I.h;
     spin += (int64_t)I.W * I.npad;
@@ -540,7 +542,7 @@ hipError_t enqueue_sweeps(rewl_ctx* c, int64_t flips) {
     for (int k = 0; k < parts && e == hipSuccess; ++k) {
       const int64_t f = part_flips(flips, parts, k);
       if (f <= 0) continue;
-      if (cp.wave) e = launch_sweep_wave(c->P, cls, cp.offset, cp.count, wave_lat_bytes(c->lo, cls), f, s);
+      if (cp.wave) e = launch_sweep_wave(c->P, cls, cp.offset, cp.count, wave_lat_bytes(c->lo, cls), c->lo.l_min[cls], f, s);
       else e = launch_sweep_class(c->P, cls, sh, cp.count, f, cp.lds_bytes, cp.prod != 0, s);
     }
   }
@@ -719,7 +721,7 @@ void plan_out(const Layout& Lo, const LaunchPlan& pl, int32_t* out) {
     const bool wave = pl.cls[cls].wave && !pl.fused;
     out[6 * cls + 0] = pl.cls[cls].P;
     out[6 * cls + 1] = wave ? 1 : pl.cls[cls].G;
-    out[6 * cls + 2] = wave ? 2 * wave_lat_bytes(Lo, cls) : (int32_t)pl.cls[cls].lds_bytes;
+    out[6 * cls + 2] = wave ? wave_lds_bytes(cls, wave_lat_bytes(Lo, cls), Lo.l_min[cls]) : (int32_t)pl.cls[cls].lds_bytes;
     out[6 * cls + 3] = pl.cls[cls].count;
     out[6 * cls + 4] = pl.cls[cls].prod;
     out[6 * cls + 5] = pl.cls[cls].nib;

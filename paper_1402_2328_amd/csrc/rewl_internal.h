@@ -133,9 +133,18 @@ hipError_t launch_even_out(int32_t n_cu, hipStream_t s);
 constexpr int64_t kEvenOutFlips = 512;
 // One wavefront per walker: n_wg entries of the table from wg_offset, each of
 // one walker of class cls; lat_bytes: spins of the class's largest lattice,
-// rounded up to 16.
+// rounded up to 16; l_min: side of its smallest.
 hipError_t launch_sweep_wave(const DevPtrs& P, int cls, int32_t wg_offset, int32_t n_wg,
-                             int32_t lat_bytes, int64_t flips, hipStream_t s);
+                             int32_t lat_bytes, int32_t l_min, int64_t flips, hipStream_t s);
+// LDS of such a workgroup, and whether it takes the form for small lattices
+// (Ising, 3 <= L <= 16: 64-bit masks per site).
+constexpr int kWaveSmallSites = 256;
+inline bool wave_small(int cls, int32_t lat_bytes, int32_t l_min) {
+  return cls == 0 && lat_bytes <= kWaveSmallSites && l_min >= 3;
+}
+inline int32_t wave_lds_bytes(int cls, int32_t lat_bytes, int32_t l_min) {
+  return (wave_small(cls, lat_bytes, l_min) ? 9 : 2) * lat_bytes;
+}
 // Every class in one launch (k_sweep_fused): n_wg entries of the table from
 // 0, class shapes sh[0..2], lds_bytes of the largest class.
 hipError_t launch_sweep_fused(const DevPtrs& P, const SweepShape sh[3], int32_t n_wg, int64_t flips,

@@ -26,18 +26,20 @@
 //     updated.
 // What bounds it: a lone wavefront issues one instruction every four cycles
 // and the attempts of one walker are a chain, so the time is the number of
-// instructions per attempt (40, of them 20 vector) and the waits between
-// dependent scalar and vector ones (295 cycles in all at Ising L = 32; the
+// instructions per attempt (35, of them 19 vector) and the waits between
+// dependent scalar and vector ones (285 cycles in all at Ising L = 32; the
 // chip is busy from 1024 walkers, one per SIMD).  Branches cost more than
 // what they skip: with early exits for rejected moves the attempt had 37
 // instructions, 7 branches and took 327 cycles.
 // Measured per attempt against one lane per walker in the default shape, on
-// 1024 walkers: Ising L = 32 135 against 453 ns, L = 64 122 against 591,
-// q = 10 Potts L = 20 173 against 554 (two-float 208 against 622).
+// 1024 walkers: Ising L = 32 122 against 453 ns, L = 64 110 against 591,
+// q = 10 Potts L = 20 168 against 554 (two-float 200 against 622).
 // The accepted sites are written back to the lattice (bytes in LDS) after
 // the 64.  The page of 64 bins moves when the walker comes near its edge:
 // stored and reloaded whole, a coalesced row segment each way.
 #include <math.h>
+
+#include <type_traits>
 
 #include "rewl_device.h"
 #include "rewl_internal.h"
@@ -59,6 +61,10 @@ __device__ __forceinline__ void wave_order() {
 __device__ __forceinline__ int lane_of(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
 __device__ __forceinline__ float lane_of(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ __forceinline__ uint64_t lane_of(uint64_t v, int lane) {
+  return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32 |
+         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
 }
 __device__ __forceinline__ double lane_of(double v, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
@@ -163,6 +169,7 @@ struct Pick {
     picked[site] = 0;
     return __ballot(others);
   }
+  __device__ __forceinline__ int step(int q, int bshift) const { return ar.step(q, bshift); }
   // attempt i was accepted: every lane's view follows
   __device__ __forceinline__ void follow(int i, int q) {
     ar.change(lane_of(site, i), lane_of(ar.proposed(), i), site, nr, nl, nd, nu, q);
@@ -178,6 +185,52 @@ struct Pick {
   }
 };
 
+// The same for small Ising lattices (3 <= L <= 16), where most accepted moves
+// touch another of the 64 attempts: a table of 64-bit lane masks per site
+// says which, and an accepted move updates the bin steps of the lanes in two
+// masks (7 vector instructions and no compare, against 20 for looking every
+// lane's five sites over).
+struct PickSmall {
+  int site, sgn, st;       // sgn: the site's spin, +1 or -1; st: bin step of its flip
+  uint64_t same, next_to;  // lanes that pick this site, or a neighbour of it
+  __device__ __forceinline__ uint64_t load(const uint8_t* lat, uint8_t* picked, uint4 r, bool live,
+                                           int side, int N, int) {
+    uint64_t* const masks = reinterpret_cast<uint64_t*>(picked);
+    site = (int)__umulhi(r.x, (uint32_t)N);
+    const int y = (int)__umulhi(r.x, (uint32_t)side);
+    const int x = site - __mul24(y, side);
+    const int nr = site + (x + 1 == side ? 1 - side : 1), nl = site + (x == 0 ? side - 1 : -1);
+    const int nd = site + (y + 1 == side ? side - N : side), nu = site + (y == 0 ? N - side : -side);
+    const uint64_t me = 1ull << threadIdx.x;
+    if (live) atomicOr(reinterpret_cast<unsigned long long*>(masks + site), (unsigned long long)me);
+    auto spin = [&](int s) { return (int)(int8_t)lat[s]; };
+    sgn = spin(site);
+    st = sgn * (spin(nr) + spin(nl) + spin(nd) + spin(nu)) / 2;  // agreeing neighbours - 2
+    wave_order();
+    same = masks[site];
+    next_to = masks[nr] | masks[nl] | masks[nd] | masks[nu];
+    wave_order();
+    masks[site] = 0;
+    return __ballot((next_to | (same & ~me)) != 0);
+  }
+  __device__ __forceinline__ int step(int, int) const { return st; }
+  // attempt i was accepted: with s the flipped spin's old value, the step
+  // (site's spin times neighbours' sum) / 2 falls by sgn s next to it and
+  // changes sign where it is the site
+  __device__ __forceinline__ void follow(int i, int) {
+    const int lane = threadIdx.x;
+    const int t = sgn * lane_of(sgn, i);
+    st -= (lane_of(next_to, i) >> lane) & 1 ? t : 0;
+    const bool s = (lane_of(same, i) >> lane) & 1;
+    st = s ? -st : st;
+    sgn = s ? -sgn : sgn;
+  }
+  __device__ __forceinline__ void settle(uint8_t* lat, uint64_t moved, uint64_t shared, int lane) const {
+    if ((moved >> lane) & 1) lat[site] = (uint8_t)(((shared >> lane) & 1) ? sgn : -sgn);
+    wave_order();
+  }
+};
+
 // ln g of one bin, the walker's running value, and the acceptance test in
 // both precisions.
 template <int PREC>
@@ -187,13 +240,18 @@ template <>
 struct LnG<kFP64> {
   double v;
   using Bound = double;
-  __device__ __forceinline__ void load(const DevPtrs& P, int64_t e) { v = P.lng[e]; }
+  __device__ __forceinline__ void load(const DevPtrs& P, int64_t e, bool in) { v = in ? P.lng[e] : INFINITY; }
   __device__ __forceinline__ void store(const DevPtrs& P, int64_t e) const { P.lng[e] = v; }
   __device__ __forceinline__ LnG at(int lane) const { return LnG{lane_of(v, lane)}; }
   __device__ __forceinline__ void put(bool here, const LnG& o) { v = here ? o.v : v; }
   __device__ __forceinline__ double minus(const LnG& o) const { return v - o.v; }
-  // frozen walkers add 0.0: ln g >= +0, so x + 0.0 is x bit for bit
-  __device__ __forceinline__ void add(double lnf, bool) { v = v + lnf; }
+  // this (or o) plus ln f; frozen walkers add 0.0: ln g >= +0, so x + 0.0 is
+  // x bit for bit
+  __device__ __forceinline__ void choose(bool other, const LnG& o, double lnf, bool) {
+    double a = o.v + lnf, b = v + lnf;
+    asm("" : "+v"(a), "+v"(b));  // keeps the compiler from choosing first
+    v = other ? a : b;
+  }
   // The uniform u = u53 2^-53 lies in [hi, hi + 1) 2^-32.  delta >= yes
   // makes u < exp(delta) certain, delta < no rules it out; both bounds keep a
   // distance of 2^-12 from ln(hi + 1) - 32 ln 2 and ln(hi) - 32 ln 2, against
@@ -216,9 +274,9 @@ template <>
 struct LnG<kFP32C> {
   float h, l;
   using Bound = float;
-  __device__ __forceinline__ void load(const DevPtrs& P, int64_t e) {
-    h = P.lhi[e];
-    l = P.llo[e];
+  __device__ __forceinline__ void load(const DevPtrs& P, int64_t e, bool in) {
+    h = in ? P.lhi[e] : INFINITY;
+    l = in ? P.llo[e] : 0.0f;
   }
   __device__ __forceinline__ void store(const DevPtrs& P, int64_t e) const {
     P.lhi[e] = h;
@@ -231,14 +289,15 @@ struct LnG<kFP32C> {
   }
   __device__ __forceinline__ float minus(const LnG& o) const { return (h - o.h) + (l - o.l); }
   // a two-float add of 0 could renormalise the pair: frozen walkers skip it
-  __device__ __forceinline__ void add(double lnf, bool frozen) {
+  __device__ __forceinline__ void choose(bool other, const LnG& o, double lnf, bool frozen) {
+    if (other) *this = o;
     if (!frozen) df_add1(h, l, (float)lnf, h, l);
   }
-  // the same for the 24-bit uniform u exactly; u = 0 accepts whatever delta
-  // is (both bounds -inf)
+  // the same for the 24-bit uniform u exactly; u = 0 (no = -inf) is left to
+  // the exact test, which knows the window
   static __device__ __forceinline__ void bounds(uint4 r, float& yes, float& no) {
     const float t = (__builtin_amdgcn_logf((float)(r.z >> 8)) - 24.0f) * 0x1.62e430p-1f;
-    yes = t + 0x1p-12f;
+    yes = r.z >> 8 ? t + 0x1p-12f : INFINITY;
     no = t - 0x1p-12f;
   }
   static __device__ __forceinline__ bool accept(uint32_t hi, uint32_t, float delta) {
@@ -387,12 +446,14 @@ hipError_t launch_init(const DevPtrs& P, int32_t lat_bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int MODEL, int PREC>
+template <int MODEL, int PREC, bool SMALL>
 __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offset, int32_t lat_bytes,
                                                       int64_t flips) {
   extern __shared__ __align__(16) uint8_t wlds[];
   uint8_t* const lat = wlds;               // [lat_bytes] spins
-  uint8_t* const picked = wlds + lat_bytes;  // [lat_bytes] attempts of the 64 that pick a site
+  // attempts of the 64 that pick a site: a count in a byte, or (SMALL) a
+  // 64-bit mask
+  uint8_t* const picked = wlds + lat_bytes;
   using L = LnG<PREC>;
   using Bound = typename L::Bound;
   const WgDesc wg = P.wg[wg_offset + (int)blockIdx.x];
@@ -406,7 +467,8 @@ __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offs
   const WinState WS = P.wst[I.win_base + w];
   const int nb = W.nb, side = I.L, N = I.N, q = I.q, bshift = I.binw_shift;
   const bool frozen = WS.frozen != 0;
-  const double lnf = frozen ? 0.0 : WS.lnf;
+  double lnf = frozen ? 0.0 : WS.lnf;
+  asm("" : "+v"(lnf));  // in vector registers: the other operand of the sums is scalar
   const uint32_t k0 = I.key0, k1 = I.key1;
   const uint32_t tagw = kTagMC | ((uint32_t)I.inst << 8);
   const int64_t row = W.lng_base + (int64_t)k * nb;  // of bin lo
@@ -424,33 +486,34 @@ __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offs
   uint32_t* const gsp = reinterpret_cast<uint32_t*>(P.spins + I.spin_base +
                                                     (int64_t)(P.cfg[g] - I.slot_base) * I.npad);
   const int words = I.npad >> 2;  // npad <= lat_bytes
-  for (int i = lane; i < words; i += kWave) {
-    reinterpret_cast<uint32_t*>(lat)[i] = gsp[i];
-    reinterpret_cast<uint32_t*>(picked)[i] = 0u;
-  }
+  for (int i = lane; i < words; i += kWave) reinterpret_cast<uint32_t*>(lat)[i] = gsp[i];
+  for (int i = lane; i < (SMALL ? 8 : 1) * words; i += kWave) reinterpret_cast<uint32_t*>(picked)[i] = 0u;
   wave_order();
 
-  // ---- the page: lane l holds bin pb + l (l <= top); c is the walker's bin
-  // in page coordinates.  Every U attempts the page is moved if the walker
-  // has come within U D bins of an end of it that is not the window's, so a
-  // proposed bin outside [0, top] is outside the window.
+  // ---- the page: lane l holds bin pb + l; c is the walker's bin in page
+  // coordinates.  Lanes outside the window (up to D of them beside it) hold
+  // +inf, so that a proposal out of the window is rejected by its delta of
+  // -inf.  Every U attempts the page is moved if the walker has come within U
+  // D bins of an end of it that is not the window's, so a proposed bin is
+  // always in the page.
   constexpr int U = MODEL == kPotts ? 2 : 4;
-  const int top = nb < kWave ? nb - 1 : kWave - 1;
   int pb, c, c_lo, c_span;
+  bool in;  // this lane's bin is in the window
   L ln;
   uint32_t hist;  // counts gathered in this lane's bin
   auto load_page = [&](int b) {
     pb = b - kWave / 2;
-    pb = pb > nb - kWave ? nb - kWave : pb;
-    pb = pb < 0 ? 0 : pb;
+    pb = pb > nb - kWave + D ? nb - kWave + D : pb;
+    pb = pb < -D ? -D : pb;
     c = b - pb;
-    c_lo = pb > 0 ? U * D : 0;
-    c_span = (pb + kWave < nb ? kWave - 1 - U * D : kWave - 1) - c_lo;
-    ln.load(P, row + pb + (lane <= top ? lane : top));
+    c_lo = pb > -D ? U * D : 0;
+    c_span = (pb + kWave < nb + D ? kWave - 1 - U * D : kWave - 1) - c_lo;
+    in = (uint32_t)(pb + lane) < (uint32_t)nb;
+    ln.load(P, row + pb + lane, in);
     hist = 0;
   };
   auto store_page = [&]() {
-    if (!frozen && lane <= top) {
+    if (!frozen && in) {
       ln.store(P, row + pb + lane);
       if (hist) atomicAdd(&P.H[row + pb + lane], hist);
     }
@@ -471,9 +534,9 @@ __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offs
     // ---- one attempt per lane
     const uint64_t a = att + (uint64_t)lane;
     const uint4 r = philox10(make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)loc, tagw), k0, k1);
-    Pick<MODEL> pick;
+    std::conditional_t<SMALL, PickSmall, Pick<MODEL>> pick;
     const uint64_t shared = pick.load(lat, picked, r, lane < n, side, N, q);
-    int step = pick.ar.step(q, bshift);
+    int step = pick.step(q, bshift);
     Bound yes, no;
     L::bounds(r, yes, no);
     uint64_t moved = 0;  // attempts whose move was accepted
@@ -483,25 +546,25 @@ __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offs
     // instructions it would skip
     auto attempt = [&](int i) {
       const int cn = c + lane_of(step, i);
-      const uint64_t bit = (uint32_t)cn <= (uint32_t)top ? 1ull << i : 0;  // 0: outside the window
-      const L next = ln.at(cn & (kWave - 1));
+      const L next = ln.at(cn);
       const auto delta = cur.minus(next);
-      const uint64_t sure = __ballot(delta >= yes) & bit;
-      const uint64_t open = __ballot(!(delta < no)) & bit;
-      uint64_t acc = sure;
-      if (__builtin_expect(((sure ^ open) | (sure & shared)) != 0, 0)) {
-        if (sure != open)
+      const uint64_t bit = 1ull << i;
+      const uint64_t sure = __ballot(delta >= yes);
+      const uint64_t open = __ballot(!(delta < no));
+      uint64_t acc = sure & bit;
+      if (__builtin_expect((((open & ~sure) | (sure & shared)) & bit) != 0, 0)) {
+        if (!acc && (uint32_t)(pb + cn) < (uint32_t)nb)
           acc = __ballot(L::accept((uint32_t)lane_of((int)r.z, i), (uint32_t)lane_of((int)r.w, i),
                                    delta)) & bit;  // the same in every lane
         if (acc & shared) {
           pick.follow(i, q);
-          step = pick.ar.step(q, bshift);
+          step = pick.step(q, bshift);
         }
       }
       moved |= acc;
       c = acc ? cn : c;
-      if (acc) cur = next;
-      cur.add(lnf, frozen);
+      // both outcomes with ln f added, off the chain of the decision
+      cur.choose(acc != 0, next, lnf, frozen);
       const bool here = lane == c;
       ln.put(here, cur);
       hist += here ? 1u : 0u;
@@ -527,17 +590,17 @@ __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offs
 }
 
 hipError_t launch_sweep_wave(const DevPtrs& P, int cls, int32_t wg_offset, int32_t n_wg,
-                             int32_t lat_bytes, int64_t flips, hipStream_t s) {
+                             int32_t lat_bytes, int32_t l_min, int64_t flips, hipStream_t s) {
   if (n_wg <= 0) return hipSuccess;
-  const dim3 grid(n_wg), blk(kWave);
-  const size_t lds = (size_t)2 * lat_bytes;  // at most 8 KiB
-  if (P.prec == kFP64) {
-    if (cls == 2) hipLaunchKernelGGL((k_sweep_wave<kPotts, kFP64>), grid, blk, lds, s, P, wg_offset, lat_bytes, flips);
-    else hipLaunchKernelGGL((k_sweep_wave<kIsing, kFP64>), grid, blk, lds, s, P, wg_offset, lat_bytes, flips);
-  } else {
-    if (cls == 2) hipLaunchKernelGGL((k_sweep_wave<kPotts, kFP32C>), grid, blk, lds, s, P, wg_offset, lat_bytes, flips);
-    else hipLaunchKernelGGL((k_sweep_wave<kIsing, kFP32C>), grid, blk, lds, s, P, wg_offset, lat_bytes, flips);
-  }
+  const bool small = wave_small(cls, lat_bytes, l_min);
+  using Fn = void (*)(DevPtrs, int32_t, int32_t, int64_t);
+  const Fn f = P.prec == kFP64
+                   ? (cls == 2 ? (Fn)k_sweep_wave<kPotts, kFP64, false>
+                               : small ? (Fn)k_sweep_wave<kIsing, kFP64, true> : (Fn)k_sweep_wave<kIsing, kFP64, false>)
+                   : (cls == 2 ? (Fn)k_sweep_wave<kPotts, kFP32C, false>
+                               : small ? (Fn)k_sweep_wave<kIsing, kFP32C, true> : (Fn)k_sweep_wave<kIsing, kFP32C, false>);
+  hipLaunchKernelGGL(f, dim3(n_wg), dim3(kWave), (size_t)wave_lds_bytes(cls, lat_bytes, l_min), s, P, wg_offset,
+                     lat_bytes, flips);
   return hipGetLastError();
 }
 
