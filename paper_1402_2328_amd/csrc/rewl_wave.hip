@@ -148,11 +148,8 @@ template <int MODEL>
 struct Pick {
   int site, nr, nl, nd, nu;
   Around<MODEL> ar;
-  // r: the attempt's random numbers; live: the lane makes an attempt;
-  // picked: a byte per site, zero before and after.  Returns the lanes whose
-  // five sites another lane picks one of.
-  __device__ __forceinline__ uint64_t load(const uint8_t* lat, uint8_t* picked, uint4 r, bool live,
-                                           int side, int N, int q) {
+  // r: the attempt's random numbers
+  __device__ __forceinline__ void look(const uint8_t* lat, uint4 r, int side, int N, int q) {
     site = (int)__umulhi(r.x, (uint32_t)N);
     // site = floor(r.x L^2 / 2^32), so its row is floor(r.x L / 2^32)
     const int y = (int)__umulhi(r.x, (uint32_t)side);
@@ -161,13 +158,22 @@ struct Pick {
     nl = site + (x == 0 ? side - 1 : -1);
     nd = site + (y + 1 == side ? side - N : side);
     nu = site + (y == 0 ? N - side : -side);
-    if (live) atomicAdd(reinterpret_cast<uint32_t*>(picked) + (site >> 2), 1u << ((site & 3) * 8));
     ar.load(lat, site, nr, nl, nd, nu, r.y, q);
+  }
+  // live: the lane makes an attempt; picked: a byte per site, zero before and
+  // after.  Returns the lanes whose five sites another lane picks one of.
+  __device__ __forceinline__ uint64_t compare(uint8_t* picked, bool live) const {
+    if (live) atomicAdd(reinterpret_cast<uint32_t*>(picked) + (site >> 2), 1u << ((site & 3) * 8));
     wave_order();
     const bool others = picked[site] > 1 || (picked[nr] | picked[nl] | picked[nd] | picked[nu]) != 0;
     wave_order();
     picked[site] = 0;
     return __ballot(others);
+  }
+  __device__ __forceinline__ uint64_t load(const uint8_t* lat, uint8_t* picked, uint4 r, bool live,
+                                           int side, int N, int q) {
+    look(lat, r, side, N, q);
+    return compare(picked, live);
   }
   __device__ __forceinline__ int step(int q, int bshift) const { return ar.step(q, bshift); }
   // attempt i was accepted: every lane's view follows
@@ -370,14 +376,15 @@ __device__ __forceinline__ void init_walker(const DevPtrs& P, const InstDesc& I,
       const int n = budget - it < kWave ? budget - it : kWave;
       const uint4 r = draw(I, wa + (uint64_t)lane, (uint32_t)loc, kTagWarm);
       Pick<MODEL> pick;
-      const uint64_t shared = pick.load(lat, picked, r, lane < n, side, N, q);
+      pick.look(lat, r, side, N, q);
       int dE = pick.ar.step(q, 0) * Around<MODEL>::kUnit;
-      uint64_t left = n < kWave ? (1ull << n) - 1 : ~0ull, moved = 0;
+      uint64_t left = n < kWave ? (1ull << n) - 1 : ~0ull, moved = 0, shared = 0;
       int made = n;
       while (left) {
         const int d = dist_to(E, elo, ehi);
         const uint64_t ok = __ballot(dist_to(E + dE, elo, ehi) <= d) & left;
         if (!ok) break;
+        if (!moved) shared = pick.compare(picked, lane < n);
         const int i = __builtin_ctzll(ok);
         moved |= 1ull << i;
         E += lane_of(dE, i);
