@@ -127,13 +127,14 @@ int rewl_run_sweeps(rewl_ctx* ctx, int64_t flips);
  * 0 = Ising L <= 32, 1 = Ising 32 < L <= 64, 2 = Potts.  A class is swept
  * with one lane per walker, in the shape below, or with one wavefront per
  * walker (walkers_per_group = 1; also the default, every argument left at
- * its default, of a batch of at most 8192 walkers): then the other
+ * its default, of a batch of up to 7168 walkers, for Potts 5632): then the other
  * arguments matter only to a fused launch (rewl_set_batching), which always
  * takes the lane form.  For class cls (-1:
  * all classes) keep page_bins ln g bins of each walker's window in LDS (the
  * rest stays in device memory; the page follows the walker) and put
  * walkers_per_group walkers in each workgroup; 0 picks the default (the
- * largest page that lets four workgroups share a compute unit).  page_bins
+ * largest page that lets as many workgroups share a compute unit as the batch
+ * needs to run at once, up to four).  page_bins
  * is rounded up to a power of two, at least 16 (32 for a class with q >= 3
  * Potts instances) and at most the power of two that holds the class's
  * largest window.  rng_producer: 1 gives each workgroup a second

@@ -226,7 +226,12 @@ int build_layout(const rewl_params* params, int32_t n, const int32_t* wlo, const
 // 12 * P bytes of LDS.  The page must hold bin +- 2D (D = 4 for q >= 3
 // Potts, else 2), so P >= 32 or 16, unless the largest window fits whole
 // (P = the power of two that holds it).  By default P is the largest page
-// that still lets T = 4 (else 3, 2, 1) full workgroups share a compute unit.
+// that still lets T full workgroups share a compute unit, T as many as the
+// batch needs to run at once, at most 4 (else 3, 2, 1): a larger page shifts
+// less often.  Per attempt with 16384 walkers (T = 1), page 128 against the 32
+// of T = 4: Ising L = 32 402 against 445 ns, L = 64 581 against 614, q = 10
+// Potts L = 20 378 against 561; with 24576 (T = 2), page 64 against 32: 447
+// against 466, 632 against 646, 540 against 586.
 struct ClassPlan {
   int32_t G = 0, P = 0, count = 0, offset = 0;
   int32_t prod = 0;  // RNG producer wavefront per workgroup
@@ -291,7 +296,7 @@ int plan_class(const Layout& Lo, int cls, int lds_budget, int page_req, int g_re
   cp = ClassPlan();
   if (Lo.walkers[cls] == 0) return REWL_OK;
   const bool any_shape = page_req == 0 && g_req == 0 && prod_req < 0 && nib_req < 0;
-  cp.wave = g_req == 1 || (any_shape && Lo.n_slots <= kWaveMaxWalkers);
+  cp.wave = g_req == 1 || (any_shape && Lo.n_slots <= (cls == 2 ? kWaveMaxPotts : kWaveMaxIsing));
   // Potts nibbles halve the lattice and so raise the workgroups per compute
   // unit, at a little extra latency per attempt: by default when the class
   // has more workgroups than the GPU has compute units
@@ -303,12 +308,21 @@ int plan_class(const Layout& Lo, int cls, int lds_budget, int page_req, int g_re
   int pmin, pmax;
   page_range(Lo, cls, pmin, pmax);
   int P = 0, G = kSweepWave;
+  // workgroups that have to share a compute unit for all of the batch to run
+  // at once
+  const int batch_wg = (Lo.n_slots + kSweepWave - 1) / kSweepWave;
+  const int share = std::min(4, std::max(1, (batch_wg + n_compute_units() - 1) / n_compute_units()));
+  if (g_req > 0) G = std::min(g_req, kSweepWave);
+  // producer by default when the class's workgroups do not outnumber the
+  // compute units (the walkers' chain, not issue, then bounds the sweep)
+  int prod = prod_req;
+  if (prod < 0) prod = (Lo.walkers[cls] + G - 1) / G <= n_compute_units() ? 1 : 0;
   if (page_req > 0) {
     P = std::min(std::max(pow2_ceil(page_req), pmin), pmax);
   } else {
-    for (int T = 4; T >= 1 && P == 0; --T) {
+    for (int T = share; T >= 1 && P == 0; --T) {
       for (int p = pmax; p >= pmin; p >>= 1) {
-        if ((size_t)T * lds_of(lat, kSweepWave, p, 0, tab) <= (size_t)lds_budget) {
+        if ((size_t)T * lds_of(lat, kSweepWave, p, share == 1 ? prod : 0, tab) <= (size_t)lds_budget) {
           P = p;
           break;
         }
@@ -316,11 +330,6 @@ int plan_class(const Layout& Lo, int cls, int lds_budget, int page_req, int g_re
     }
     if (P == 0) P = pmin;
   }
-  if (g_req > 0) G = std::min(g_req, kSweepWave);
-  // producer by default when the class's workgroups do not outnumber the
-  // compute units (the walkers' chain, not issue, then bounds the sweep)
-  int prod = prod_req;
-  if (prod < 0) prod = (Lo.walkers[cls] + G - 1) / G <= n_compute_units() ? 1 : 0;
   while (G > 1 && lds_of(lat, G, P, prod, tab) > (size_t)lds_budget) --G;
   if (lds_of(lat, G, P, prod, tab) > (size_t)lds_budget) return REWL_E_INVAL;
   cp.G = G;
@@ -881,7 +890,7 @@ int rewl_autotune(rewl_ctx* c, int64_t flips, int32_t repeats, int32_t* out) {
     pl.cls[cls].wave = 1;
     return true;
   };
-  const bool try_wave = L.n_slots <= 4 * kWaveMaxWalkers;
+  const bool try_wave = L.n_slots <= 4 * kWaveMaxIsing;
   if (try_wave && !rc) {
     LaunchPlan pl = c->plan;
     pl.fused = 0;

@@ -18,13 +18,15 @@ constexpr int kSweepWave = 64;    // walkers' wavefront of a sweep workgroup
 constexpr int kRngChunk = 16;     // attempts per hand-over of the RNG producer
 // Batches of at most this many walkers are swept with one wavefront per
 // walker by default, larger ones with one lane per walker.  A wavefront
-// makes an attempt in 130 to 210 ns while no SIMD holds two of them (1024
-// walkers) and the SIMDs fill up from there; a lane takes 440 to 620 ns in
-// its default shape however many there are.  At 8192 walkers, wavefronts
-// against lanes per attempt: Ising L = 32 397 against 442 ns, L = 64 455
-// against 606, q = 10 Potts L = 20 492 against 557 (two-float 546 against
-// 621); at 16384 723 against 445, 772 against 613, 861 against 560.
-constexpr int kWaveMaxWalkers = 8192;
+// makes an attempt in 110 to 200 ns while no SIMD holds two of them (1024
+// walkers), from there on the time grows with their number; a lane takes 340
+// to 510 ns in its default shape however many there are (up to 16384).  At
+// 6144 walkers, wavefronts against lanes: Ising L = 32 304 against 341 ns,
+// L = 64 360 against 502, q = 10 Potts L = 20 418 against 386 (two-float 452
+// against 390), q = 8 Potts L = 32 343 against 475; at 8192 386 against 343,
+// 437 against 503, 490 against 389, 550 against 391, 441 against 477.
+constexpr int kWaveMaxIsing = 7168;
+constexpr int kWaveMaxPotts = 5632;
 constexpr int kMaxTemps = 16384;  // rewl_thermo temperatures per call
 // Allocation-free jackknife: doubles of the per-GPU device array that holds
 // one instance's window representatives and (m + 2) x nbins leave-one-out
