@@ -730,7 +730,7 @@ void plan_out(const Layout& Lo, const LaunchPlan& pl, int32_t* out) {
     const bool wave = pl.cls[cls].wave && !pl.fused;
     out[6 * cls + 0] = pl.cls[cls].P;
     out[6 * cls + 1] = wave ? 1 : pl.cls[cls].G;
-    out[6 * cls + 2] = wave ? wave_lds_bytes(cls, wave_lat_bytes(Lo, cls), Lo.l_min[cls]) : (int32_t)pl.cls[cls].lds_bytes;
+    out[6 * cls + 2] = wave ? wave_lds_bytes(cls, wave_lat_bytes(Lo, cls), Lo.l_min[cls], pl.cls[cls].count) : (int32_t)pl.cls[cls].lds_bytes;
     out[6 * cls + 3] = pl.cls[cls].count;
     out[6 * cls + 4] = pl.cls[cls].prod;
     out[6 * cls + 5] = pl.cls[cls].nib;

@@ -138,14 +138,17 @@ constexpr int64_t kEvenOutFlips = 512;
 // rounded up to 16; l_min: side of its smallest.
 hipError_t launch_sweep_wave(const DevPtrs& P, int cls, int32_t wg_offset, int32_t n_wg,
                              int32_t lat_bytes, int32_t l_min, int64_t flips, hipStream_t s);
-// LDS of such a workgroup, and whether it takes the form for small lattices
-// (Ising, 3 <= L <= 16: 64-bit masks per site).
-constexpr int kWaveSmallSites = 256;
-inline bool wave_small(int cls, int32_t lat_bytes, int32_t l_min) {
-  return cls == 0 && lat_bytes <= kWaveSmallSites && l_min >= 3;
+// Whether such a workgroup keeps a 64-bit lane mask per site (else a count in a
+// byte), and its LDS.  The masks say which accepted moves concern a later
+// attempt, the counts only which concern another; they are taken while all
+// n_wg workgroups stay resident with them (17 per compute unit at 1024
+// sites).  At L = 2 right and left neighbour are one site, which a mask
+// cannot say for Ising.
+inline bool wave_masks(int cls, int32_t lat_bytes, int32_t l_min, int32_t n_wg) {
+  return (cls == 2 || l_min >= 3) && (lat_bytes <= 256 || (lat_bytes <= 1024 && n_wg <= 4096));
 }
-inline int32_t wave_lds_bytes(int cls, int32_t lat_bytes, int32_t l_min) {
-  return (wave_small(cls, lat_bytes, l_min) ? 9 : 2) * lat_bytes;
+inline int32_t wave_lds_bytes(int cls, int32_t lat_bytes, int32_t l_min, int32_t n_wg) {
+  return (wave_masks(cls, lat_bytes, l_min, n_wg) ? 9 : 2) * lat_bytes;
 }
 // Every class in one launch (k_sweep_fused): n_wg entries of the table from
 // 0, class shapes sh[0..2], lds_bytes of the largest class.

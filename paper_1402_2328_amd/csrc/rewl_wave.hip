@@ -19,21 +19,23 @@
 //     v_readlane, so no memory is touched and an attempt costs one
 //     subtraction, two compares and some twenty cheap instructions.
 //   * An accepted move changes the lattice under the attempts still to be
-//     made.  A byte per site counts how many of the 64 attempts pick it, so a
-//     lane knows beforehand whether its site or a neighbour of it is picked
-//     by another attempt; only then (a third of the accepted moves at
-//     L = 32 and less) are the other lanes' neighbours and energy changes
-//     updated.
+//     made.  A mask per site of the lanes that pick it (or, where the masks
+//     would not fit in LDS, a count) tells a lane beforehand whether its move
+//     concerns a later attempt, or any other on the same site; only then (one
+//     accepted move in seven at L = 32) are the other lanes' neighbours and
+//     energy changes updated.  Against counts alone the masks took 8 Ising L =
+//     32 instances from 122 to 115 ns per attempt, q = 10 Potts L = 20 from
+//     168 to 149.
 // What bounds it: a lone wavefront issues one instruction every four cycles
 // and the attempts of one walker are a chain, so the time is the number of
-// instructions per attempt (35, of them 19 vector) and the waits between
-// dependent scalar and vector ones (285 cycles in all at Ising L = 32; the
-// chip is busy from 1024 walkers, one per SIMD).  Branches cost more than
-// what they skip: with early exits for rejected moves the attempt had 37
-// instructions, 7 branches and took 327 cycles.
+// instructions per attempt (37 at Ising L = 32, of them 18 vector: 160 of 256
+// cycles) and the waits between dependent scalar and vector ones; the chip
+// is busy from 1024 walkers, one per SIMD.  Branches cost more than what they
+// skip: with early exits for rejected moves the attempt had 37 instructions,
+// 7 branches and took 327 cycles, without them and 40 instructions 295.
 // Measured per attempt against one lane per walker in the default shape, on
-// 1024 walkers: Ising L = 32 122 against 453 ns, L = 64 110 against 591,
-// q = 10 Potts L = 20 168 against 554 (two-float 200 against 622).
+// 1024 walkers: Ising L = 32 115 against 453 ns, L = 64 110 against 591,
+// q = 10 Potts L = 20 152 against 554.
 // The accepted sites are written back to the lattice (bytes in LDS) after
 // the 64.  The page of 64 bins moves when the walker comes near its edge:
 // stored and reloaded whole, a coalesced row segment each way.
@@ -144,7 +146,7 @@ struct Around<kPotts> {
 // The site that one attempt picks, its neighbours and the lattice around
 // them, per lane; and whether another of the wavefront's attempts picks one
 // of the five.
-template <int MODEL>
+template <int MODEL, bool MASKS>
 struct Pick {
   int site, nr, nl, nd, nu;
   Around<MODEL> ar;
@@ -160,9 +162,21 @@ struct Pick {
     nu = site + (y == 0 ? N - side : -side);
     ar.load(lat, site, nr, nl, nd, nu, r.y, q);
   }
-  // live: the lane makes an attempt; picked: a byte per site, zero before and
-  // after.  Returns the lanes whose five sites another lane picks one of.
+  // live: the lane makes an attempt; picked: zero before and after, a byte
+  // per site that counts the lanes that pick it, or (MASKS) their mask.
+  // Returns the lanes whose five sites another lane picks one of; with masks
+  // only those that a later lane picks next to, or any other the same.
   __device__ __forceinline__ uint64_t compare(uint8_t* picked, bool live) const {
+    if constexpr (MASKS) {
+      uint64_t* const masks = reinterpret_cast<uint64_t*>(picked);
+      const uint64_t me = 1ull << threadIdx.x;
+      if (live) atomicOr(reinterpret_cast<unsigned long long*>(masks + site), (unsigned long long)me);
+      wave_order();
+      const uint64_t same = masks[site], next_to = masks[nr] | masks[nl] | masks[nd] | masks[nu];
+      wave_order();
+      masks[site] = 0;
+      return __ballot(((next_to & ~(me | (me - 1))) | (same & ~me)) != 0);
+    }
     if (live) atomicAdd(reinterpret_cast<uint32_t*>(picked) + (site >> 2), 1u << ((site & 3) * 8));
     wave_order();
     const bool others = picked[site] > 1 || (picked[nr] | picked[nl] | picked[nd] | picked[nu]) != 0;
@@ -191,12 +205,11 @@ struct Pick {
   }
 };
 
-// The same for small Ising lattices (3 <= L <= 16), where most accepted moves
-// touch another of the 64 attempts: a table of 64-bit lane masks per site
-// says which, and an accepted move updates the bin steps of the lanes in two
-// masks (7 vector instructions and no compare, against 20 for looking every
-// lane's five sites over).
-struct PickSmall {
+// The same for Ising lattices (L >= 3) with the masks kept in registers: an
+// accepted move updates the bin steps of the lanes in two masks (7 vector
+// instructions and no compare, against 20 for looking every lane's five sites
+// over).
+struct PickIsing {
   int site, sgn, st;       // sgn: the site's spin, +1 or -1; st: bin step of its flip
   uint64_t same, next_to;  // lanes that pick this site, or a neighbour of it
   __device__ __forceinline__ uint64_t load(const uint8_t* lat, uint8_t* picked, uint4 r, bool live,
@@ -217,7 +230,7 @@ struct PickSmall {
     next_to = masks[nr] | masks[nl] | masks[nd] | masks[nu];
     wave_order();
     masks[site] = 0;
-    return __ballot((next_to | (same & ~me)) != 0);
+    return __ballot(((next_to & ~(me | (me - 1))) | (same & ~me)) != 0);
   }
   __device__ __forceinline__ int step(int, int) const { return st; }
   // attempt i was accepted: with s the flipped spin's old value, the step
@@ -378,7 +391,7 @@ __device__ __forceinline__ void init_walker(const DevPtrs& P, const InstDesc& I,
       const int n = budget - it < kWave ? budget - it : kWave;
       const uint64_t a = wa + (uint64_t)lane;
       const uint4 r = philox10(make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)loc, tag), k0, k1);
-      Pick<MODEL> pick;
+      Pick<MODEL, false> pick;
       pick.look(lat, r, side, N, q);
       int dE = pick.ar.step(q, 0) * Around<MODEL>::kUnit;
       uint64_t left = n < kWave ? (1ull << n) - 1 : ~0ull, moved = 0, shared = 0;
@@ -462,13 +475,12 @@ hipError_t launch_init(const DevPtrs& P, int32_t lat_bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int MODEL, int PREC, bool SMALL>
+template <int MODEL, int PREC, bool MASKS>
 __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offset, int32_t lat_bytes,
                                                       int64_t flips) {
   extern __shared__ __align__(16) uint8_t wlds[];
   uint8_t* const lat = wlds;               // [lat_bytes] spins
-  // attempts of the 64 that pick a site: a count in a byte, or (SMALL) a
-  // 64-bit mask
+  // attempts of the 64 that pick a site: a count in a byte, or a 64-bit mask
   uint8_t* const picked = wlds + lat_bytes;
   using L = LnG<PREC>;
   using Bound = typename L::Bound;
@@ -503,7 +515,7 @@ __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offs
                                                     (int64_t)(P.cfg[g] - I.slot_base) * I.npad);
   const int words = I.npad >> 2;  // npad <= lat_bytes
   for (int i = lane; i < words; i += kWave) reinterpret_cast<uint32_t*>(lat)[i] = gsp[i];
-  for (int i = lane; i < (SMALL ? 8 : 1) * words; i += kWave) reinterpret_cast<uint32_t*>(picked)[i] = 0u;
+  for (int i = lane; i < (MASKS ? 8 : 1) * words; i += kWave) reinterpret_cast<uint32_t*>(picked)[i] = 0u;
   wave_order();
 
   // ---- the page: lane l holds bin pb + l; c is the walker's bin in page
@@ -550,7 +562,7 @@ __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offs
     // ---- one attempt per lane
     const uint64_t a = att + (uint64_t)lane;
     const uint4 r = philox10(make_uint4((uint32_t)a, (uint32_t)(a >> 32), (uint32_t)loc, tagw), k0, k1);
-    std::conditional_t<SMALL, PickSmall, Pick<MODEL>> pick;
+    std::conditional_t<MASKS && MODEL == kIsing, PickIsing, Pick<MODEL, MASKS>> pick;
     const uint64_t shared = pick.load(lat, picked, r, lane < n, side, N, q);
     int step = pick.step(q, bshift);
     Bound yes, no;
@@ -608,14 +620,14 @@ __global__ __launch_bounds__(kWave) void k_sweep_wave(DevPtrs P, int32_t wg_offs
 hipError_t launch_sweep_wave(const DevPtrs& P, int cls, int32_t wg_offset, int32_t n_wg,
                              int32_t lat_bytes, int32_t l_min, int64_t flips, hipStream_t s) {
   if (n_wg <= 0) return hipSuccess;
-  const bool small = wave_small(cls, lat_bytes, l_min);
+  const bool masks = wave_masks(cls, lat_bytes, l_min, n_wg);
   using Fn = void (*)(DevPtrs, int32_t, int32_t, int64_t);
-  const Fn f = P.prec == kFP64
-                   ? (cls == 2 ? (Fn)k_sweep_wave<kPotts, kFP64, false>
-                               : small ? (Fn)k_sweep_wave<kIsing, kFP64, true> : (Fn)k_sweep_wave<kIsing, kFP64, false>)
-                   : (cls == 2 ? (Fn)k_sweep_wave<kPotts, kFP32C, false>
-                               : small ? (Fn)k_sweep_wave<kIsing, kFP32C, true> : (Fn)k_sweep_wave<kIsing, kFP32C, false>);
-  hipLaunchKernelGGL(f, dim3(n_wg), dim3(kWave), (size_t)wave_lds_bytes(cls, lat_bytes, l_min), s, P, wg_offset,
+  const Fn potts = P.prec == kFP64 ? (masks ? (Fn)k_sweep_wave<kPotts, kFP64, true> : (Fn)k_sweep_wave<kPotts, kFP64, false>)
+                                   : (masks ? (Fn)k_sweep_wave<kPotts, kFP32C, true> : (Fn)k_sweep_wave<kPotts, kFP32C, false>);
+  const Fn ising = P.prec == kFP64 ? (masks ? (Fn)k_sweep_wave<kIsing, kFP64, true> : (Fn)k_sweep_wave<kIsing, kFP64, false>)
+                                   : (masks ? (Fn)k_sweep_wave<kIsing, kFP32C, true> : (Fn)k_sweep_wave<kIsing, kFP32C, false>);
+  const Fn f = cls == 2 ? potts : ising;
+  hipLaunchKernelGGL(f, dim3(n_wg), dim3(kWave), (size_t)wave_lds_bytes(cls, lat_bytes, l_min, n_wg), s, P, wg_offset,
                      lat_bytes, flips);
   return hipGetLastError();
 }

@@ -29,6 +29,7 @@ CASES = {
     "ising_L8_fp32c": (_c(WL.ISING, 8, n_windows=3, precision=WL.FP32C), None),
     "ising_L16_257_bins": (_c(WL.ISING, 16), None),
     "ising_L16_257_bins_fp32c_1t": (_c(WL.ISING, 16, precision=WL.FP32C, schedule=WL.ONE_OVER_T), None),
+    "ising_L17_290_bins": (_c(WL.ISING, 17, n_windows=1), None),
     "ising_L32_h2": (_c(WL.ISING, 32, n_windows=2), None),
     "ising_L64_h3": (_c(WL.ISING, 64, n_windows=3), None),
     "potts_q2_L9": (_c(WL.POTTS, 9, q=2), None),
@@ -86,3 +87,18 @@ def test_a_fused_batch_of_a_default_plan_takes_the_lane_form():
             oracle_cycle(sim, 777)
             oracle_cycle(sim, 777)
             compare_state(ctx, i, sim)
+
+
+@pytest.mark.parametrize("model,L,q", [(WL.ISING, 18, 2), (WL.POTTS, 18, 5)])
+def test_many_walkers_on_lattices_of_more_than_256_sites(model, L, q):
+    """Above 4096 walkers such lattices are swept with counts in place of lane
+    masks: 65 instances of 64 walkers, the last compared in full."""
+    cfg = _c(model, L, q=q, walkers_per_window=64)
+    ctx = gpu_context([cfg] * 65)
+    (plan,) = ctx.set_launch(walkers_per_group=1).values()
+    assert plan["workgroups"] == 65 * 64
+    ctx.run_cycles(2, 1500)
+    sim = oracle_sim(cfg, instance=64)
+    for _ in range(2):
+        oracle_cycle(sim, 1500)
+    compare_state(ctx, 64, sim)
