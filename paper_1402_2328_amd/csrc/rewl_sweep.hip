@@ -6,12 +6,13 @@
 //     L <= 32, two for L <= 64), Potts spins as 4-bit nibbles (q <= 16) or
 //     bytes;
 //   * a page of PG = 2^k bins of its ln g window, direct-mapped (bin b lives
-//     in slot b mod PG), with the histogram increments H gathered since the
-//     launch began.  Walkers move at most D bins per attempt (D = 2 for
-//     Ising and q = 2 Potts, 4 for q >= 3 Potts); the page always covers
-//     [bin - 2D, bin + 2D] inside the window and follows the walker by at
+//     in slot b mod PG), with the histogram H (Ising L = 32: the counts; else
+//     the increments gathered since the bin entered).  Walkers move at most
+//     D bins per attempt (D = 2 for Ising and q = 2 Potts, 4 for q >= 3
+//     Potts); the page always covers [bin - 2D, bin + 2D] inside the window
+//     and follows the walker by at
 //     most D bins per move: the bin that leaves is written back (ln g
-//     stored, its H increments added to the histogram in device memory) and
+//     stored, its H count stored or its increments added to device memory) and
 //     the bin that enters shares its slot; the entering ln g is loaded into
 //     registers and committed one attempt later, since it cannot be reached
 //     before then, so the load has a whole attempt to arrive (the leaving
@@ -29,12 +30,12 @@
 // three rows next to each other (both words of ln g, then H), so one address
 // serves all three.
 // What bounds it on a full chip is instruction issue, and the clock that the
-// power of the wide multiplies and LDS accesses leaves: 111 vector
+// power of the wide multiplies and LDS accesses leaves: 107 vector
 // instructions per wave-attempt on 1024 Ising L = 32 instances (122 with ln
 // g and H as arrays of their own, bins counted from the range's lowest and
-// every Philox round in full), 6.22 against 6.9 ms per sweep of 10^4 attempts
-// with the wavefronts placed alike; 145 against 167 on q = 10 Potts L = 20 in
-// two-float FP32, 4.85 against 6.3 ms.  Random numbers come
+// every Philox round in full), 6.2 against 6.9 ms per sweep of 10^4 attempts
+// with the wavefronts placed alike (5.75 with H as counts); 136 against 167 on
+// q = 10 Potts L = 20 in two-float FP32, 4.85 against 6.3 ms.  Random numbers come
 // from Philox4x32-10 keyed by (walker slot, attempt), so results do not
 // depend on the walker-to-lane mapping, page size or launch shape.
 #include <math.h>
@@ -110,7 +111,8 @@ __device__ __forceinline__ int potts_de(int a, int b, int c, int d, int s0, int 
 // rows next to each other are reached by offsets in the instruction (one
 // ds_read2st64_b32 for both words of an FP64 ln g).
 // The sweep of workgroup-table entry wgi, with the launch's dynamic LDS.
-template <int MODEL, int PREC, int ROWW, bool PROD, bool S64>
+// COUNTS: the L = 32 loop keeps whole counts of H in the page (below).
+template <int MODEL, int PREC, int ROWW, bool PROD, bool S64, bool COUNTS>
 __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& sh, int64_t flips, int wgi,
                                            unsigned char* lds) {
   const WgDesc wg = P.wg[wgi];
@@ -255,7 +257,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
 
   // ---- page: bins [base, base + cnt) of the window, slot of bin b = b & PM.
   // A slot is three rows of 32-bit words: ln g (FP64 low and high half, or
-  // FP32C high and low part) and the H increments.
+  // FP32C high and low part) and H (counts or increments).
   const int lane4 = lane * 4;
   const int S4 = S * 4;
   // byte offset of this lane's word in a row; addresses stay below 2^24, so
@@ -273,6 +275,17 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   };
   auto getf = [&](int off, int row) { return __uint_as_float(word(off, row)); };
   auto putf = [&](int off, int row, float v) { word(off, row) = __float_as_uint(v); };
+  // H in the page: in the L = 32 Ising loop a bin's whole count, loaded with
+  // its ln g and stored back; in the others the increments since it entered,
+  // added to device memory by an atomic when it leaves.  The atomics fetch
+  // the same lines and are the slower way out where device memory is busy,
+  // the load is one more per entering bin.  Counts against increments: 5.80
+  // against 6.23 ms per sweep on 1024 instances (131072 walkers) of Ising
+  // L = 32 with 16 windows, 777 against 897 ns per attempt with 8, 1 to 2 %
+  // fewer on 49152 walkers; but 1 to 2 % more on L = 8 to 28, 2 % more on Potts
+  // with one wavefront per SIMD, and 0.5 % more in the fused launch of the
+  // 64-instance mix.
+  const bool h_load = COUNTS && L == 32;
   const int cnt = nb < PG ? nb : PG;
   const int hi_pm = nb - cnt;  // highest page start; 0: the window is in LDS entirely
   int m_pm = __builtin_amdgcn_readfirstlane(M - PM);
@@ -290,31 +303,31 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       putf(j, 0, *at_off(lhw, e << 2));
       putf(j, 1, *at_off(llw, e << 2));
     }
-    word(j, 2) = 0;
+    word(j, 2) = h_load ? *at_off(Hw, e << 2) : 0u;
   }
   constexpr int DMAX = (MODEL == kPotts) ? 4 : 2;
   // Bins in flight after a page shift of pend_n bins: slot pend_row[i] holds
-  // the leaving bin of element pend_e + i with its ln g and H increments
+  // the leaving bin of element pend_e + i with its ln g and H
   // (read from LDS) and gets the entering bin's ln g (loaded from device
   // memory); both are settled one attempt later, which keeps the LDS read's
   // latency out of the shift.
   int pend_n = 0;
   uint32_t pend_e = 0u;
   int pend_row[DMAX];
-  uint32_t ev_h[DMAX];
+  uint32_t pend_h[DMAX], ev_h[DMAX];
   double pend_l[DMAX], ev_l[DMAX];
   float pend_hi[DMAX], pend_lo[DMAX], ev_hi[DMAX], ev_lo[DMAX];
 #pragma unroll
   for (int i = 0; i < DMAX; ++i) {
     pend_row[i] = 0;
-    ev_h[i] = 0u;
+    pend_h[i] = ev_h[i] = 0u;
     pend_l[i] = ev_l[i] = 0.0;
     pend_hi[i] = pend_lo[i] = ev_hi[i] = ev_lo[i] = 0.0f;
   }
   // Settles the bins in flight: the leaving bins are written back (ln g
-  // stored, H increments added to the histogram in device memory) and the
+  // stored, H counts stored or increments added in device memory) and the
   // entering bins take their slots.
-  auto settle = [&]() {
+  auto settle = [&](auto counts) {
     // All lanes' loads have arrived here (vmcnt 0).  Waited for inside the
     // branch only, the compiler has to take them as pending after it, and
     // may wait again, then for the stores below as well, where the next
@@ -330,14 +343,15 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
           putf(j, 0, pend_hi[i]);
           putf(j, 1, pend_lo[i]);
         }
-        word(j, 2) = 0;
+        word(j, 2) = counts ? pend_h[i] : 0u;
         if (PREC == kFP64) {
           *at_off(lngw, (pend_e << 3) + 8u * i) = ev_l[i];
         } else {
           *at_off(lhw, (pend_e << 2) + 4u * i) = ev_hi[i];
           *at_off(llw, (pend_e << 2) + 4u * i) = ev_lo[i];
         }
-        atomicAdd(at_off(Hw, (pend_e << 2) + 4u * i), ev_h[i]);
+        if (counts) *at_off(Hw, (pend_e << 2) + 4u * i) = ev_h[i];
+        else atomicAdd(at_off(Hw, (pend_e << 2) + 4u * i), ev_h[i]);
       }
     }
     pend_n = 0;
@@ -367,6 +381,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
                       uint32_t fm, int site, auto lkt, auto nbt) -> bool {
     constexpr bool NB = decltype(nbt)::value;
     constexpr bool TAB = decltype(lkt)::value == 3;
+    constexpr bool H_LOAD = COUNTS && decltype(lkt)::value == 2;
     const bool inwin = (uint32_t)bn < (uint32_t)nb;
     const int jn = pslot(bn);
     bool acc;
@@ -437,7 +452,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       lds_add(jcur + (S64 ? 512 : 2 * S4), 1u);
     }
     // settle the bins of the last shift, then follow the walker
-    settle();
+    settle(std::bool_constant<H_LOAD>{});
     // bin + M - PM is the lowest page start that still covers bin + M,
     // bin - M the highest that covers bin - M (PM >= 2M); the start then
     // stays inside [0, hi_pm] (0 for a window that is in LDS entirely, which
@@ -449,7 +464,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       // above them enter; down: the bins from the new start to the old one
       // enter and those PG above them leave.  Either way they are counted
       // from the lower start, and each pair shares a slot.  A frozen walker
-      // writes back its unchanged ln g and no H increments.
+      // writes back its unchanged ln g and H.
       const bool up = nbase > base;
       const int bot = up ? base : nbase;
       pend_n = (up ? nbase : base) - bot;  // 1..D
@@ -470,6 +485,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
             ev_hi[i] = getf(j, 0);
             ev_lo[i] = getf(j, 1);
           }
+          if (H_LOAD) pend_h[i] = *at_off(Hw, (en << 2) + 4u * i);
           ev_h[i] = word(j, 2);
           pend_row[i] = j;
         }
@@ -727,7 +743,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   }
 
   // ---- stage out ----
-  settle();
+  settle(h_load);
   if (!frozen) {
     for (int i = 0; i < cnt; ++i) {
       const int b = base + i;
@@ -740,7 +756,8 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
         *at_off(llw, e << 2) = getf(j, 1);
       }
       const uint32_t h = word(j, 2);
-      if (h) atomicAdd(at_off(Hw, e << 2), h);
+      if (h_load) *at_off(Hw, e << 2) = h;
+      else if (h) atomicAdd(at_off(Hw, e << 2), h);
     }
   }
   if (MODEL == kIsing) {
@@ -772,7 +789,7 @@ template <int MODEL, int PREC, int ROWW, bool PROD, bool S64>
 __global__ __launch_bounds__(PROD ? 2 * kSweepWave : kSweepWave) void k_sweep(DevPtrs P, SweepShape sh,
                                                                                 int64_t flips) {
   extern __shared__ __align__(16) unsigned char lds[];
-  sweep_body<MODEL, PREC, ROWW, PROD, S64>(P, sh, flips, sh.wg_offset + (int)blockIdx.x, lds);
+  sweep_body<MODEL, PREC, ROWW, PROD, S64, MODEL == kIsing && ROWW == 1>(P, sh, flips, sh.wg_offset + (int)blockIdx.x, lds);
 }
 
 // Every kernel class of a batch in one launch: workgroup b runs table entry
@@ -787,9 +804,9 @@ __global__ __launch_bounds__(PROD ? 2 * kSweepWave : kSweepWave) void k_sweep_fu
   extern __shared__ __align__(16) unsigned char lds[];
   const int wgi = (int)blockIdx.x;
   const int cls = P.wg[wgi].cls;
-  if (cls == 0) sweep_body<kIsing, PREC, 1, PROD, S64>(P, s0, flips, wgi, lds);
-  else if (cls == 1) sweep_body<kIsing, PREC, 2, PROD, S64>(P, s1, flips, wgi, lds);
-  else sweep_body<kPotts, PREC, 0, PROD, S64>(P, s2, flips, wgi, lds);
+  if (cls == 0) sweep_body<kIsing, PREC, 1, PROD, S64, false>(P, s0, flips, wgi, lds);
+  else if (cls == 1) sweep_body<kIsing, PREC, 2, PROD, S64, false>(P, s1, flips, wgi, lds);
+  else sweep_body<kPotts, PREC, 0, PROD, S64, false>(P, s2, flips, wgi, lds);
 }
 
 namespace {
