@@ -133,8 +133,8 @@ int rewl_run_sweeps(rewl_ctx* ctx, int64_t flips);
  * all classes) keep page_bins ln g bins of each walker's window in LDS (the
  * rest stays in device memory; the page follows the walker) and put
  * walkers_per_group walkers in each workgroup; 0 picks the default (the
- * largest page that lets as many workgroups share a compute unit as the batch
- * needs to run at once, up to four).  page_bins
+ * largest page that lets the batch's workgroups run in as few turns per
+ * compute unit as the smallest page would, up to eight at a time).  page_bins
  * is rounded up to a power of two, at least 16 (32 for a class with q >= 3
  * Potts instances) and at most the power of two that holds the class's
  * largest window.  rng_producer: 1 gives each workgroup a second

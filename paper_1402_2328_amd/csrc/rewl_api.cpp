@@ -225,13 +225,26 @@ int build_layout(const rewl_params* params, int32_t n, const int32_t* wlo, const
 // slice of the workgroup table.  Per lane a class needs 4 * lat_words +
 // 12 * P bytes of LDS.  The page must hold bin +- 2D (D = 4 for q >= 3
 // Potts, else 2), so P >= 32 or 16, unless the largest window fits whole
-// (P = the power of two that holds it).  By default P is the largest page
-// that still lets T full workgroups share a compute unit, T as many as the
-// batch needs to run at once, at most 4 (else 3, 2, 1): a larger page shifts
-// less often.  Per attempt with 16384 walkers (T = 1), page 128 against the 32
-// of T = 4: Ising L = 32 402 against 445 ns, L = 64 581 against 614, q = 10
-// Potts L = 20 378 against 561; with 24576 (T = 2), page 64 against 32: 447
-// against 466, 632 against 646, 540 against 586.
+// (P = the power of two that holds it).  By default the batch's workgroups
+// take turns on a compute unit, as few turns as the smallest page allows with
+// at most kMaxShare of them at a time, and P is the largest page that still
+// lets as many share it as these turns need: a larger page shifts less often,
+// a turn more costs far more than that.  Per attempt with 16384 walkers (one
+// workgroup per compute unit), page 128 against 32: Ising L = 32 402 against
+// 445 ns, L = 64 581 against 614, q = 10 Potts L = 20 378 against 561; with
+// 24576 (two), page 64 against 32: 447 against 466, 632 against 646, 540
+// against 586.  Ising L = 32 with 98304 (six), page 16 in one turn against 32
+// in two: 627 against 945 ns; with 131072 (eight) 691 against 962; L = 64 with
+// 65536 (four), two turns of two with page 64 against three and one with 16:
+// 1136 against 1235.  Workgroups are counted as they are made, of one
+// instance each: 4096 instances of 4 walkers (L = 8, sixteen per compute
+// unit) 1211 ns against 5334 when taken for one full workgroup.
+// LDS is given out in pieces of this size (gfx950).  Ising L = 20 with 49152
+// walkers, three workgroups per compute unit: page 64, 54272 bytes each, of
+// which three would fit without it, 812 ns per attempt against 431.
+constexpr int kLdsGrain = 1280;
+// Two wavefronts per SIMD: they fill 89 % of its issue cycles.
+constexpr int kMaxShare = 8;
 struct ClassPlan {
   int32_t G = 0, P = 0, count = 0, offset = 0;
   int32_t prod = 0;  // RNG producer wavefront per workgroup
@@ -288,6 +301,15 @@ int n_compute_units() {
   return 256;  // MI355X
 }
 
+// Workgroups of a class (-1: of the batch) with up to G walkers each, all of
+// one instance.
+int wg_count(const Layout& Lo, int cls, int G) {
+  int n = 0;
+  for (const InstDesc& I : Lo.inst)
+    if (cls < 0 || class_of(I) == cls) n += (I.W + G - 1) / G;
+  return n;
+}
+
 // Spin bytes of a class's largest lattice in the wavefront-per-walker form.
 int wave_lat_bytes(const Layout& Lo, int cls) { return (int)align_up((size_t)Lo.n_max[cls], 16); }
 
@@ -300,7 +322,7 @@ int plan_class(const Layout& Lo, int cls, int lds_budget, int page_req, int g_re
   // Potts nibbles halve the lattice and so raise the workgroups per compute
   // unit, at a little extra latency per attempt: by default when the class
   // has more workgroups than the GPU has compute units
-  const bool many = (Lo.walkers[cls] + kSweepWave - 1) / kSweepWave > n_compute_units();
+  const bool many = wg_count(Lo, cls, kSweepWave) > n_compute_units();
   int nib = cls == 2 && Lo.nib_ok[cls] ? (nib_req < 0 ? (many ? 1 : 0) : nib_req) : 0;
   if (nib_req >= 1 && !(cls == 2 && Lo.nib_ok[cls])) nib = 0;
   const int lat = 4 * (nib ? Lo.lat_words_nib[cls] : Lo.lat_words[cls]);
@@ -308,27 +330,28 @@ int plan_class(const Layout& Lo, int cls, int lds_budget, int page_req, int g_re
   int pmin, pmax;
   page_range(Lo, cls, pmin, pmax);
   int P = 0, G = kSweepWave;
-  // workgroups that have to share a compute unit for all of the batch to run
-  // at once
-  const int batch_wg = (Lo.n_slots + kSweepWave - 1) / kSweepWave;
-  const int share = std::min(4, std::max(1, (batch_wg + n_compute_units() - 1) / n_compute_units()));
+  // the batch's workgroups per compute unit
+  const int per_cu = (wg_count(Lo, -1, kSweepWave) + n_compute_units() - 1) / n_compute_units();
   if (g_req > 0) G = std::min(g_req, kSweepWave);
   // producer by default when the class's workgroups do not outnumber the
   // compute units (the walkers' chain, not issue, then bounds the sweep)
   int prod = prod_req;
-  if (prod < 0) prod = (Lo.walkers[cls] + G - 1) / G <= n_compute_units() ? 1 : 0;
+  if (prod < 0) prod = wg_count(Lo, cls, G) <= n_compute_units() ? 1 : 0;
   if (page_req > 0) {
     P = std::min(std::max(pow2_ceil(page_req), pmin), pmax);
   } else {
-    for (int T = share; T >= 1 && P == 0; --T) {
-      for (int p = pmax; p >= pmin; p >>= 1) {
-        if ((size_t)T * lds_of(lat, kSweepWave, p, share == 1 ? prod : 0, tab) <= (size_t)lds_budget) {
-          P = p;
-          break;
-        }
+    auto takes = [&](int p, int pr) { return (int)align_up(lds_of(lat, kSweepWave, p, pr, tab), kLdsGrain); };
+    const int fit = std::max(1, lds_budget / takes(pmin, 0));
+    const int most = std::min({per_cu, fit, kMaxShare});
+    const int turns = (per_cu + most - 1) / most;
+    const int share = (per_cu + turns - 1) / turns;
+    P = pmin;
+    for (int p = pmax; p > pmin; p >>= 1) {
+      if (share * takes(p, per_cu == 1 ? prod : 0) <= lds_budget) {
+        P = p;
+        break;
       }
     }
-    if (P == 0) P = pmin;
   }
   while (G > 1 && lds_of(lat, G, P, prod, tab) > (size_t)lds_budget) --G;
   if (lds_of(lat, G, P, prod, tab) > (size_t)lds_budget) return REWL_E_INVAL;
