@@ -127,7 +127,8 @@ int rewl_run_sweeps(rewl_ctx* ctx, int64_t flips);
  * 0 = Ising L <= 32, 1 = Ising 32 < L <= 64, 2 = Potts.  A class is swept
  * with one lane per walker, in the shape below, or with one wavefront per
  * walker (walkers_per_group = 1; also the default, every argument left at
- * its default, of a batch of up to 7168 walkers, for Potts 5632): then the other
+ * its default, of a batch of up to 7168 walkers, for Potts 5632, and of
+ * larger ones whose instances have few: up to 7 and 5.5 on average): then the other
  * arguments matter only to a fused launch (rewl_set_batching), which always
  * takes the lane form.  For class cls (-1:
  * all classes) keep page_bins ln g bins of each walker's window in LDS (the

@@ -218,6 +218,13 @@ int build_layout(const rewl_params* params, int32_t n, const int32_t* wlo, const
   return REWL_OK;
 }
 
+// LDS is given out in pieces of this size (gfx950).  Ising L = 20 with 49152
+// walkers, three workgroups per compute unit: page 64, 54272 bytes each, of
+// which three would fit without it, 812 ns per attempt against 431.
+constexpr int kLdsGrain = 1280;
+// Two wavefronts per SIMD: they fill 89 % of its issue cycles.
+constexpr int kMaxShare = 8;
+
 // Sweep launch plan, per kernel class: either one wavefront per walker
 // (wave; rewl_wave.hip), or one lane per walker:
 // walkers per workgroup (G, one
@@ -239,12 +246,6 @@ int build_layout(const rewl_params* params, int32_t n, const int32_t* wlo, const
 // 1136 against 1235.  Workgroups are counted as they are made, of one
 // instance each: 4096 instances of 4 walkers (L = 8, sixteen per compute
 // unit) 1211 ns against 5334 when taken for one full workgroup.
-// LDS is given out in pieces of this size (gfx950).  Ising L = 20 with 49152
-// walkers, three workgroups per compute unit: page 64, 54272 bytes each, of
-// which three would fit without it, 812 ns per attempt against 431.
-constexpr int kLdsGrain = 1280;
-// Two wavefronts per SIMD: they fill 89 % of its issue cycles.
-constexpr int kMaxShare = 8;
 struct ClassPlan {
   int32_t G = 0, P = 0, count = 0, offset = 0;
   int32_t prod = 0;  // RNG producer wavefront per workgroup
@@ -318,7 +319,9 @@ int plan_class(const Layout& Lo, int cls, int lds_budget, int page_req, int g_re
   cp = ClassPlan();
   if (Lo.walkers[cls] == 0) return REWL_OK;
   const bool any_shape = page_req == 0 && g_req == 0 && prod_req < 0 && nib_req < 0;
-  cp.wave = g_req == 1 || (any_shape && Lo.n_slots <= (cls == 2 ? kWaveMaxPotts : kWaveMaxIsing));
+  const int all_wg = wg_count(Lo, -1, kSweepWave);
+  const int64_t wave_max = cls == 2 ? kWaveMaxPotts : kWaveMaxIsing;
+  cp.wave = g_req == 1 || (any_shape && (int64_t)Lo.n_slots * kSimds <= wave_max * std::max(all_wg, kSimds));
   // Potts nibbles halve the lattice and so raise the workgroups per compute
   // unit, at a little extra latency per attempt: by default when the class
   // has more workgroups than the GPU has compute units
@@ -331,7 +334,7 @@ int plan_class(const Layout& Lo, int cls, int lds_budget, int page_req, int g_re
   page_range(Lo, cls, pmin, pmax);
   int P = 0, G = kSweepWave;
   // the batch's workgroups per compute unit
-  const int per_cu = (wg_count(Lo, -1, kSweepWave) + n_compute_units() - 1) / n_compute_units();
+  const int per_cu = (all_wg + n_compute_units() - 1) / n_compute_units();
   if (g_req > 0) G = std::min(g_req, kSweepWave);
   // producer by default when the class's workgroups do not outnumber the
   // compute units (the walkers' chain, not issue, then bounds the sweep)

@@ -25,8 +25,14 @@ constexpr int kRngChunk = 16;     // attempts per hand-over of the RNG producer
 // L = 64 360 against 502, q = 10 Potts L = 20 418 against 386 (two-float 452
 // against 390), q = 8 Potts L = 32 343 against 475; at 8192 386 against 343,
 // 437 against 503, 490 against 389, 550 against 391, 441 against 477.
+// Where the lane form's workgroups outnumber the SIMDs, its time grows with
+// their number as well, and the limits with it: 7 (5.5) walkers in each.
+// 16384 walkers in instances of few, wavefronts against lanes: Ising L = 32
+// of 6 712 against 1285 ns, L = 64 of 5 765 against 3957, q = 10 Potts
+// L = 20 of 5 911 against 2606; of 10 (Ising L = 32) 691 against 517.
 constexpr int kWaveMaxIsing = 7168;
 constexpr int kWaveMaxPotts = 5632;
+constexpr int kSimds = 1024;
 constexpr int kMaxTemps = 16384;  // rewl_thermo temperatures per call
 // Allocation-free jackknife: doubles of the per-GPU device array that holds
 // one instance's window representatives and (m + 2) x nbins leave-one-out

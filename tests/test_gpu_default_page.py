@@ -34,3 +34,22 @@ def test_default_page_of_a_large_batch(L, per_cu, page):
         oracle_cycle(sim, 600)
         oracle_cycle(sim, 600)
         compare_state(ctx, i, sim)
+
+
+@pytest.mark.parametrize("model,L,q,h,wave", [
+    (WL.ISING, 12, 2, 6, True), (WL.ISING, 12, 2, 8, False),
+    (WL.POTTS, 6, 10, 5, True), (WL.POTTS, 6, 10, 6, False),
+])
+def test_default_form_of_many_small_instances(model, L, q, h, wave):
+    """Up to 7 (Potts 5.5) walkers per instance have a wavefront each."""
+    cfg = WL.config(model, L, q=q, n_windows=h, walkers_per_window=1)
+    n = 1700
+    ctx = gpu_context([cfg] * n)
+    (plan,) = ctx.set_launch().values()
+    assert (plan["walkers_per_group"] == 1) == wave, plan
+    ctx.run_cycles(2, 700)
+    for i in (0, n - 1):
+        sim = oracle_sim(cfg, instance=i)
+        oracle_cycle(sim, 700)
+        oracle_cycle(sim, 700)
+        compare_state(ctx, i, sim)
