@@ -222,7 +222,8 @@ int build_layout(const rewl_params* params, int32_t n, const int32_t* wlo, const
 // walkers, three workgroups per compute unit: page 64, 54272 bytes each, of
 // which three would fit without it, 812 ns per attempt against 431.
 constexpr int kLdsGrain = 1280;
-// Two wavefronts per SIMD: they fill 89 % of its issue cycles.
+// Two wavefronts per SIMD: together they have an instruction in issue on every
+// cycle.
 constexpr int kMaxShare = 8;
 
 // Sweep launch plan, per kernel class: either one wavefront per walker
