@@ -219,6 +219,9 @@ __global__ __launch_bounds__(256) void k_cycle_end(DevPtrs P, int32_t merged, in
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = (int)blockDim.x >> 6;
   const InstDesc& I = P.inst[inst];
   const InstState st = P.ist[inst];
+  // thread 0 writes the counters below, in a round without window pairs with
+  // no other barrier between: every wavefront has to have read them
+  __syncthreads();
   if (st.done || st.error) return;
   if (merged) {
     if (tid == 0) open = 0;
