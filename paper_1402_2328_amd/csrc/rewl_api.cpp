@@ -504,6 +504,9 @@ void fill_ptrs(rewl_ctx* c) {
   P.n_slots = L.n_slots;
   P.n_wg = (int32_t)c->plan.wg.size();
   P.prec = L.prec;
+  int64_t proposals = 0;
+  for (const InstDesc& I : L.inst) proposals = std::max(proposals, (int64_t)(I.h / 2) * I.m);
+  P.cycle_end_threads = cycle_end_threads(proposals);
 }
 
 int hip_rc(hipError_t e) { return e == hipSuccess ? REWL_OK : REWL_E_HIP; }

@@ -113,8 +113,18 @@ struct DevPtrs {
   double* jk;                // jackknife scratch: (m + 2) x nbins of one instance
   int32_t n_inst, n_win, n_slots, n_wg;
   int32_t prec;
-  int32_t pad;
+  int32_t cycle_end_threads;
 };
+
+// Threads of a block of the cycle end, from the most exchange proposals a
+// round of one of the batch's instances has: enough that each takes about one,
+// but no more than a batch of many small instances needs.
+constexpr int kCycleEndThreads = 256, kCycleEndMaxThreads = 1024;
+inline int cycle_end_threads(int64_t proposals) {
+  int t = kCycleEndThreads;
+  while (t < kCycleEndMaxThreads && t < proposals) t *= 2;
+  return t;
+}
 
 // Launch shape of one sweep kernel class (Ising L <= 32, Ising L <= 64,
 // Potts): lanes per LDS row (walkers per workgroup), 32-bit lattice words

@@ -203,20 +203,26 @@ __global__ __launch_bounds__(256) void k_merge_windows(DevPtrs P) {
 }
 
 // ---------------------------------------------------------------------------
-// End of a cycle, one 256-thread block per instance: the instance's merge
-// counter and finished flag (merged), then a replica exchange round over its
-// window pairs (exchange).  One launch in place of three: each costs 10 us
-// or so of a small batch's cycle, whose sweep takes 130 us (Ising L = 8).
-// The permutations are drawn by one thread per pair, the swaps made by one
-// wavefront per pair.
+// End of a cycle, one block per instance: the instance's merge counter and
+// finished flag (merged), then a replica exchange round over its window pairs
+// (exchange).  One launch in place of three: each costs 10 us or so of a small
+// batch's cycle, whose sweep takes 130 us (Ising L = 8).
+// Latency bounds it.  The permutations are drawn by one thread per pair (rows
+// padded to an odd number of words, else the threads' accesses meet in four
+// LDS banks), then one thread takes each proposal of all pairs, so an
+// instance of many windows needs a large block (cycle_end_threads): a round of
+// 300 windows of 8 walkers takes 6.8 us, of 64 walkers 28.9, with 256 threads
+// and a wavefront per pair 48.9 and 76.9; 48 windows of 16 walkers 6.3 and 9.4.
 // ---------------------------------------------------------------------------
-constexpr int kPairs = 64;  // window pairs at a time
+constexpr int kPairs = 256;  // window pairs at a time; no more than threads
+static_assert(kPairs <= kCycleEndThreads, "a thread draws each pair's permutation");
 
-__global__ __launch_bounds__(256) void k_cycle_end(DevPtrs P, int32_t merged, int32_t exchange) {
-  __shared__ uint8_t pi[kPairs][kMaxWalkersPerWindow];
+__global__ __launch_bounds__(kCycleEndMaxThreads) void k_cycle_end(DevPtrs P, int32_t merged, int32_t exchange) {
+  __shared__ uint8_t pi[kPairs][kMaxWalkersPerWindow + 4];
+  __shared__ uint32_t n_inr[kPairs], n_acc[kPairs];
   __shared__ int open;
   const int inst = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = (int)blockDim.x >> 6;
+  const int tid = threadIdx.x, nt = blockDim.x;
   const InstDesc& I = P.inst[inst];
   const InstState st = P.ist[inst];
   // thread 0 writes the counters below, in a round without window pairs with
@@ -226,7 +232,7 @@ __global__ __launch_bounds__(256) void k_cycle_end(DevPtrs P, int32_t merged, in
   if (merged) {
     if (tid == 0) open = 0;
     __syncthreads();
-    for (int w = tid; w < I.h; w += blockDim.x)
+    for (int w = tid; w < I.h; w += nt)
       if (!P.wst[I.win_base + w].frozen) open = 1;
     __syncthreads();
     if (tid == 0) {
@@ -261,47 +267,48 @@ __global__ __launch_bounds__(256) void k_cycle_end(DevPtrs P, int32_t merged, in
         p[i] = p[j];
         p[j] = tmp;
       }
+      n_inr[tid] = n_acc[tid] = 0;
     }
     __syncthreads();
-    for (int q = wave; q < pairs; q += waves) {
+    // proposal e: walker k of the lower window of pair q
+    for (int e = tid; e < pairs * m; e += nt) {
+      const int q = e / m, k = e - q * m;
       const int w = base + 2 * q, gw = I.win_base + w;
       const WinDesc W = P.win[gw], Wn = P.win[gw + 1];
-      bool inr = false, acc = false;
-      if (lane < m) {
-        const int k = pi[q][lane];
-        const int li = w * m + lane, lj = (w + 1) * m + k;
-        const int si = I.slot_base + li, sj = I.slot_base + lj;
-        const int32_t EX = P.E[si], EY = P.E[sj];
-        const int bx = (EX - I.emin) >> I.binw_shift, by = (EY - I.emin) >> I.binw_shift;
-        if (!(by < W.lo || by > W.hi || bx < Wn.lo || bx > Wn.hi)) {
-          inr = true;
-          const int64_t bi = W.lng_base + (int64_t)lane * W.nb;
-          const int64_t bj = Wn.lng_base + (int64_t)k * Wn.nb;
-          const int ix = bx - W.lo, iy = by - W.lo, jx = bx - Wn.lo, jy = by - Wn.lo;
-          const uint4 r = draw(I, t, (uint32_t)li, kTagAcc);
-          if (P.prec == kFP64) {
-            const double lnP = (P.lng[bi + ix] - P.lng[bi + iy]) + (P.lng[bj + jy] - P.lng[bj + jx]);
-            acc = accept64(u53(r.z, r.w), lnP);
-          } else {
-            const float x1 = (P.lhi[bi + ix] - P.lhi[bi + iy]) + (P.llo[bi + ix] - P.llo[bi + iy]);
-            const float x2 = (P.lhi[bj + jy] - P.lhi[bj + jx]) + (P.llo[bj + jy] - P.llo[bj + jx]);
-            acc = accept32(r.z >> 8, x1 + x2);
-          }
-          if (acc) {
-            const int32_t ci = P.cfg[si];
-            P.cfg[si] = P.cfg[sj];
-            P.cfg[sj] = ci;
-            P.E[si] = EY;
-            P.E[sj] = EX;
-          }
-        }
+      const int kn = pi[q][k];
+      const int li = w * m + k, lj = (w + 1) * m + kn;
+      const int si = I.slot_base + li, sj = I.slot_base + lj;
+      const int32_t EX = P.E[si], EY = P.E[sj];
+      const int bx = (EX - I.emin) >> I.binw_shift, by = (EY - I.emin) >> I.binw_shift;
+      if (by < W.lo || by > W.hi || bx < Wn.lo || bx > Wn.hi) continue;
+      atomicAdd(&n_inr[q], 1u);
+      const int64_t bi = W.lng_base + (int64_t)k * W.nb;
+      const int64_t bj = Wn.lng_base + (int64_t)kn * Wn.nb;
+      const int ix = bx - W.lo, iy = by - W.lo, jx = bx - Wn.lo, jy = by - Wn.lo;
+      const uint4 r = draw(I, t, (uint32_t)li, kTagAcc);
+      bool acc;
+      if (P.prec == kFP64) {
+        const double lnP = (P.lng[bi + ix] - P.lng[bi + iy]) + (P.lng[bj + jy] - P.lng[bj + jx]);
+        acc = accept64(u53(r.z, r.w), lnP);
+      } else {
+        const float x1 = (P.lhi[bi + ix] - P.lhi[bi + iy]) + (P.llo[bi + ix] - P.llo[bi + iy]);
+        const float x2 = (P.lhi[bj + jy] - P.lhi[bj + jx]) + (P.llo[bj + jy] - P.llo[bj + jx]);
+        acc = accept32(r.z >> 8, x1 + x2);
       }
-      const int n_inr = __popcll(__ballot(inr)), n_acc = __popcll(__ballot(acc));
-      if (lane == 0) {
-        P.xstats[3 * gw + 0] += (uint64_t)m;
-        P.xstats[3 * gw + 1] += (uint64_t)n_inr;
-        P.xstats[3 * gw + 2] += (uint64_t)n_acc;
-      }
+      if (!acc) continue;
+      atomicAdd(&n_acc[q], 1u);
+      const int32_t ci = P.cfg[si];
+      P.cfg[si] = P.cfg[sj];
+      P.cfg[sj] = ci;
+      P.E[si] = EY;
+      P.E[sj] = EX;
+    }
+    __syncthreads();
+    if (tid < pairs) {
+      uint64_t* const xs = P.xstats + 3 * (int64_t)(I.win_base + base + 2 * tid);
+      xs[0] += (uint64_t)m;
+      xs[1] += (uint64_t)n_inr[tid];
+      xs[2] += (uint64_t)n_acc[tid];
     }
     __syncthreads();
   }
@@ -596,18 +603,18 @@ __global__ __launch_bounds__(256) void k_thermo(DevPtrs P, int32_t instance, int
 // ---------------------------------------------------------------------------
 hipError_t launch_merge(const DevPtrs& P, hipStream_t s) {
   hipLaunchKernelGGL(k_merge_windows, dim3(P.n_win), dim3(256), 0, s, P);
-  hipLaunchKernelGGL(k_cycle_end, dim3(P.n_inst), dim3(256), 0, s, P, 1, 0);
+  hipLaunchKernelGGL(k_cycle_end, dim3(P.n_inst), dim3(P.cycle_end_threads), 0, s, P, 1, 0);
   return hipGetLastError();
 }
 
 hipError_t launch_exchange(const DevPtrs& P, hipStream_t s) {
-  hipLaunchKernelGGL(k_cycle_end, dim3(P.n_inst), dim3(256), 0, s, P, 0, 1);
+  hipLaunchKernelGGL(k_cycle_end, dim3(P.n_inst), dim3(P.cycle_end_threads), 0, s, P, 0, 1);
   return hipGetLastError();
 }
 
 hipError_t launch_merge_exchange(const DevPtrs& P, hipStream_t s) {
   hipLaunchKernelGGL(k_merge_windows, dim3(P.n_win), dim3(256), 0, s, P);
-  hipLaunchKernelGGL(k_cycle_end, dim3(P.n_inst), dim3(256), 0, s, P, 1, 1);
+  hipLaunchKernelGGL(k_cycle_end, dim3(P.n_inst), dim3(P.cycle_end_threads), 0, s, P, 1, 1);
   return hipGetLastError();
 }
 

@@ -27,3 +27,17 @@ def test_rounds_without_pairs(m):
             assert ctx.status(i)["rounds"] == rnd + 1
     for i, sim in enumerate(sims):
         compare_state(ctx, i, sim)
+
+
+@pytest.mark.parametrize("h,m", [(130, 1), (65, 9), (33, 33), (17, 64), (520, 2)])
+def test_rounds_of_many_proposals(h, m):
+    """Blocks of 256, 512 and 1024 threads with a last turn that is partly
+    empty, and more than 256 pairs."""
+    cfg = WL.config(WL.ISING, 40 if h > 300 else 24, n_windows=h, walkers_per_window=m, seed=3)
+    ctx, sim = gpu_context([cfg]), oracle_sim(cfg)
+    for _ in range(3):
+        ctx.run_sweeps(150)
+        ctx.exchange()
+        sim.sweep(150)
+        sim.exchange()
+    compare_state(ctx, 0, sim)
