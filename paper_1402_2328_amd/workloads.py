@@ -32,12 +32,24 @@ POTTS_Q10_L20_FP32C = dict(POTTS_Q10_L20, precision=FP32C)
 
 def bench_replicas(cfg, n_cu=256):
     """Copies of `cfg` that fill every compute unit with resident sweep
-    workgroups once, for the default launch plan."""
+    workgroups once, in the plan of the largest page that lets four of them
+    share a unit (else three, two or one).  The pages are asked for one by
+    one: the default page follows the size of the batch, here one instance."""
     from . import rewl
+    lds = 160 * 1024
     ctx = rewl.Context([rewl_params_of(cfg)])
-    (plan,) = ctx.set_launch(rng_producer=0, potts_nibbles=1).values()
+    plans, page = [], 1
+    while True:
+        (plan,) = ctx.set_launch(page_bins=page, rng_producer=0, potts_nibbles=1).values()
+        if plans and plan["page_bins"] == plans[-1]["page_bins"]:
+            break
+        plans.append(plan)
+        page = 2 * plan["page_bins"]
     ctx.close()
-    per_cu = max(1, (160 * 1024) // plan["lds_bytes"])
+    whole = [p for p in plans if p["walkers_per_group"] == 64]
+    plan = next((p for share in (4, 3, 2, 1) for p in reversed(whole) if share * p["lds_bytes"] <= lds),
+                plans[0])
+    per_cu = max(1, lds // plan["lds_bytes"])
     return max(1, (n_cu * per_cu) // plan["workgroups"])
 
 
