@@ -126,11 +126,11 @@ int rewl_run_sweeps(rewl_ctx* ctx, int64_t flips);
 /* Launch shape of the sweep.  Walkers are grouped by kernel class:
  * 0 = Ising L <= 32, 1 = Ising 32 < L <= 64, 2 = Potts.  A class is swept
  * with one lane per walker, in the shape below, or with one wavefront per
- * walker (walkers_per_group = 1; also the default, every argument left at
- * its default, of a batch of up to 7168 walkers, for Potts 5632, and of
- * larger ones whose instances have few: up to 7 and 5.5 on average): then the other
- * arguments matter only to a fused launch (rewl_set_batching), which always
- * takes the lane form.  For class cls (-1:
+ * walker: with walkers_per_group = 1 and the other arguments at their
+ * defaults (0, -1, -1), and by default, all four left so, where the batch has
+ * few walkers: up to 7168, for Potts 5632, and in larger ones up to 7 and 5.5
+ * per instance on average.  A fused launch (rewl_set_batching) always takes
+ * the lane form.  For lanes: in class cls (-1:
  * all classes) keep page_bins ln g bins of each walker's window in LDS (the
  * rest stays in device memory; the page follows the walker) and put
  * walkers_per_group walkers in each workgroup; 0 picks the default (the
@@ -153,7 +153,9 @@ int rewl_run_sweeps(rewl_ctx* ctx, int64_t flips);
  * shape, only speed does.  out: NULL
  * or 21 entries: per class {page_bins, walkers_per_group, LDS bytes per
  * workgroup, workgroups, rng_producer, potts_nibbles}, then the batch's
- * {fused, splits, order} (rewl_set_batching).  A fused batch whose classes
+ * {fused, splits, order} (rewl_set_batching).  The values set again give the
+ * same plan; a class swept with wavefronts has page_bins 0, walkers_per_group
+ * 1, rng_producer -1 and potts_nibbles -1.  A fused batch whose classes
  * no longer share one rng_producer setting returns to per-class launches.
  * Synchronises.  Errors: INVAL (shape does not fit in LDS), HIP. */
 int rewl_set_launch(rewl_ctx* ctx, int32_t cls, int32_t page_bins, int32_t walkers_per_group,

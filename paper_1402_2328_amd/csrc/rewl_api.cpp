@@ -319,10 +319,11 @@ int plan_class(const Layout& Lo, int cls, int lds_budget, int page_req, int g_re
                int nib_req, ClassPlan& cp) {
   cp = ClassPlan();
   if (Lo.walkers[cls] == 0) return REWL_OK;
-  const bool any_shape = page_req == 0 && g_req == 0 && prod_req < 0 && nib_req < 0;
+  // a request that names a page, a producer or a lattice form is for lanes
+  const bool any_shape = page_req == 0 && prod_req < 0 && nib_req < 0;
   const int all_wg = wg_count(Lo, -1, kSweepWave);
   const int64_t wave_max = cls == 2 ? kWaveMaxPotts : kWaveMaxIsing;
-  cp.wave = g_req == 1 || (any_shape && (int64_t)Lo.n_slots * kSimds <= wave_max * std::max(all_wg, kSimds));
+  cp.wave = any_shape && (g_req == 1 || (g_req == 0 && (int64_t)Lo.n_slots * kSimds <= wave_max * std::max(all_wg, kSimds)));
   // Potts nibbles halve the lattice and so raise the workgroups per compute
   // unit, at a little extra latency per attempt: by default when the class
   // has more workgroups than the GPU has compute units
@@ -754,16 +755,19 @@ int install_plan(rewl_ctx* c, const LaunchPlan& pl) {
   return rc;
 }
 
+// What a caller can set again for the same plan: a class swept with
+// wavefronts has no page, producer or lattice form to report.
 void plan_out(const Layout& Lo, const LaunchPlan& pl, int32_t* out) {
   if (!out) return;
   for (int cls = 0; cls < 3; ++cls) {
-    const bool wave = pl.cls[cls].wave && !pl.fused;
-    out[6 * cls + 0] = pl.cls[cls].P;
-    out[6 * cls + 1] = wave ? 1 : pl.cls[cls].G;
-    out[6 * cls + 2] = wave ? wave_lds_bytes(cls, wave_lat_bytes(Lo, cls), Lo.l_min[cls], pl.cls[cls].count) : (int32_t)pl.cls[cls].lds_bytes;
-    out[6 * cls + 3] = pl.cls[cls].count;
-    out[6 * cls + 4] = pl.cls[cls].prod;
-    out[6 * cls + 5] = pl.cls[cls].nib;
+    const ClassPlan& cp = pl.cls[cls];
+    const bool wave = cp.wave && !pl.fused;
+    out[6 * cls + 0] = wave ? 0 : cp.P;
+    out[6 * cls + 1] = wave ? 1 : cp.G;
+    out[6 * cls + 2] = wave ? wave_lds_bytes(cls, wave_lat_bytes(Lo, cls), Lo.l_min[cls], cp.count) : (int32_t)cp.lds_bytes;
+    out[6 * cls + 3] = cp.count;
+    out[6 * cls + 4] = wave ? -1 : cp.prod;
+    out[6 * cls + 5] = wave ? -1 : cp.nib;
   }
   out[18] = pl.fused;
   out[19] = pl.splits;
