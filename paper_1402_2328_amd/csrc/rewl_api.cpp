@@ -45,6 +45,7 @@ struct Layout {
   int32_t walkers[3] = {0, 0, 0};
   int32_t n_max[3] = {0, 0, 0};          // most sites of an instance
   int32_t l_min[3] = {kMaxL, kMaxL, kMaxL};  // side of the smallest lattice
+  int32_t l_max[3] = {0, 0, 0};              // and of the largest
   int32_t prec = 0;
   // byte offsets inside the workspace
   int64_t jk_elems = 0;  // largest (m + 2) * nbins of any instance
@@ -166,6 +167,7 @@ int build_layout(const rewl_params* params, int32_t n, const int32_t* wlo, const
     Lo.walkers[cls] += I.W;
     Lo.n_max[cls] = std::max(Lo.n_max[cls], I.N);
     Lo.l_min[cls] = std::min(Lo.l_min[cls], I.L);
+    Lo.l_max[cls] = std::max(Lo.l_max[cls], I.L);
     slot += I.W;
     win += I.h;
     spin += (int64_t)I.W * I.npad;
@@ -322,8 +324,8 @@ int plan_class(const Layout& Lo, int cls, int lds_budget, int page_req, int g_re
   // a request that names a page, a producer or a lattice form is for lanes
   const bool any_shape = page_req == 0 && prod_req < 0 && nib_req < 0;
   const int all_wg = wg_count(Lo, -1, kSweepWave);
-  const int64_t wave_max = cls == 2 ? kWaveMaxPotts : kWaveMaxIsing;
-  cp.wave = any_shape && (g_req == 1 || (g_req == 0 && (int64_t)Lo.n_slots * kSimds <= wave_max * std::max(all_wg, kSimds)));
+  const bool few = Lo.n_slots <= wave_max_walkers(cls, Lo.l_max[cls], !Lo.potts3[cls], all_wg, n_compute_units());
+  cp.wave = any_shape && (g_req == 1 || (g_req == 0 && few));
   // Potts nibbles halve the lattice and so raise the workgroups per compute
   // unit, at a little extra latency per attempt: by default when the class
   // has more workgroups than the GPU has compute units
@@ -924,7 +926,7 @@ int rewl_autotune(rewl_ctx* c, int64_t flips, int32_t repeats, int32_t* out) {
     pl.cls[cls].wave = 1;
     return true;
   };
-  const bool try_wave = L.n_slots <= 4 * kWaveMaxIsing;
+  const bool try_wave = L.n_slots <= 28672;
   if (try_wave && !rc) {
     LaunchPlan pl = c->plan;
     pl.fused = 0;

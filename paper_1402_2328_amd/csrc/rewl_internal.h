@@ -16,23 +16,61 @@ constexpr int kMaxWalkersPerWindow = 64;
 constexpr int kMaxL = 64;
 constexpr int kSweepWave = 64;    // walkers' wavefront of a sweep workgroup
 constexpr int kRngChunk = 16;     // attempts per hand-over of the RNG producer
-// Batches of at most this many walkers are swept with one wavefront per
-// walker by default, larger ones with one lane per walker.  A wavefront
-// makes an attempt in 110 to 200 ns while no SIMD holds two of them (1024
-// walkers), from there on the time grows with their number; a lane takes 340
-// to 510 ns in its default shape however many there are (up to 16384).  At
-// 6144 walkers, wavefronts against lanes: Ising L = 32 304 against 341 ns,
-// L = 64 360 against 502, q = 10 Potts L = 20 418 against 386 (two-float 452
-// against 390), q = 8 Potts L = 32 343 against 475; at 8192 386 against 343,
-// 437 against 503, 490 against 389, 550 against 391, 441 against 477.
-// Where the lane form's workgroups outnumber the SIMDs, its time grows with
-// their number as well, and the limits with it: 7 (5.5) walkers in each.
-// 16384 walkers in instances of few, wavefronts against lanes: Ising L = 32
-// of 6 712 against 1285 ns, L = 64 of 5 765 against 3957, q = 10 Potts
-// L = 20 of 5 911 against 2606; of 10 (Ising L = 32) 691 against 517.
-constexpr int kWaveMaxIsing = 7168;
-constexpr int kWaveMaxPotts = 5632;
 constexpr int kSimds = 1024;
+// Walkers up to which a class of a batch is swept with one wavefront per
+// walker by default (larger batches with one lane per walker): cls the kernel
+// class, l_max the side of its largest lattice, two_state an Ising model or
+// q = 2 Potts throughout, n_wg the lane form's workgroups (of up to 64 walkers
+// of one instance), n_cu the compute units.
+//
+// A wavefront makes an attempt in 110 to 200 ns while no SIMD holds two of them
+// (1024 walkers), from there on the time grows with their number, and faster
+// on small lattices, where more of 64 attempts touch each other's sites.  A
+// lane takes as long however many there are, until the workgroups wait for
+// one another.  ns per attempt below are lanes, wavefronts.
+//
+// Up to a workgroup per compute unit, each with its producer, lanes are at
+// their best, and the better the smaller the lattice.  8 walkers per window:
+//   Ising, walkers  4096      5120      6144      7168
+//     L =  8     302, 300  304, 349  303, 403  304, 477
+//     L = 16     320, 268  319, 312  319, 357  318, 410
+//     L = 24     360, 240  360, 292  360, 335  363, 383
+//     L = 32     363, 228  363, 272  365, 311  366, 358
+//     L = 48     495, 222  499, 256  499, 291  503, 335
+//   Potts, walkers  4096      5120      5632
+//     q = 10, L =  8  398, 355  392, 417
+//     q = 10, L = 12  397, 334  396, 389  403, 459
+//     q =  3, L = 16  406, 300  409, 352  424, 413
+//     q = 10, L = 20  404, 283  404, 367
+// (two-float: Ising L = 8 329, 339 at 4096; L = 32 395, 410 at 7168; q = 10
+// Potts L = 20 411, 402 at 5120).  With more workgroups than that there is no
+// producer, and up to one workgroup per SIMD wavefronts win throughout: 16
+// walkers per instance, Ising L = 8 505, 477 at 7168, L = 24 613, 383; q = 10
+// Potts L = 8 627, 476 at 5632.
+//
+// Where the lane form's workgroups outnumber the SIMDs, their time grows with
+// their number as well, and the limit becomes one of walkers per workgroup: 7
+// (Potts 5.5).  16380 walkers, Ising of 7 per instance, L = 16 1211, 802; q =
+// 10 Potts L = 20 of 5 2605, 907.  Beyond five workgroups per SIMD the lane
+// form's turns on a compute unit are all full ones, and small lattices of two
+// states, whose lanes are quick, are better off with fewer walkers per
+// workgroup.  40960 (65536) walkers: Ising L = 8 of 4 2317, 2189 (3354, 3442),
+// of 5 1974, 2139 (2795, 3344); L = 12 of 6 2006, 2053 (2791, 3212); L = 16 of
+// 6 2144, 1955 (3013, 3005), of 7 1899, 1944 (2715, 3006); L = 20 of 7 2202,
+// 1884 (3117, 2961); q = 2 Potts L = 8 of 5 2441, 2532 (3531, 3908); but L = 32
+// of 7 2548, 1713 (3799, 2712), q = 10 Potts L = 6 of 5 3007, 2319 (4512,
+// 3557).
+inline int64_t wave_max_walkers(int cls, int l_max, bool two_state, int n_wg, int n_cu) {
+  const int64_t most = cls == 2 ? 5632 : 7168;
+  if (n_wg <= n_cu) {
+    const int64_t alone = 3072 + 128 * (int64_t)l_max;
+    return alone < most ? alone : most;
+  }
+  if (n_wg <= kSimds) return most;
+  const int64_t crowded = 3328 + 192 * (int64_t)l_max;
+  const int64_t per_simd = n_wg > 5 * kSimds && two_state && crowded < most ? crowded : most;
+  return per_simd * n_wg / kSimds;
+}
 constexpr int kMaxTemps = 16384;  // rewl_thermo temperatures per call
 // Allocation-free jackknife: doubles of the per-GPU device array that holds
 // one instance's window representatives and (m + 2) x nbins leave-one-out
