@@ -194,7 +194,8 @@ int rewl_set_batching(rewl_ctx* ctx, int32_t fused, int32_t splits, int32_t orde
  * the plan with the lowest mean plus standard deviation of its cycle times
  * is kept (a plan whose time swings with the placement of concurrent
  * kernels pays for the swings).
- * The plan in force before the call is the first candidate.
+ * The plan in force before the call and the default plan are the first
+ * candidates.
  * The simulation state is saved to host memory first and restored
  * afterwards, so tuning changes nothing but the launch shape.  out: as for
  * rewl_set_launch.  Synchronises.

@@ -422,6 +422,15 @@ void fill_table(const Layout& Lo, LaunchPlan& pl) {
   }
 }
 
+bool same_plan(const LaunchPlan& a, const LaunchPlan& b) {
+  bool same = a.fused == b.fused && a.splits == b.splits && a.order == b.order;
+  for (int cls = 0; cls < 3; ++cls) {
+    const ClassPlan &x = a.cls[cls], &y = b.cls[cls];
+    same = same && x.G == y.G && x.P == y.P && x.prod == y.prod && x.nib == y.nib && x.wave == y.wave;
+  }
+  return same;
+}
+
 // A fused launch needs one RNG-producer setting for every class present.
 bool fusable(const Layout& Lo, const LaunchPlan& pl) {
   int prod = -1, classes = 0;
@@ -881,7 +890,12 @@ int rewl_autotune(rewl_ctx* c, int64_t flips, int32_t repeats, int32_t* out) {
     return REWL_OK;
   };
   auto best = [&]() -> const LaunchPlan& { return top.front().second; };
-  rc = consider(c->plan);
+  const LaunchPlan before = c->plan;
+  // The plan in force, and the default one whatever is in force.
+  LaunchPlan by_default;
+  if (!rc) rc = plan_launch(L, budget, 0, 0, by_default);
+  if (!rc) rc = consider(c->plan);
+  if (!rc && !same_plan(by_default, before)) rc = consider(by_default);
   int pmin_all = 1 << 30, pmax_all = 0, classes = 0;
   for (int cls = 0; cls < 3; ++cls) {
     if (L.walkers[cls] == 0) continue;
@@ -919,14 +933,15 @@ int rewl_autotune(rewl_ctx* c, int64_t flips, int32_t repeats, int32_t* out) {
         }
       }
   // One wavefront per walker in every class, unless there are far too many
-  // walkers for it to pay.
+  // walkers for it to pay (four times the most that have it by default).
   auto as_wave = [&](LaunchPlan& pl, int cls) {
     if (L.walkers[cls] == 0) return true;
     if (plan_class(L, cls, budget, 0, 0, -1, -1, pl.cls[cls])) return false;
     pl.cls[cls].wave = 1;
     return true;
   };
-  const bool try_wave = L.n_slots <= 28672;
+  const int n_wg = std::max(wg_count(L, -1, kSweepWave), kSimds);
+  const bool try_wave = (int64_t)L.n_slots * kSimds <= (int64_t)28672 * n_wg;
   if (try_wave && !rc) {
     LaunchPlan pl = c->plan;
     pl.fused = 0;
