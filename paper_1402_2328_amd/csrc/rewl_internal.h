@@ -179,9 +179,34 @@ struct SweepShape {
 hipError_t launch_init(const DevPtrs& P, int32_t lat_bytes, hipStream_t s);
 // One sweep kernel class: 0 = Ising L <= 32, 1 = Ising 32 < L <= 64,
 // 2 = Potts; n_wg workgroups starting at sh.wg_offset of the table;
-// producer: a second wavefront per workgroup computes the random numbers.
+// producer: a second wavefront per workgroup computes the random numbers;
+// counts: h_in_page.
 hipError_t launch_sweep_class(const DevPtrs& P, int cls, SweepShape sh, int32_t n_wg, int64_t flips,
-                              size_t lds_bytes, bool producer, hipStream_t s);
+                              size_t lds_bytes, bool producer, bool counts, hipStream_t s);
+// Whether the page of a class (pages of `page` bins; not in a fused launch)
+// holds whole counts of H, loaded and stored with their ln g, or increments,
+// added to H by an atomic when a bin leaves.  lng_elems: walkers' bins of the
+// batch.  The load is one more per entering bin, the atomic takes longer to
+// leave and fetches its line.  Counts win where pages shift seldom, and where
+// ln g and H (12 bytes per bin) do not stay in the 256 MB last-level cache.  ns
+// per attempt, increments against counts:
+//   page 32 to 128: Ising L = 8, 32768 walkers 333, 318; L = 16, 65536 516,
+//     486, two-float 569, 542; L = 24, 65536 634, 611, two-float 16384 408,
+//     396; L = 32, 65536 662, 628; L = 48, 16384 514, 503; L = 64, 32768 717,
+//     707; the worst L = 64, 8192 620, 627.
+//   page 16, 8 walkers per window, up to 200 MB: L = 8 (60 MB) 1245, 1271; L =
+//     12 (65 MB) 603, 608; L = 16 (111 MB) 697, 708, two-float (148 MB) 860,
+//     877; L = 40 (76 MB) 868, 887; L = 28 (196 MB) 986, 993.
+//   page 16, beyond: L = 20 (230 MB) 939, 909; L = 16 (296 MB) 1831, 1744, (591
+//     MB) 3603, 3082; L = 24 (331 MB) 1080, 1026; L = 32 (341 MB) 1271, 1230,
+//     with 16 walkers in 4 windows (922 MB) 1623, 1424; L = 48 (1037 MB) 1154,
+//     1094; the worst L = 40 (266 MB) 877, 890.
+// Potts pages shift most often (four bins a move): q = 10 L = 20, 65536 684,
+// 695, two-float 131072 1508, 1540; L = 32 (340 MB) 1604, 1619.  The fused
+// launch of 64 uneven instances takes 0.5 % more with counts.
+inline bool h_in_page(int cls, int page, int64_t lng_elems) {
+  return cls != 2 && (page > 16 || 12 * lng_elems > (int64_t)192 << 20);
+}
 // Deals the wavefronts of the next launch evenly to the SIMDs of every
 // compute unit; before a sweep of at least as many workgroups as there are.
 hipError_t launch_even_out(int32_t n_cu, hipStream_t s);

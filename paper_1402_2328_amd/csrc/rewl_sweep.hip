@@ -111,7 +111,7 @@ __device__ __forceinline__ int potts_de(int a, int b, int c, int d, int s0, int 
 // rows next to each other are reached by offsets in the instruction (one
 // ds_read2st64_b32 for both words of an FP64 ln g).
 // The sweep of workgroup-table entry wgi, with the launch's dynamic LDS.
-// COUNTS: the L = 32 loop keeps whole counts of H in the page (below).
+// COUNTS: whole counts of H in the page (h_in_page), not increments.
 template <int MODEL, int PREC, int ROWW, bool PROD, bool S64, bool COUNTS>
 __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& sh, int64_t flips, int wgi,
                                            unsigned char* lds) {
@@ -275,17 +275,9 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   };
   auto getf = [&](int off, int row) { return __uint_as_float(word(off, row)); };
   auto putf = [&](int off, int row, float v) { word(off, row) = __float_as_uint(v); };
-  // H in the page: in the L = 32 Ising loop a bin's whole count, loaded with
-  // its ln g and stored back; in the others the increments since it entered,
-  // added to device memory by an atomic when it leaves.  The atomics fetch
-  // the same lines and are the slower way out where device memory is busy,
-  // the load is one more per entering bin.  Counts against increments: 5.80
-  // against 6.23 ms per sweep on 1024 instances (131072 walkers) of Ising
-  // L = 32 with 16 windows, 777 against 897 ns per attempt with 8, 1 to 2 %
-  // fewer on 49152 walkers; but 1 to 2 % more on L = 8 to 28, 2 % more on Potts
-  // with one wavefront per SIMD, and 0.5 % more in the fused launch of the
-  // 64-instance mix.
-  const bool h_load = COUNTS && L == 32;
+  // H in the page: a bin's whole count, loaded with its ln g and stored back
+  // (COUNTS), or the increments since it entered, added to device memory by an
+  // atomic when it leaves.  h_in_page says which and why.
   const int cnt = nb < PG ? nb : PG;
   const int hi_pm = nb - cnt;  // highest page start; 0: the window is in LDS entirely
   int m_pm = __builtin_amdgcn_readfirstlane(M - PM);
@@ -303,7 +295,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       putf(j, 0, *at_off(lhw, e << 2));
       putf(j, 1, *at_off(llw, e << 2));
     }
-    word(j, 2) = h_load ? *at_off(Hw, e << 2) : 0u;
+    word(j, 2) = COUNTS ? *at_off(Hw, e << 2) : 0u;
   }
   constexpr int DMAX = (MODEL == kPotts) ? 4 : 2;
   // Bins in flight after a page shift of pend_n bins: slot pend_row[i] holds
@@ -327,7 +319,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   // Settles the bins in flight: the leaving bins are written back (ln g
   // stored, H counts stored or increments added in device memory) and the
   // entering bins take their slots.
-  auto settle = [&](auto counts) {
+  auto settle = [&]() {
     // All lanes' loads have arrived here (vmcnt 0).  Waited for inside the
     // branch only, the compiler has to take them as pending after it, and
     // may wait again, then for the stores below as well, where the next
@@ -343,14 +335,14 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
           putf(j, 0, pend_hi[i]);
           putf(j, 1, pend_lo[i]);
         }
-        word(j, 2) = counts ? pend_h[i] : 0u;
+        word(j, 2) = COUNTS ? pend_h[i] : 0u;
         if (PREC == kFP64) {
           *at_off(lngw, (pend_e << 3) + 8u * i) = ev_l[i];
         } else {
           *at_off(lhw, (pend_e << 2) + 4u * i) = ev_hi[i];
           *at_off(llw, (pend_e << 2) + 4u * i) = ev_lo[i];
         }
-        if (counts) *at_off(Hw, (pend_e << 2) + 4u * i) = ev_h[i];
+        if (COUNTS) *at_off(Hw, (pend_e << 2) + 4u * i) = ev_h[i];
         else atomicAdd(at_off(Hw, (pend_e << 2) + 4u * i), ev_h[i]);
       }
     }
@@ -381,7 +373,6 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
                       uint32_t fm, int site, auto lkt, auto nbt) -> bool {
     constexpr bool NB = decltype(nbt)::value;
     constexpr bool TAB = decltype(lkt)::value == 3;
-    constexpr bool H_LOAD = COUNTS && decltype(lkt)::value == 2;
     const bool inwin = (uint32_t)bn < (uint32_t)nb;
     const int jn = pslot(bn);
     bool acc;
@@ -452,7 +443,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       lds_add(jcur + (S64 ? 512 : 2 * S4), 1u);
     }
     // settle the bins of the last shift, then follow the walker
-    settle(std::bool_constant<H_LOAD>{});
+    settle();
     // bin + M - PM is the lowest page start that still covers bin + M,
     // bin - M the highest that covers bin - M (PM >= 2M); the start then
     // stays inside [0, hi_pm] (0 for a window that is in LDS entirely, which
@@ -485,7 +476,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
             ev_hi[i] = getf(j, 0);
             ev_lo[i] = getf(j, 1);
           }
-          if (H_LOAD) pend_h[i] = *at_off(Hw, (en << 2) + 4u * i);
+          if (COUNTS) pend_h[i] = *at_off(Hw, (en << 2) + 4u * i);
           ev_h[i] = word(j, 2);
           pend_row[i] = j;
         }
@@ -743,7 +734,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   }
 
   // ---- stage out ----
-  settle(h_load);
+  settle();
   if (!frozen) {
     for (int i = 0; i < cnt; ++i) {
       const int b = base + i;
@@ -756,7 +747,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
         *at_off(llw, e << 2) = getf(j, 1);
       }
       const uint32_t h = word(j, 2);
-      if (h_load) *at_off(Hw, e << 2) = h;
+      if (COUNTS) *at_off(Hw, e << 2) = h;
       else if (h) atomicAdd(at_off(Hw, e << 2), h);
     }
   }
@@ -785,11 +776,11 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
 
 // One kernel class per launch: the class's workgroups are entries
 // [sh.wg_offset, sh.wg_offset + gridDim.x) of the table.
-template <int MODEL, int PREC, int ROWW, bool PROD, bool S64>
+template <int MODEL, int PREC, int ROWW, bool PROD, bool S64, bool COUNTS>
 __global__ __launch_bounds__(PROD ? 2 * kSweepWave : kSweepWave) void k_sweep(DevPtrs P, SweepShape sh,
                                                                                 int64_t flips) {
   extern __shared__ __align__(16) unsigned char lds[];
-  sweep_body<MODEL, PREC, ROWW, PROD, S64, MODEL == kIsing && ROWW == 1>(P, sh, flips, sh.wg_offset + (int)blockIdx.x, lds);
+  sweep_body<MODEL, PREC, ROWW, PROD, S64, COUNTS>(P, sh, flips, sh.wg_offset + (int)blockIdx.x, lds);
 }
 
 // Every kernel class of a batch in one launch: workgroup b runs table entry
@@ -815,17 +806,18 @@ using SweepFn = void (*)(DevPtrs, SweepShape, int64_t);
 using FusedFn = void (*)(DevPtrs, SweepShape, SweepShape, SweepShape, int64_t);
 
 template <int PREC, bool PROD, bool S64>
-SweepFn sweep_fn(int cls) {
-  return cls == 0 ? k_sweep<kIsing, PREC, 1, PROD, S64>
-                  : cls == 1 ? k_sweep<kIsing, PREC, 2, PROD, S64> : k_sweep<kPotts, PREC, 0, PROD, S64>;
+SweepFn sweep_fn(int cls, bool counts) {
+  if (cls == 0) return counts ? k_sweep<kIsing, PREC, 1, PROD, S64, true> : k_sweep<kIsing, PREC, 1, PROD, S64, false>;
+  if (cls == 1) return counts ? k_sweep<kIsing, PREC, 2, PROD, S64, true> : k_sweep<kIsing, PREC, 2, PROD, S64, false>;
+  return k_sweep<kPotts, PREC, 0, PROD, S64, false>;
 }
 
-SweepFn sweep_fn(int prec, bool prod, bool s64, int cls) {
+SweepFn sweep_fn(int prec, bool prod, bool s64, int cls, bool counts) {
   if (prec == kFP64)
-    return prod ? (s64 ? sweep_fn<kFP64, true, true>(cls) : sweep_fn<kFP64, true, false>(cls))
-                : (s64 ? sweep_fn<kFP64, false, true>(cls) : sweep_fn<kFP64, false, false>(cls));
-  return prod ? (s64 ? sweep_fn<kFP32C, true, true>(cls) : sweep_fn<kFP32C, true, false>(cls))
-              : (s64 ? sweep_fn<kFP32C, false, true>(cls) : sweep_fn<kFP32C, false, false>(cls));
+    return prod ? (s64 ? sweep_fn<kFP64, true, true>(cls, counts) : sweep_fn<kFP64, true, false>(cls, counts))
+                : (s64 ? sweep_fn<kFP64, false, true>(cls, counts) : sweep_fn<kFP64, false, false>(cls, counts));
+  return prod ? (s64 ? sweep_fn<kFP32C, true, true>(cls, counts) : sweep_fn<kFP32C, true, false>(cls, counts))
+              : (s64 ? sweep_fn<kFP32C, false, true>(cls, counts) : sweep_fn<kFP32C, false, false>(cls, counts));
 }
 
 FusedFn fused_fn(int prec, bool prod, bool s64) {
@@ -842,8 +834,9 @@ hipError_t prepare_sweep_lds(size_t lds_bytes) {
   for (int i = 0; i < 8; ++i) {
     const int prec = i & 1 ? kFP32C : kFP64;
     const bool prod = (i & 2) != 0, s64 = (i & 4) != 0;
-    const void* fns[] = {(const void*)sweep_fn(prec, prod, s64, 0), (const void*)sweep_fn(prec, prod, s64, 1),
-                         (const void*)sweep_fn(prec, prod, s64, 2), (const void*)fused_fn(prec, prod, s64)};
+    const void* fns[] = {(const void*)sweep_fn(prec, prod, s64, 0, false), (const void*)sweep_fn(prec, prod, s64, 0, true),
+                         (const void*)sweep_fn(prec, prod, s64, 1, false), (const void*)sweep_fn(prec, prod, s64, 1, true),
+                         (const void*)sweep_fn(prec, prod, s64, 2, false), (const void*)fused_fn(prec, prod, s64)};
     for (const void* f : fns) {
       hipFuncAttributes at;
       hipError_t e = hipFuncGetAttributes(&at, f);
@@ -873,9 +866,9 @@ hipError_t launch_even_out(int32_t n_cu, hipStream_t s) {
 }
 
 hipError_t launch_sweep_class(const DevPtrs& P, int cls, SweepShape sh, int32_t n_wg, int64_t flips,
-                              size_t lds_bytes, bool producer, hipStream_t s) {
+                              size_t lds_bytes, bool producer, bool counts, hipStream_t s) {
   if (n_wg <= 0) return hipSuccess;
-  const SweepFn f = sweep_fn(P.prec, producer, sh.stride == kSweepWave, cls);
+  const SweepFn f = sweep_fn(P.prec, producer, sh.stride == kSweepWave, cls, counts);
   hipLaunchKernelGGL(f, dim3(n_wg), dim3(producer ? 2 * kSweepWave : kSweepWave), lds_bytes, s, P, sh, flips);
   return hipGetLastError();
 }
