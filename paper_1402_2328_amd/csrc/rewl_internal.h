@@ -174,6 +174,21 @@ struct SweepShape {
   int32_t stride, nw, page, wg_offset, nib, tab;
 };
 
+// f(first, n) launches workgroups first to first + n - 1 of `total`, each of
+// `threads` threads.  A launch's threads have to stay below 2^32: beyond that
+// their number wraps round and the rest is left out without an error, which a
+// wavefront per walker reaches with 2^26 walkers.
+template <typename F>
+hipError_t in_slices(int32_t total, int32_t threads, F f) {
+  const int32_t most = (int32_t)(((int64_t)1 << 31) / threads);
+  hipError_t e = hipSuccess;
+  for (int64_t first = 0; first < total && e == hipSuccess; first += most) {
+    f((int32_t)first, total - first < most ? (int32_t)(total - first) : most);
+    e = hipGetLastError();
+  }
+  return e;
+}
+
 // Launchers (kernels TU).  All enqueue on `s` and return the launch status.
 // lat_bytes: spins of the batch's largest lattice, rounded up to 16.
 hipError_t launch_init(const DevPtrs& P, int32_t lat_bytes, hipStream_t s);

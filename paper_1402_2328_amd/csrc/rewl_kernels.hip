@@ -106,10 +106,10 @@ __device__ __forceinline__ TwoFloat mean_two_float(const float* hi, const float*
 // wavefront (a block reduction per walker took 181 us for 64 walkers of a
 // 206-bin window).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_merge_windows(DevPtrs P) {
+__global__ __launch_bounds__(256) void k_merge_windows(DevPtrs P, int32_t first) {
   __shared__ uint32_t red[8];
   __shared__ int not_ready;
-  const int gw = blockIdx.x;
+  const int gw = first + (int)blockIdx.x;
   const WinDesc W = P.win[gw];
   const InstDesc& I = P.inst[W.inst];
   const WinState ws0 = P.wst[gw];
@@ -217,11 +217,12 @@ __global__ __launch_bounds__(256) void k_merge_windows(DevPtrs P) {
 constexpr int kPairs = 256;  // window pairs at a time; no more than threads
 static_assert(kPairs <= kCycleEndThreads, "a thread draws each pair's permutation");
 
-__global__ __launch_bounds__(kCycleEndMaxThreads) void k_cycle_end(DevPtrs P, int32_t merged, int32_t exchange) {
+__global__ __launch_bounds__(kCycleEndMaxThreads) void k_cycle_end(DevPtrs P, int32_t first, int32_t merged,
+                                                                   int32_t exchange) {
   __shared__ uint8_t pi[kPairs][kMaxWalkersPerWindow + 4];
   __shared__ uint32_t n_inr[kPairs], n_acc[kPairs];
   __shared__ int open;
-  const int inst = blockIdx.x;
+  const int inst = first + (int)blockIdx.x;
   const int tid = threadIdx.x, nt = blockDim.x;
   const InstDesc& I = P.inst[inst];
   const InstState st = P.ist[inst];
@@ -601,21 +602,28 @@ __global__ __launch_bounds__(256) void k_thermo(DevPtrs P, int32_t instance, int
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
-hipError_t launch_merge(const DevPtrs& P, hipStream_t s) {
-  hipLaunchKernelGGL(k_merge_windows, dim3(P.n_win), dim3(256), 0, s, P);
-  hipLaunchKernelGGL(k_cycle_end, dim3(P.n_inst), dim3(P.cycle_end_threads), 0, s, P, 1, 0);
-  return hipGetLastError();
+static hipError_t merge_windows(const DevPtrs& P, hipStream_t s) {
+  return in_slices(P.n_win, 256, [&](int32_t first, int32_t n) {
+    hipLaunchKernelGGL(k_merge_windows, dim3(n), dim3(256), 0, s, P, first);
+  });
 }
 
-hipError_t launch_exchange(const DevPtrs& P, hipStream_t s) {
-  hipLaunchKernelGGL(k_cycle_end, dim3(P.n_inst), dim3(P.cycle_end_threads), 0, s, P, 0, 1);
-  return hipGetLastError();
+static hipError_t cycle_end(const DevPtrs& P, int32_t merged, int32_t exchange, hipStream_t s) {
+  return in_slices(P.n_inst, P.cycle_end_threads, [&](int32_t first, int32_t n) {
+    hipLaunchKernelGGL(k_cycle_end, dim3(n), dim3(P.cycle_end_threads), 0, s, P, first, merged, exchange);
+  });
 }
+
+hipError_t launch_merge(const DevPtrs& P, hipStream_t s) {
+  const hipError_t e = merge_windows(P, s);
+  return e == hipSuccess ? cycle_end(P, 1, 0, s) : e;
+}
+
+hipError_t launch_exchange(const DevPtrs& P, hipStream_t s) { return cycle_end(P, 0, 1, s); }
 
 hipError_t launch_merge_exchange(const DevPtrs& P, hipStream_t s) {
-  hipLaunchKernelGGL(k_merge_windows, dim3(P.n_win), dim3(256), 0, s, P);
-  hipLaunchKernelGGL(k_cycle_end, dim3(P.n_inst), dim3(P.cycle_end_threads), 0, s, P, 1, 1);
-  return hipGetLastError();
+  const hipError_t e = merge_windows(P, s);
+  return e == hipSuccess ? cycle_end(P, 1, 1, s) : e;
 }
 
 // LDS representatives of an instance: all of them up to 128 KiB, and always

@@ -456,9 +456,9 @@ __device__ __forceinline__ void init_walker(const DevPtrs& P, const InstDesc& I,
   }
 }
 
-__global__ __launch_bounds__(kWave) void k_init(DevPtrs P, int32_t lat_bytes) {
+__global__ __launch_bounds__(kWave) void k_init(DevPtrs P, int32_t first, int32_t lat_bytes) {
   extern __shared__ __align__(16) uint8_t wlds[];
-  const int g = (int)blockIdx.x;
+  const int g = first + (int)blockIdx.x;
   int lo = 0, hi = P.n_inst - 1;  // the instance that owns slot g
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -471,8 +471,9 @@ __global__ __launch_bounds__(kWave) void k_init(DevPtrs P, int32_t lat_bytes) {
 }
 
 hipError_t launch_init(const DevPtrs& P, int32_t lat_bytes, hipStream_t s) {
-  hipLaunchKernelGGL(k_init, dim3(P.n_slots), dim3(kWave), (size_t)2 * lat_bytes, s, P, lat_bytes);
-  return hipGetLastError();
+  return in_slices(P.n_slots, kWave, [&](int32_t first, int32_t n) {
+    hipLaunchKernelGGL(k_init, dim3(n), dim3(kWave), (size_t)2 * lat_bytes, s, P, first, lat_bytes);
+  });
 }
 
 template <int MODEL, int PREC, bool MASKS>
@@ -627,9 +628,10 @@ hipError_t launch_sweep_wave(const DevPtrs& P, int cls, int32_t wg_offset, int32
   const Fn ising = P.prec == kFP64 ? (masks ? (Fn)k_sweep_wave<kIsing, kFP64, true> : (Fn)k_sweep_wave<kIsing, kFP64, false>)
                                    : (masks ? (Fn)k_sweep_wave<kIsing, kFP32C, true> : (Fn)k_sweep_wave<kIsing, kFP32C, false>);
   const Fn f = cls == 2 ? potts : ising;
-  hipLaunchKernelGGL(f, dim3(n_wg), dim3(kWave), (size_t)wave_lds_bytes(cls, lat_bytes, l_min, n_wg), s, P, wg_offset,
-                     lat_bytes, flips);
-  return hipGetLastError();
+  const size_t lds = (size_t)wave_lds_bytes(cls, lat_bytes, l_min, n_wg);
+  return in_slices(n_wg, kWave, [&](int32_t first, int32_t n) {
+    hipLaunchKernelGGL(f, dim3(n), dim3(kWave), lds, s, P, wg_offset + first, lat_bytes, flips);
+  });
 }
 
 }  // namespace rewl
