@@ -1069,6 +1069,7 @@ int rewl_exchange(rewl_ctx* c) {
 
 int rewl_run_cycles(rewl_ctx* c, int64_t cycles, int64_t flips, int32_t use_graph) {
   if (!c || cycles < 0 || flips < 0) return REWL_E_INVAL;
+  if (cycles == 0) return REWL_OK;
   if (!use_graph) {
     for (int64_t i = 0; i < cycles; ++i) {
       int rc = enqueue_cycle(c, flips);
