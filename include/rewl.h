@@ -244,7 +244,8 @@ int rewl_running(rewl_ctx* ctx, int32_t* n_running);
  * FP64 and normalised (Ising: sum g = 2^N; Potts: g(E_min) = q); which = 1:
  * joined, not normalised.  host_out: capacity doubles, receives nbins values
  * (-inf where no walker of the supplying window visited); joins: NULL or
- * n_windows-1 join bins.  Errors: INVAL (capacity too small), HIP. */
+ * n_windows-1 join bins.  Errors: INVAL (capacity too small), NOMEM (host
+ * memory), HIP. */
 int rewl_get_lng(rewl_ctx* ctx, int32_t instance, int32_t which, double* host_out,
                  int32_t capacity, int32_t* n_bins_out, int32_t* joins);
 
@@ -302,15 +303,15 @@ int rewl_get_piece(rewl_ctx* ctx, int32_t instance, int32_t slot, double* host_l
  * against a spread of 2e-3 between instances); error bars must come from
  * independent instances (a batch).  mean, err: capacity doubles each,
  * nbins used.  Errors: INVAL (capacity), STATE (instance not
- * finished, or m < 2), HIP. */
+ * finished, or m < 2), NOMEM (host memory), HIP. */
 int rewl_jackknife(rewl_ctx* ctx, int32_t instance, double* host_mean, double* host_err,
                    int32_t capacity, int32_t* n_bins_out);
 
 /* For callers that cannot allocate device memory (code under graph capture,
  * tight serving loops, harnesses that forbid it): rewl_jackknife with the
- * same arguments, results and errors, whose leave-one-out rows and window
- * representatives live in a device array of the library instead of the
- * workspace.  It calls no allocator.  Limit: the instance's
+ * same arguments, results and errors, whose leave-one-out rows live in a
+ * device array of the library instead of the workspace.  It calls no
+ * allocator.  Limit: the instance's
  * (m + 2) * nbins + (sum of its window sizes, rounded up to 32) doubles
  * must fit in 2^19 doubles (4 MiB), else NOMEM (every Ising instance,
  * and Potts up to L = 60, fits for any m <= 64).  Every GPU holds one such array for the life of the
@@ -322,7 +323,7 @@ int rewl_jackknife_noalloc(rewl_ctx* ctx, int32_t instance, double* host_mean, d
 
 /* Synchronises.  Canonical <E> and C_V (Sec. 5, Eqs. 7-8, k_B = 1) from the joined,
  * normalised ln g of an instance, evaluated on the GPU in FP64 for nT
- * temperatures.  Errors: INVAL, HIP. */
+ * temperatures.  Errors: INVAL, NOMEM (host memory), HIP. */
 int rewl_thermo(rewl_ctx* ctx, int32_t instance, const double* T, int32_t nT,
                 double* E_mean, double* C_v);
 

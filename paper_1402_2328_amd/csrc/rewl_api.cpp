@@ -32,7 +32,6 @@ struct Layout {
   int64_t spin_bytes = 0;
   int64_t lng_elems = 0;
   int32_t u_elems = 0;
-  int32_t rep_elems = 0;
   int32_t r_elems = 0;
   // per sweep class (Ising L <= 32, Ising L <= 64, Potts): largest lattice
   // in the sweep's LDS format (32-bit words), largest window (bins), whether
@@ -50,7 +49,7 @@ struct Layout {
   // byte offsets inside the workspace
   int64_t jk_elems = 0;  // largest (m + 2) * nbins of any instance
   size_t o_inst, o_win, o_wg, o_ist, o_wst, o_sm, o_xs, o_cfg, o_E, o_att, o_watt, o_spins,
-      o_lng, o_lhi, o_llo, o_H, o_pieces, o_U, o_rep, o_R, o_thermo, o_joins, o_jk, total;
+      o_lng, o_lhi, o_llo, o_H, o_pieces, o_U, o_R, o_thermo, o_joins, o_jk, total;
 };
 
 // Equal-size windows with overlap num/den over bins 0..nbins-1 (Fig. 1a):
@@ -178,7 +177,6 @@ int build_layout(const rewl_params* params, int32_t n, const int32_t* wlo, const
   Lo.n_slots = slot;
   Lo.spin_bytes = spin;
   Lo.lng_elems = lng;
-  Lo.rep_elems = rep;
   Lo.r_elems = rbase;
   // workspace offsets
   size_t o = 0;
@@ -211,7 +209,7 @@ int build_layout(const rewl_params* params, int32_t n, const int32_t* wlo, const
   Lo.o_H = take(sizeof(uint32_t) * lng);
   Lo.o_pieces = take(sizeof(double) * lng);
   Lo.o_U = take((size_t)Lo.u_elems);
-  Lo.o_rep = take(sizeof(double) * rep);
+  (void)take(sizeof(double) * rep);  // nothing lies here; saved states have the gap
   Lo.o_R = take(sizeof(double) * rbase);
   Lo.o_thermo = take(sizeof(double) * 3 * kMaxTemps);
   Lo.o_joins = take(sizeof(int32_t) * nw);
@@ -506,7 +504,6 @@ void fill_ptrs(rewl_ctx* c) {
   P.H = at<uint32_t>(c, L.o_H);
   P.pieces = at<double>(c, L.o_pieces);
   P.U = at<uint8_t>(c, L.o_U);
-  P.rep = at<double>(c, L.o_rep);
   P.R = at<double>(c, L.o_R);
   P.thermo = at<double>(c, L.o_thermo);
   P.joins = at<int32_t>(c, L.o_joins);
@@ -1322,17 +1319,16 @@ int rewl_jackknife_noalloc(rewl_ctx* c, int32_t instance, double* mean, double* 
   if (n_bins_out) *n_bins_out = I.nbins;
   if (capacity < I.nbins) return REWL_E_INVAL;
   if (I.m < 2) return REWL_E_STATE;
-  // representatives first, then the (m + 2) x nbins rows
+  // the documented limit, which counts the window sizes as well as the rows
   const size_t reps = (size_t)rep_count(c->lo, I);
-  const size_t rows_at = (reps + 31) / 32 * 32;  // 256-byte aligned rows
-  if (rows_at + (size_t)(I.m + 2) * (size_t)I.nbins > kScratchDoubles) return REWL_E_NOMEM;
+  if ((reps + 31) / 32 * 32 + (size_t)(I.m + 2) * (size_t)I.nbins > kScratchDoubles) return REWL_E_NOMEM;
   if (!c->scratch) return REWL_E_HIP;
   InstState st;
   int rc = d2h(c, &st, c->P.ist + instance, 1);
   if (rc) return rc;
   if (!st.done) return REWL_E_STATE;
-  double* jk = c->scratch + rows_at;
-  rc = hip_rc(launch_jackknife(c->P, I, rep_count(c->lo, I), jk, c->stream));
+  double* const jk = c->scratch;
+  rc = hip_rc(launch_jackknife(c->P, I, (int32_t)reps, jk, c->stream));
   if (!rc) rc = d2h(c, mean, jk + (int64_t)I.m * I.nbins, (size_t)I.nbins);
   if (!rc) rc = d2h(c, err, jk + (int64_t)(I.m + 1) * I.nbins, (size_t)I.nbins);
   return rc;

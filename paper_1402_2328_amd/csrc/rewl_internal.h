@@ -73,8 +73,8 @@ inline int64_t wave_max_walkers(int cls, int l_max, bool two_state, int n_wg, in
 }
 constexpr int kMaxTemps = 16384;  // rewl_thermo temperatures per call
 // Allocation-free jackknife: doubles of the per-GPU device array that holds
-// one instance's window representatives and (m + 2) x nbins leave-one-out
-// rows (4 MiB), and the device ordinals it serves.
+// one instance's (m + 2) x nbins leave-one-out rows (4 MiB), and the device
+// ordinals it serves.
 constexpr size_t kScratchDoubles = (size_t)1 << 19;
 constexpr int kMaxDevices = 64;
 
@@ -91,7 +91,7 @@ struct InstDesc {
   int32_t npad;          // bytes per stored configuration (multiple of 16)
   int32_t nbmax;         // largest window of this instance, bins
   int32_t r_base;        // offset of this instance's joined ln g in the R / out arrays
-  int32_t rep_base;      // offset of its window representatives in rep[]
+  int32_t rep_base;      // window bins of the instances before (read by no kernel, part of saved states)
   int64_t spin_base;     // byte offset of configuration 0 of this instance
   double lnf_final;
   uint32_t key0, key1;
@@ -102,7 +102,7 @@ struct WinDesc {
   int32_t lo, hi, nb, inst;
   int64_t lng_base;      // element offset of walker k = 0, bin lo of this window
   int32_t u_base;        // offset of the visited mask
-  int32_t rep_off;       // offset of the representative within rep[]
+  int32_t rep_off;       // window bins of the windows before, over the batch
 };
 
 struct WinState {
@@ -144,7 +144,6 @@ struct DevPtrs {
   uint32_t* H;               // histograms, same indexing as ln g
   double* pieces;            // ln g of every walker just before its window froze
   uint8_t* U;                // visited-union masks per window
-  double* rep;               // window representatives for joining
   double* R;                 // joined ln g per instance
   double* thermo;            // 3 kMaxTemps: T, then from kMaxTemps on nT <E> and nT C_V
   int32_t* joins;            // [windows] join bin of (w-1, w)

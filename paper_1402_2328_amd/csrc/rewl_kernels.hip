@@ -334,7 +334,6 @@ constexpr int kChunkWindows = 256;
 
 struct JoinShared {
   double red[kJoinThreads / 64];
-  int64_t redi[kJoinThreads / 64];
   double a[kChunkWindows], b[kChunkWindows], shift[kChunkWindows];
   int best[kChunkWindows];
 };
@@ -535,9 +534,8 @@ __global__ __launch_bounds__(64) void k_jackknife_rows(DevPtrs P, int32_t instan
 }
 
 // Device memory of the allocation-free jackknife (rewl_jackknife_noalloc):
-// the window representatives and leave-one-out rows of one instance.  Every
-// GPU the library runs on holds its own copy until the process ends; calls
-// that overlap on one GPU share it.
+// the leave-one-out rows of one instance.  Every GPU the library runs on holds
+// its own copy until the process ends; calls that overlap on one GPU share it.
 static __device__ __align__(256) double scratch[kScratchDoubles];
 
 hipError_t scratch_address(double** out) {
