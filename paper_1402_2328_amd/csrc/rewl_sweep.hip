@@ -40,6 +40,7 @@
 // depend on the walker-to-lane mapping, page size or launch shape.
 #include <math.h>
 
+#include <mutex>
 #include <type_traits>
 
 #include "rewl_device.h"
@@ -831,6 +832,16 @@ FusedFn fused_fn(int prec, bool prod, bool s64) {
 }  // namespace
 
 hipError_t prepare_sweep_lds(size_t lds_bytes) {
+  // once per device: for 48 kernels it is a tenth of the time that a context
+  // of a few walkers takes to set up (80 us)
+  static std::mutex mu;
+  static bool done[kMaxDevices] = {};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+  std::lock_guard<std::mutex> lock(mu);
+  if (done[dev]) return hipSuccess;
   for (int i = 0; i < 8; ++i) {
     const int prec = i & 1 ? kFP32C : kFP64;
     const bool prod = (i & 2) != 0, s64 = (i & 4) != 0;
@@ -839,13 +850,14 @@ hipError_t prepare_sweep_lds(size_t lds_bytes) {
                          (const void*)sweep_fn(prec, prod, s64, 2, false), (const void*)fused_fn(prec, prod, s64)};
     for (const void* f : fns) {
       hipFuncAttributes at;
-      hipError_t e = hipFuncGetAttributes(&at, f);
+      e = hipFuncGetAttributes(&at, f);
       if (e != hipSuccess) return e;
       if (at.sharedSizeBytes != 0) return hipErrorInvalidValue;  // dynamic LDS must start at 0
       e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
       if (e != hipSuccess) return e;
     }
   }
+  done[dev] = true;
   return hipSuccess;
 }
 
