@@ -31,39 +31,39 @@ constexpr int kSimds = 1024;
 //
 // Up to a workgroup per compute unit, each with its producer, lanes are at
 // their best, and the better the smaller the lattice.  8 walkers per window:
-//   Ising, walkers  4096      5120      6144      7168
-//     L =  8     302, 300  304, 349  303, 403  304, 477
-//     L = 16     320, 268  319, 312  319, 357  318, 410
-//     L = 24     360, 240  360, 292  360, 335  363, 383
-//     L = 32     363, 228  363, 272  365, 311  366, 358
-//     L = 48     495, 222  499, 256  499, 291  503, 335
-//   Potts, walkers  4096      5120      5632
-//     q = 10, L =  8  398, 355  392, 417
-//     q = 10, L = 12  397, 334  396, 389  403, 459
-//     q =  3, L = 16  406, 300  409, 352  424, 413
-//     q = 10, L = 20  404, 283  404, 367
-// (two-float: Ising L = 8 329, 339 at 4096; L = 32 395, 410 at 7168; q = 10
-// Potts L = 20 411, 402 at 5120).  With more workgroups than that there is no
+//   Ising, walkers  3584      4608      5632      6656      7168
+//     L =  8     296, 296  294, 349  293, 396  292, 453  291, 481
+//     L = 16     307, 265  308, 311  309, 354  311, 402  311, 409
+//     L = 24     352, 240  354, 292  356, 334  356, 383  357, 389
+//     L = 32     363, 227  365, 272  367, 312  368, 352  367, 359
+//     L = 48     485, 220  485, 257  488, 291  492, 331  495, 339
+//   Potts, walkers    4096      4608      5632
+//     q = 10, L =  8  400, 354  397, 416  393, 480
+//     q = 10, L = 12  397, 335  397, 388  397, 406
+//     q =  3, L = 16  408, 299  403, 351  407, 408
+//     q = 10, L = 20  404, 284  403, 364  406, 417
+// (two-float: Ising L = 8 315, 338 at 3584; L = 32 394, 400 at 6656; q = 10
+// Potts L = 20 412, 404 at 5120).  With more workgroups than that there is no
 // producer, and up to one workgroup per SIMD wavefronts win throughout: 16
-// walkers per instance, Ising L = 8 505, 477 at 7168, L = 24 613, 383; q = 10
-// Potts L = 8 627, 476 at 5632.
+// walkers per instance, Ising L = 8 506, 473 at 7168, L = 24 626, 383; q = 10
+// Potts L = 8 628, 480 at 5632.
 //
 // Where the lane form's workgroups outnumber the SIMDs, their time grows with
 // their number as well, and the limit becomes one of walkers per workgroup: 7
-// (Potts 5.5).  16380 walkers, Ising of 7 per instance, L = 16 1211, 802; q =
-// 10 Potts L = 20 of 5 2605, 907.  Beyond five workgroups per SIMD the lane
+// (Potts 5.5).  16380 walkers, Ising of 7 per instance, L = 16 1200, 810; q =
+// 10 Potts L = 20 of 5 2631, 917.  Beyond five workgroups per SIMD the lane
 // form's turns on a compute unit are all full ones, and small lattices of two
 // states, whose lanes are quick, are better off with fewer walkers per
-// workgroup.  40960 (65536) walkers: Ising L = 8 of 4 2317, 2189 (3354, 3442),
-// of 5 1974, 2139 (2795, 3344); L = 12 of 6 2006, 2053 (2791, 3212); L = 16 of
-// 6 2144, 1955 (3013, 3005), of 7 1899, 1944 (2715, 3006); L = 20 of 7 2202,
-// 1884 (3117, 2961); q = 2 Potts L = 8 of 5 2441, 2532 (3531, 3908); but L = 32
-// of 7 2548, 1713 (3799, 2712), q = 10 Potts L = 6 of 5 3007, 2319 (4512,
-// 3557).
+// workgroup.  40960 (65536) walkers: Ising L = 8 of 4 2274, 2218 (3391, 3453),
+// of 5 1929, 2203 (2785, 3373); L = 12 of 6 2014, 2098 (2769, 3247); L = 16 of
+// 6 2132, 1974 (2979, 3047), of 7 1859, 1935 (2690, 3032); L = 20 of 7 2201,
+// 1898 (3132, 2950); q = 2 Potts L = 8 of 5 2436, 2509 (3524, 3917); but L = 32
+// of 7 2558, 1728 (3830, 2721), q = 10 Potts L = 6 of 5 3047, 2345 (4512,
+// 3638).
 inline int64_t wave_max_walkers(int cls, int l_max, bool two_state, int n_wg, int n_cu) {
   const int64_t most = cls == 2 ? 5632 : 7168;
   if (n_wg <= n_cu) {
-    const int64_t alone = 3072 + 128 * (int64_t)l_max;
+    const int64_t alone = cls == 2 ? 3072 + 128 * (int64_t)l_max : 2304 + 160 * (int64_t)l_max;
     return alone < most ? alone : most;
   }
   if (n_wg <= kSimds) return most;
