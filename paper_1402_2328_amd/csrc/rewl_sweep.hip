@@ -30,11 +30,11 @@
 // three rows next to each other (both words of ln g, then H), so one address
 // serves all three.
 // What bounds it on a full chip is instruction issue, and the clock that the
-// power of the wide multiplies and LDS accesses leaves: 107 vector
+// power of the wide multiplies and LDS accesses leaves: 109 vector
 // instructions per wave-attempt on 1024 Ising L = 32 instances (122 with ln
 // g and H as arrays of their own, bins counted from the range's lowest and
 // every Philox round in full), 6.2 against 6.9 ms per sweep of 10^4 attempts
-// with the wavefronts placed alike (5.75 with H as counts); 136 against 167 on
+// with the wavefronts placed alike, 5.80 with H as counts; 136 against 167 on
 // q = 10 Potts L = 20 in two-float FP32, 4.85 against 6.3 ms.  Random numbers come
 // from Philox4x32-10 keyed by (walker slot, attempt), so results do not
 // depend on the walker-to-lane mapping, page size or launch shape.
@@ -864,12 +864,12 @@ hipError_t prepare_sweep_lds(size_t lds_bytes) {
 // One wavefront per compute unit that ends at once.  The wavefronts of a
 // launch are dealt to the four SIMDs of a CU from where the launch before
 // left off.  After a kernel of larger workgroups (the merge) that is not the
-// same place in every CU, and 7 % of the SIMDs got one wavefront of the sweep
-// too many and as many one too few (hardware ids read back: of 1024 SIMDs
-// with two wavefronts each, 68 had three and 68 one; none after this
+// same place in every CU, and 7 to 10 % of the SIMDs got one wavefront of the
+// sweep too many and as many one too few (hardware ids read back: of 1024
+// SIMDs with two wavefronts each, 98 had three and 98 one; none after this
 // launch).  The sweep waits for the fullest SIMD: 1024 Ising L = 32 instances
-// took 7.41 against 6.56 ms, 128 q = 10 Potts L = 20 instances 7.03 against
-// 5.80 ms; this launch takes 3 us.
+// took 7.15 against 5.85 ms, 128 q = 10 Potts L = 20 instances in two-float
+// FP32 6.44 against 5.11 ms; this launch takes 3 us.
 __global__ __launch_bounds__(kSweepWave) void k_even_out() {}
 
 hipError_t launch_even_out(int32_t n_cu, hipStream_t s) {
