@@ -128,8 +128,8 @@ int rewl_run_sweeps(rewl_ctx* ctx, int64_t flips);
  * with one lane per walker, in the shape below, or with one wavefront per
  * walker: with walkers_per_group = 1 and the other arguments at their
  * defaults (0, -1, -1), and by default, all four left so, where the batch has
- * few walkers (3584 on lattices of L = 8 up to 7168 from L = 31 on, for Potts
- * 4096 up to 5632 from L = 20 on; in batches of many instances up to 7 and 5.5
+ * few walkers (4096 on lattices of L = 8 up to 7168 from L = 32 on, for Potts up
+ * to 5632 from L = 20 on; in batches of many instances up to 7 and 5.5
  * per instance, on small lattices fewer).  A fused launch (rewl_set_batching)
  * always takes the lane form.  For lanes: in class cls (-1:
  * all classes) keep page_bins ln g bins of each walker's window in LDS (the

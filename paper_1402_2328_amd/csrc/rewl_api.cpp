@@ -594,7 +594,7 @@ hipError_t enqueue_sweeps(rewl_ctx* c, int64_t flips) {
       if (f <= 0) continue;
       if (cp.wave) e = launch_sweep_wave(c->P, cls, cp.offset, cp.count, wave_lat_bytes(c->lo, cls), c->lo.l_min[cls], f, s);
       else e = launch_sweep_class(c->P, cls, sh, cp.count, f, cp.lds_bytes, cp.prod != 0,
-                                  h_in_page(cls, cp.P, c->lo.lng_elems), s);
+                                  h_in_page(cls, cp.count, c->lo.lng_elems), s);
     }
   }
   if (fork) {

@@ -27,43 +27,44 @@ constexpr int kSimds = 1024;
 // (1024 walkers), from there on the time grows with their number, and faster
 // on small lattices, where more of 64 attempts touch each other's sites.  A
 // lane takes as long however many there are, until the workgroups wait for
-// one another.  ns per attempt below are lanes, wavefronts.
+// one another.  ns per attempt below are lanes, wavefronts, of batches that
+// have run for 30000 attempts per walker.
 //
 // Up to a workgroup per compute unit, each with its producer, lanes are at
 // their best, and the better the smaller the lattice.  8 walkers per window:
-//   Ising, walkers  3584      4608      5632      6656      7168
-//     L =  8     296, 296  294, 349  293, 396  292, 453  291, 481
-//     L = 16     307, 265  308, 311  309, 354  311, 402  311, 409
-//     L = 24     352, 240  354, 292  356, 334  356, 383  357, 389
-//     L = 32     363, 227  365, 272  367, 312  368, 352  367, 359
-//     L = 48     485, 220  485, 257  488, 291  492, 331  495, 339
-//   Potts, walkers    4096      4608      5632
-//     q = 10, L =  8  400, 354  397, 416  393, 480
-//     q = 10, L = 12  397, 335  397, 388  397, 406
-//     q =  3, L = 16  408, 299  403, 351  407, 408
-//     q = 10, L = 20  404, 284  403, 364  406, 417
-// (two-float: Ising L = 8 315, 338 at 3584; L = 32 394, 400 at 6656; q = 10
-// Potts L = 20 412, 404 at 5120).  With more workgroups than that there is no
-// producer, and up to one workgroup per SIMD wavefronts win throughout: 16
-// walkers per instance, Ising L = 8 506, 473 at 7168, L = 24 626, 383; q = 10
-// Potts L = 8 628, 480 at 5632.
+//   Ising, walkers  4096      4608      5120      5632      6144      7168
+//     L =  8     305, 302  304, 353  305, 351  304, 398  306, 405  306, 470
+//     L = 16     325, 268  326, 312  325, 314  327, 356  326, 355  327, 410
+//     L = 24     377, 242  375, 292  378, 293  377, 334  379, 334  377, 384
+//     L = 32     377, 230  380, 270  374, 274  377, 310  377, 312  382, 357
+//     L = 48     514, 223  516, 257  513, 259  515, 295  514, 292  519, 340
+//   Potts
+//     q = 10, L =  8  400, 354  390, 411  391, 416  393, 480
+//     q = 10, L = 12  400, 333  400, 388  400, 390  400, 431
+//     q =  3, L = 16  432, 302  432, 349  435, 352  434, 406
+//     q = 10, L = 20  416, 284  415, 368  416, 371  416, 419
+// (two-float: Ising L = 8 330, 338 at 4096; L = 32 409, 406 at 7168; q = 10
+// Potts L = 20 423, 405 at 5120, 425, 458 at 5632).  With more workgroups than
+// that there is no producer, and up to one workgroup per SIMD wavefronts win
+// throughout: 16 walkers per instance, Ising L = 8 508, 475 at 7168, L = 24
+// 621, 389; q = 10 Potts L = 8 632, 480 at 5632.
 //
 // Where the lane form's workgroups outnumber the SIMDs, their time grows with
 // their number as well, and the limit becomes one of walkers per workgroup: 7
-// (Potts 5.5).  16380 walkers, Ising of 7 per instance, L = 16 1200, 810; q =
-// 10 Potts L = 20 of 5 2631, 917.  Beyond five workgroups per SIMD the lane
+// (Potts 5.5).  16380 walkers, Ising of 7 per instance, L = 16 1222, 816; q =
+// 10 Potts L = 20 of 5 2609, 891.  Beyond five workgroups per SIMD the lane
 // form's turns on a compute unit are all full ones, and small lattices of two
 // states, whose lanes are quick, are better off with fewer walkers per
-// workgroup.  40960 (65536) walkers: Ising L = 8 of 4 2274, 2218 (3391, 3453),
-// of 5 1929, 2203 (2785, 3373); L = 12 of 6 2014, 2098 (2769, 3247); L = 16 of
-// 6 2132, 1974 (2979, 3047), of 7 1859, 1935 (2690, 3032); L = 20 of 7 2201,
-// 1898 (3132, 2950); q = 2 Potts L = 8 of 5 2436, 2509 (3524, 3917); but L = 32
-// of 7 2558, 1728 (3830, 2721), q = 10 Potts L = 6 of 5 3047, 2345 (4512,
-// 3638).
+// workgroup.  40960 (65536) walkers: Ising L = 8 of 4 2341, 2243 (3355, 3452),
+// of 5 1965, 2183 (2805, 3338); L = 12 of 6 1939, 2008 (2769, 3093); L = 16 of
+// 6 2077, 1930 (2921, 2932), of 7 1884, 1879 (2673, 2912); L = 20 of 7 2182,
+// 1866 (3073, 2919); q = 2 Potts L = 8 of 5 2406, 2540 (3514, 3926); but L = 32
+// of 7 2590, 1696 (3723, 2629), q = 10 Potts L = 6 of 5 3063, 2278 (4507,
+// 3505).
 inline int64_t wave_max_walkers(int cls, int l_max, bool two_state, int n_wg, int n_cu) {
   const int64_t most = cls == 2 ? 5632 : 7168;
   if (n_wg <= n_cu) {
-    const int64_t alone = cls == 2 ? 3072 + 128 * (int64_t)l_max : 2304 + 160 * (int64_t)l_max;
+    const int64_t alone = 3072 + 128 * (int64_t)l_max;
     return alone < most ? alone : most;
   }
   if (n_wg <= kSimds) return most;
@@ -194,32 +195,34 @@ hipError_t launch_init(const DevPtrs& P, int32_t lat_bytes, hipStream_t s);
 // One sweep kernel class: 0 = Ising L <= 32, 1 = Ising 32 < L <= 64,
 // 2 = Potts; n_wg workgroups starting at sh.wg_offset of the table;
 // producer: a second wavefront per workgroup computes the random numbers;
-// counts: h_in_page.
+// all_counts: h_in_page (else kRotationLoop for class 0, kNone for the others).
 hipError_t launch_sweep_class(const DevPtrs& P, int cls, SweepShape sh, int32_t n_wg, int64_t flips,
-                              size_t lds_bytes, bool producer, bool counts, hipStream_t s);
-// Whether the page of a class (pages of `page` bins; not in a fused launch)
-// holds whole counts of H, loaded and stored with their ln g, or increments,
-// added to H by an atomic when a bin leaves.  lng_elems: walkers' bins of the
-// batch.  The load is one more per entering bin, the atomic takes longer to
-// leave and fetches its line.  Counts win where pages shift seldom, and where
-// ln g and H (12 bytes per bin) do not stay in the 256 MB last-level cache.  ns
-// per attempt, increments against counts:
-//   page 32 to 128: Ising L = 8, 32768 walkers 333, 318; L = 16, 65536 516,
-//     486, two-float 569, 542; L = 24, 65536 634, 611, two-float 16384 408,
-//     396; L = 32, 65536 662, 628; L = 48, 16384 514, 503; L = 64, 32768 717,
-//     707; the worst L = 64, 8192 620, 627.
-//   page 16, 8 walkers per window, up to 200 MB: L = 8 (60 MB) 1245, 1271; L =
-//     12 (65 MB) 603, 608; L = 16 (111 MB) 697, 708, two-float (148 MB) 860,
-//     877; L = 40 (76 MB) 868, 887; L = 28 (196 MB) 986, 993.
-//   page 16, beyond: L = 20 (230 MB) 939, 909; L = 16 (296 MB) 1831, 1744, (591
-//     MB) 3603, 3082; L = 24 (331 MB) 1080, 1026; L = 32 (341 MB) 1271, 1230,
-//     with 16 walkers in 4 windows (922 MB) 1623, 1424; L = 48 (1037 MB) 1154,
-//     1094; the worst L = 40 (266 MB) 877, 890.
-// Potts pages shift most often (four bins a move): q = 10 L = 20, 65536 684,
-// 695, two-float 131072 1508, 1540; L = 32 (340 MB) 1604, 1619.  The fused
-// launch of 64 uneven instances takes 0.5 % more with counts.
-inline bool h_in_page(int cls, int page, int64_t lng_elems) {
-  return cls != 2 && (page > 16 || 12 * lng_elems > (int64_t)192 << 20);
+                              size_t lds_bytes, bool producer, bool all_counts, hipStream_t s);
+// Which lane loops keep whole counts of H in the page, loaded and stored with
+// their ln g; the others keep increments, added to H by an atomic when a bin
+// leaves.  The load is one more per entering bin; the atomic takes longer to
+// leave and fetches its line.  ns per attempt, increments against counts
+// (batches that have run for 30000 attempts per walker, FP64, two-float in
+// brackets):
+//   the rotation loop (Ising L = 32) gains at every size and page: 8192 walkers
+//     384, 379 (410, 405), 24576 443, 431 (476, 470), 65536 531, 507 (555,
+//     549), 131072 1321, 1227 (1430, 1368);
+//   the other Ising loops gain where the traffic binds, with a workgroup per
+//     SIMD and more ln g and H (12 bytes per bin) than stay in the 256 MB
+//     last-level cache: L = 24, 331 MB 1053, 988 (1178, 1135); L = 31, 1135 MB
+//     1215, 1118 (1326, 1229); L = 36, 431 MB 1992, 1939 (2082, 1981); L = 50,
+//     415 MB 809, 802 (855, 820); L = 64, 679 MB 1493, 1454 (1533, 1478);
+//     below that they lose or gain little: L = 16, 148 MB 717, 727 (767, 815);
+//     L = 24, 248 MB 853, 854 (888, 901); L = 40, 266 MB 655, 667 (704, 683);
+//     L = 31 with 768 workgroups, 567 MB 536, 539 (569, 577); L = 20, 8192
+//     walkers 343, 340 (390, 363), 16384 348, 356 (393, 378);
+//   Potts, whose pages shift most often, loses (L = 20, q = 10, 65536 walkers
+//     684, 695; two-float, 131072 1508, 1540; L = 32, 340 MB 1604, 1619), and
+//     so does the fused launch of 64 uneven instances (0.5 %).
+enum class HCounts : int32_t { kNone, kRotationLoop, kAllLoops };
+// kAllLoops for a class of n_wg workgroups in a batch of lng_elems bins.
+inline bool h_in_page(int cls, int n_wg, int64_t lng_elems) {
+  return cls != 2 && n_wg >= kSimds && 12 * lng_elems > (int64_t)288 << 20;
 }
 // Deals the wavefronts of the next launch evenly to the SIMDs of every
 // compute unit; before a sweep of at least as many workgroups as there are.

@@ -112,8 +112,9 @@ __device__ __forceinline__ int potts_de(int a, int b, int c, int d, int s0, int 
 // rows next to each other are reached by offsets in the instruction (one
 // ds_read2st64_b32 for both words of an FP64 ln g).
 // The sweep of workgroup-table entry wgi, with the launch's dynamic LDS.
-// COUNTS: whole counts of H in the page (h_in_page), not increments.
-template <int MODEL, int PREC, int ROWW, bool PROD, bool S64, bool COUNTS>
+// COUNTS: loops that keep whole counts of H in the page, not increments
+// (h_in_page).
+template <int MODEL, int PREC, int ROWW, bool PROD, bool S64, HCounts COUNTS>
 __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& sh, int64_t flips, int wgi,
                                            unsigned char* lds) {
   const WgDesc wg = P.wg[wgi];
@@ -276,9 +277,10 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   };
   auto getf = [&](int off, int row) { return __uint_as_float(word(off, row)); };
   auto putf = [&](int off, int row, float v) { word(off, row) = __float_as_uint(v); };
-  // H in the page: a bin's whole count, loaded with its ln g and stored back
-  // (COUNTS), or the increments since it entered, added to device memory by an
-  // atomic when it leaves.  h_in_page says which and why.
+  // H in the page: a bin's whole count, loaded with its ln g and stored back,
+  // or the increments since it entered, added to device memory by an atomic
+  // when it leaves.  h_in_page says which and why.
+  const bool h_load = COUNTS == HCounts::kAllLoops || (COUNTS == HCounts::kRotationLoop && L == 32);
   const int cnt = nb < PG ? nb : PG;
   const int hi_pm = nb - cnt;  // highest page start; 0: the window is in LDS entirely
   int m_pm = __builtin_amdgcn_readfirstlane(M - PM);
@@ -296,7 +298,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       putf(j, 0, *at_off(lhw, e << 2));
       putf(j, 1, *at_off(llw, e << 2));
     }
-    word(j, 2) = COUNTS ? *at_off(Hw, e << 2) : 0u;
+    word(j, 2) = h_load ? *at_off(Hw, e << 2) : 0u;
   }
   constexpr int DMAX = (MODEL == kPotts) ? 4 : 2;
   // Bins in flight after a page shift of pend_n bins: slot pend_row[i] holds
@@ -320,7 +322,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   // Settles the bins in flight: the leaving bins are written back (ln g
   // stored, H counts stored or increments added in device memory) and the
   // entering bins take their slots.
-  auto settle = [&]() {
+  auto settle = [&](auto counts) {
     // All lanes' loads have arrived here (vmcnt 0).  Waited for inside the
     // branch only, the compiler has to take them as pending after it, and
     // may wait again, then for the stores below as well, where the next
@@ -336,14 +338,14 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
           putf(j, 0, pend_hi[i]);
           putf(j, 1, pend_lo[i]);
         }
-        word(j, 2) = COUNTS ? pend_h[i] : 0u;
+        word(j, 2) = counts ? pend_h[i] : 0u;
         if (PREC == kFP64) {
           *at_off(lngw, (pend_e << 3) + 8u * i) = ev_l[i];
         } else {
           *at_off(lhw, (pend_e << 2) + 4u * i) = ev_hi[i];
           *at_off(llw, (pend_e << 2) + 4u * i) = ev_lo[i];
         }
-        if (COUNTS) *at_off(Hw, (pend_e << 2) + 4u * i) = ev_h[i];
+        if (counts) *at_off(Hw, (pend_e << 2) + 4u * i) = ev_h[i];
         else atomicAdd(at_off(Hw, (pend_e << 2) + 4u * i), ev_h[i]);
       }
     }
@@ -374,6 +376,8 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
                       uint32_t fm, int site, auto lkt, auto nbt) -> bool {
     constexpr bool NB = decltype(nbt)::value;
     constexpr bool TAB = decltype(lkt)::value == 3;
+    constexpr bool H_LOAD = COUNTS == HCounts::kAllLoops ||
+                            (COUNTS == HCounts::kRotationLoop && decltype(lkt)::value == 2);
     const bool inwin = (uint32_t)bn < (uint32_t)nb;
     const int jn = pslot(bn);
     bool acc;
@@ -444,7 +448,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
       lds_add(jcur + (S64 ? 512 : 2 * S4), 1u);
     }
     // settle the bins of the last shift, then follow the walker
-    settle();
+    settle(std::bool_constant<H_LOAD>{});
     // bin + M - PM is the lowest page start that still covers bin + M,
     // bin - M the highest that covers bin - M (PM >= 2M); the start then
     // stays inside [0, hi_pm] (0 for a window that is in LDS entirely, which
@@ -477,7 +481,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
             ev_hi[i] = getf(j, 0);
             ev_lo[i] = getf(j, 1);
           }
-          if (COUNTS) pend_h[i] = *at_off(Hw, (en << 2) + 4u * i);
+          if (H_LOAD) pend_h[i] = *at_off(Hw, (en << 2) + 4u * i);
           ev_h[i] = word(j, 2);
           pend_row[i] = j;
         }
@@ -735,7 +739,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
   }
 
   // ---- stage out ----
-  settle();
+  settle(h_load);
   if (!frozen) {
     for (int i = 0; i < cnt; ++i) {
       const int b = base + i;
@@ -748,7 +752,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
         *at_off(llw, e << 2) = getf(j, 1);
       }
       const uint32_t h = word(j, 2);
-      if (COUNTS) *at_off(Hw, e << 2) = h;
+      if (h_load) *at_off(Hw, e << 2) = h;
       else if (h) atomicAdd(at_off(Hw, e << 2), h);
     }
   }
@@ -777,7 +781,7 @@ __device__ __forceinline__ void sweep_body(const DevPtrs& P, const SweepShape& s
 
 // One kernel class per launch: the class's workgroups are entries
 // [sh.wg_offset, sh.wg_offset + gridDim.x) of the table.
-template <int MODEL, int PREC, int ROWW, bool PROD, bool S64, bool COUNTS>
+template <int MODEL, int PREC, int ROWW, bool PROD, bool S64, HCounts COUNTS>
 __global__ __launch_bounds__(PROD ? 2 * kSweepWave : kSweepWave) void k_sweep(DevPtrs P, SweepShape sh,
                                                                                 int64_t flips) {
   extern __shared__ __align__(16) unsigned char lds[];
@@ -796,9 +800,9 @@ __global__ __launch_bounds__(PROD ? 2 * kSweepWave : kSweepWave) void k_sweep_fu
   extern __shared__ __align__(16) unsigned char lds[];
   const int wgi = (int)blockIdx.x;
   const int cls = P.wg[wgi].cls;
-  if (cls == 0) sweep_body<kIsing, PREC, 1, PROD, S64, false>(P, s0, flips, wgi, lds);
-  else if (cls == 1) sweep_body<kIsing, PREC, 2, PROD, S64, false>(P, s1, flips, wgi, lds);
-  else sweep_body<kPotts, PREC, 0, PROD, S64, false>(P, s2, flips, wgi, lds);
+  if (cls == 0) sweep_body<kIsing, PREC, 1, PROD, S64, HCounts::kNone>(P, s0, flips, wgi, lds);
+  else if (cls == 1) sweep_body<kIsing, PREC, 2, PROD, S64, HCounts::kNone>(P, s1, flips, wgi, lds);
+  else sweep_body<kPotts, PREC, 0, PROD, S64, HCounts::kNone>(P, s2, flips, wgi, lds);
 }
 
 namespace {
@@ -807,18 +811,19 @@ using SweepFn = void (*)(DevPtrs, SweepShape, int64_t);
 using FusedFn = void (*)(DevPtrs, SweepShape, SweepShape, SweepShape, int64_t);
 
 template <int PREC, bool PROD, bool S64>
-SweepFn sweep_fn(int cls, bool counts) {
-  if (cls == 0) return counts ? k_sweep<kIsing, PREC, 1, PROD, S64, true> : k_sweep<kIsing, PREC, 1, PROD, S64, false>;
-  if (cls == 1) return counts ? k_sweep<kIsing, PREC, 2, PROD, S64, true> : k_sweep<kIsing, PREC, 2, PROD, S64, false>;
-  return k_sweep<kPotts, PREC, 0, PROD, S64, false>;
+SweepFn sweep_fn(int cls, bool all) {
+  constexpr HCounts kAll = HCounts::kAllLoops, kRot = HCounts::kRotationLoop, kNone = HCounts::kNone;
+  if (cls == 0) return all ? k_sweep<kIsing, PREC, 1, PROD, S64, kAll> : k_sweep<kIsing, PREC, 1, PROD, S64, kRot>;
+  if (cls == 1) return all ? k_sweep<kIsing, PREC, 2, PROD, S64, kAll> : k_sweep<kIsing, PREC, 2, PROD, S64, kNone>;
+  return k_sweep<kPotts, PREC, 0, PROD, S64, kNone>;
 }
 
-SweepFn sweep_fn(int prec, bool prod, bool s64, int cls, bool counts) {
+SweepFn sweep_fn(int prec, bool prod, bool s64, int cls, bool all) {
   if (prec == kFP64)
-    return prod ? (s64 ? sweep_fn<kFP64, true, true>(cls, counts) : sweep_fn<kFP64, true, false>(cls, counts))
-                : (s64 ? sweep_fn<kFP64, false, true>(cls, counts) : sweep_fn<kFP64, false, false>(cls, counts));
-  return prod ? (s64 ? sweep_fn<kFP32C, true, true>(cls, counts) : sweep_fn<kFP32C, true, false>(cls, counts))
-              : (s64 ? sweep_fn<kFP32C, false, true>(cls, counts) : sweep_fn<kFP32C, false, false>(cls, counts));
+    return prod ? (s64 ? sweep_fn<kFP64, true, true>(cls, all) : sweep_fn<kFP64, true, false>(cls, all))
+                : (s64 ? sweep_fn<kFP64, false, true>(cls, all) : sweep_fn<kFP64, false, false>(cls, all));
+  return prod ? (s64 ? sweep_fn<kFP32C, true, true>(cls, all) : sweep_fn<kFP32C, true, false>(cls, all))
+              : (s64 ? sweep_fn<kFP32C, false, true>(cls, all) : sweep_fn<kFP32C, false, false>(cls, all));
 }
 
 FusedFn fused_fn(int prec, bool prod, bool s64) {
@@ -878,9 +883,9 @@ hipError_t launch_even_out(int32_t n_cu, hipStream_t s) {
 }
 
 hipError_t launch_sweep_class(const DevPtrs& P, int cls, SweepShape sh, int32_t n_wg, int64_t flips,
-                              size_t lds_bytes, bool producer, bool counts, hipStream_t s) {
+                              size_t lds_bytes, bool producer, bool all_counts, hipStream_t s) {
   if (n_wg <= 0) return hipSuccess;
-  const SweepFn f = sweep_fn(P.prec, producer, sh.stride == kSweepWave, cls, counts);
+  const SweepFn f = sweep_fn(P.prec, producer, sh.stride == kSweepWave, cls, all_counts);
   hipLaunchKernelGGL(f, dim3(n_wg), dim3(producer ? 2 * kSweepWave : kSweepWave), lds_bytes, s, P, sh, flips);
   return hipGetLastError();
 }

@@ -12,9 +12,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("model,L,q,h,m,n,wave", [
-    # 64 walkers, one workgroup, per instance: up to 2304 + 160 L walkers, Potts 3072 + 128 L
-    (WL.ISING, 8, 2, 4, 16, 56, True), (WL.ISING, 8, 2, 4, 16, 57, False), (WL.ISING, 8, 2, 4, 16, 112, False),
-    (WL.ISING, 16, 2, 4, 16, 76, True), (WL.ISING, 16, 2, 4, 16, 77, False),
+    # 64 walkers, one workgroup, per instance: up to 3072 + 128 L walkers
+    (WL.ISING, 8, 2, 4, 16, 64, True), (WL.ISING, 8, 2, 4, 16, 65, False), (WL.ISING, 8, 2, 4, 16, 112, False),
+    (WL.ISING, 16, 2, 4, 16, 80, True), (WL.ISING, 16, 2, 4, 16, 81, False),
     (WL.ISING, 32, 2, 4, 16, 112, True), (WL.ISING, 32, 2, 4, 16, 113, False),
     (WL.ISING, 48, 2, 4, 16, 112, True), (WL.ISING, 48, 2, 4, 16, 113, False),
     (WL.POTTS, 8, 10, 4, 16, 64, True), (WL.POTTS, 8, 10, 4, 16, 65, False),
