@@ -220,7 +220,7 @@ int build_layout(const rewl_params* params, int32_t n, const int32_t* wlo, const
 
 // LDS is given out in pieces of this size (gfx950).  Ising L = 20 with 49152
 // walkers, three workgroups per compute unit: page 64, 54272 bytes each, of
-// which three would fit without it, 784 ns per attempt against 460 with page
+// which three would fit without it, 832 ns per attempt against 456 with page
 // 32.
 constexpr int kLdsGrain = 1280;
 // Two wavefronts per SIMD: together they have an instruction in issue on every
@@ -238,17 +238,17 @@ constexpr int kMaxShare = 8;
 // take turns on a compute unit, as few turns as the smallest page allows with
 // at most kMaxShare of them at a time, and P is the largest page that still
 // lets as many share it as these turns need: a larger page shifts less often,
-// a turn more costs far more than that.  ns per attempt of a fresh batch with
-// 16384 walkers (one workgroup per compute unit): Ising L = 32 page 128 383,
-// 32 440; L = 64 page 64 644, 32 667, and 1260 with 128, of which 63 walkers
-// fit; q = 10 Potts L = 20 page 128 402, 32 502; with 24576 (two), page 64
-// against 32: 413, 460; 689, 723; 460, 510.  Ising L = 32 with 98304 (six),
-// page 16 in one turn against 32 in two: 1020, 1262; with 131072 (eight) 1211,
-// 1329; L = 64 with 65536 (four), two turns of two with page 64 against three
-// and one with 16: 2058, 2208.  Workgroups are counted as they are made, of
-// one instance each: 4096 instances of 4 walkers (L = 8, sixteen per compute
-// unit) in lanes with page 16 1213, with 64, the page of a lone workgroup,
-// 2750.
+// a turn more costs far more than that.  ns per attempt (after 30000 attempts
+// per walker) with 16384 walkers (one workgroup per compute unit): Ising L = 32
+// page 128 394, 32 436; L = 64 page 64 645, 32 655, and 1273 with 128, of which
+// 63 walkers fit; q = 10 Potts L = 20 page 128 401, 32 501; with 24576 (two),
+// page 64 against 32: 443, 470; 710, 724; 459, 512.  Ising L = 32 with 98304
+// (six), page 16 in one turn against 32 in two: 1017, 1320; with 131072 (eight)
+// 1224, 1396; L = 64 with 65536 (four), two turns of two with page 64 against
+// three and one with 16: 2106, 2246.  Workgroups are counted as they are made,
+// of one instance each: 4096 instances of 4 walkers (L = 8, sixteen per compute
+// unit) in lanes with page 16 1143, with 64, the page of a lone workgroup,
+// 2758.
 struct ClassPlan {
   int32_t G = 0, P = 0, count = 0, offset = 0;
   int32_t prod = 0;  // RNG producer wavefront per workgroup
